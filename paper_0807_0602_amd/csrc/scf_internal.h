@@ -70,6 +70,15 @@ hipError_t launch_step_fused(int bx, bool masked, const Chan* chans, const TileD
 hipError_t launch_step_fused2(int bx, bool masked, const Chan* chans, const TileDesc* tiles,
                               int ntiles, const int32_t* first, int grid, float* ws, int src,
                               hipStream_t s);
+// k = 1..4 time steps of a small tile per launch, one thread per node (see k_step_region).  The
+// block's region of nodes is 22 x 23 or 32 x 32; its output tile is 2 (2k - 1) nodes smaller each
+// way.  `one` holds a single channel's constants, its tiles following from the block index; with
+// `tiles` (several channels) both come from the tables.
+enum { kRegionSmall = 0, kRegionLarge = 1, kRegionMaxSteps = 4 };
+inline int region_out_x(int region, int k) { return (region == kRegionSmall ? 22 : 32) - 2 * (2 * k - 1); }
+inline int region_out_y(int region, int k) { return (region == kRegionSmall ? 23 : 32) - 2 * (2 * k - 1); }
+hipError_t launch_step_region(int region, int k, bool masked, const Chan& one, const Chan* chans, const TileDesc* tiles,
+                              int ntiles, float* ws, int src, hipStream_t s);
 // Blocks of the fused step (fuse 1 or 2) that one CU holds at once; 0 if the query fails.
 int resident_blocks_per_cu(int bx, bool masked, int fuse);
 hipError_t launch_step_two_kernel(const Chan* chans, const RowRef* rows, int nrows, float* ws,

@@ -42,9 +42,11 @@ constexpr int kMaxRowsPerGeom = 1 << 20;
 // rows where a channel is taller (each band pays the pipeline's start-up rows once).
 constexpr int kMaxPersistBlocks = 8192;
 constexpr int kMinRange = 16;
+constexpr double kNarrowBlocksPerCu = 7.25;
+constexpr double kNarrowMaxRows = 21.0;
 // Version of the schedule space and kernels in the autotuner cache key (a cached schedule from
 // another version is timed again).
-constexpr int kTuneVersion = 5;
+constexpr int kTuneVersion = 6;
 constexpr int kPlanesPerChannel = 38;   // 2 x 18 population planes + 2 density planes
 
 // Float planes of one channel: populations and densities, plus one for the uint16 codes of a
@@ -182,6 +184,11 @@ struct Engine {
     int grid1 = 0, grid2 = 0;
     int cus = 0;
     int bpc = 0;   // requested blocks per CU of persistent schedules (0: occupancy)
+    // steps per launch of the node-parallel step (0: the row-walking kernels run), its region and,
+    // per step count, its tiles (in d_tiles2() from entry region_first when nchan > 1)
+    int region_k = 0, region = 0;
+    bool narrow = false;   // the two-step list holds 64-lane tiles (see narrow_rows)
+    int region_tiles[scf::kRegionMaxSteps + 1] = {}, region_first[scf::kRegionMaxSteps + 1] = {};
     float tuned_ms = 0.0f;   // time per step of the last autotuned schedule
     hipGraphExec_t g_steps[2] = {nullptr, nullptr};
     hipGraphExec_t g_sample[2] = {nullptr, nullptr};
@@ -247,18 +254,7 @@ struct Engine {
                 }
         }
         if (!(ord & SCF_ORDER_XCD)) return tl;
-        const int n = (int)tl.size();
-        const int per = (n + 7) / 8;
-        std::vector<scf::TileDesc> out((size_t)per * 8);
-        for (int v = 0; v < per * 8; ++v) {
-            const int t = (v & 7) * per + (v >> 3);
-            if (t < n) {
-                out[v] = tl[t];
-            } else {
-                std::memset(&out[v], 0, sizeof out[v]);   // empty tile (ye == yb)
-            }
-        }
-        return out;
+        return deal_to_xcds(tl);
     }
 
     // (channel, band, strip) tiles over strips `stripw` wide, k_c = max(1, round(ny_c / target))
@@ -372,6 +368,92 @@ struct Engine {
         first[nblocks] = (int32_t)tl.size();
     }
 
+    // Schedules that ask for the row-walking kernels as they are: an explicit number of blocks per
+    // CU (below the kernel's occupancy, under a persistent order).
+    bool walk_forced(int bxv, int ord) const {
+        if (bpc <= 0) return false;
+        if (!(ord & SCF_ORDER_PERSIST)) return true;
+        return bpc < scf::resident_blocks_per_cu(bxv, any_masked, 2);
+    }
+
+    // Narrow two-step walk for boxes whose persistent bands would be short (every band pays six
+    // start-up rows): one 64-lane block per tile, dispatched in list order, 7.25 blocks per CU.
+    // Measured, us per step, against the persistent 256-lane bands: 8192 x 130 19.4 for 32.4,
+    // 8192 x 202 26.6 for 36.9, 8192 x 256 (19.6 rows per band) 41.3 for 45.3; 8192 x 300 (23 rows)
+    // 50.9 for 48.9: past about 1.8 M nodes both buffers leave the last-level cache, and the narrow
+    // strips' partial lines cost more than the short bands.
+    double narrow_rows() const {
+        double strip_rows = 0.0;
+        for (const scf_geometry& g : geom) strip_rows += (double)((g.nx + 57) / 58) * g.ny;
+        return std::max(2.0, strip_rows / (kNarrowBlocksPerCu * cus));
+    }
+
+    // The XCD order: block b runs on XCD b mod 8, so the list is permuted to give each XCD a
+    // contiguous eighth (empty tiles pad the last round).
+    static std::vector<scf::TileDesc> deal_to_xcds(const std::vector<scf::TileDesc>& tl) {
+        const int n = (int)tl.size();
+        const int per = (n + 7) / 8;
+        std::vector<scf::TileDesc> out((size_t)per * 8);
+        for (int v = 0; v < per * 8; ++v) {
+            const int t = (v & 7) * per + (v >> 3);
+            if (t < n) {
+                out[v] = tl[t];
+            } else {
+                std::memset(&out[v], 0, sizeof out[v]);   // empty tile (ye == yb)
+            }
+        }
+        return out;
+    }
+
+    int64_t region_max_tiles() const { return 5 * (int64_t)cus; }
+
+    int64_t region_count(int rg, int k) const {
+        const int ox = scf::region_out_x(rg, k), oy = scf::region_out_y(rg, k);
+        int64_t n = 0;
+        for (const scf_geometry& g : geom) n += (int64_t)((g.nx + ox - 1) / ox) * ((g.ny + oy - 1) / oy);
+        return n;
+    }
+
+    // The node-parallel step for boxes that the row walk would spread over too few blocks: a walk's
+    // launch lasts one row iteration (2.3-5 us) per row of its bands plus six, a region's launch
+    // K stages whatever the box.  The most steps per launch whose tiles all run at once, one block
+    // per CU, are the fastest per step (200 x 24: 2.1 us with 75 small regions of 4 steps, 2.8 with
+    // large ones; 4096 x 22: 3.5 us with 187 regions of 3 steps, 5.8 with 456 of 4).  Beyond, two
+    // steps per launch, up to five blocks per CU: at 4096 x 202 (4.9) 15.8 us against 16.9 for the
+    // walk, at 8192 x 202 (9.9) 27.9 against 26.6.
+    void plan_regions(std::vector<scf::TileDesc>& tl, std::vector<scf::TileDesc>& walk) {
+        region_k = 0;
+        struct Pick { int region, k; int64_t most; };
+        const Pick picks[] = {{scf::kRegionSmall, 4, cus}, {scf::kRegionLarge, 4, cus}, {scf::kRegionLarge, 3, cus},
+                              {scf::kRegionLarge, 2, region_max_tiles()}};
+        for (const Pick& p : picks)
+            if (region_count(p.region, p.k) <= p.most) {
+                region = p.region;
+                region_k = p.k;
+                break;
+            }
+        if (!region_k) return;
+        tl.clear();
+        for (int k = 1; k <= region_k; ++k) {
+            const int ox = scf::region_out_x(region, k), oy = scf::region_out_y(region, k);
+            region_first[k] = (int)(walk.size() + tl.size());
+            region_tiles[k] = (int)region_count(region, k);
+            if (nchan == 1) continue;
+            for (int c = 0; c < nchan; ++c)
+                for (int y = 0; y < geom[c].ny; y += oy)
+                    for (int x = 0; x < geom[c].nx; x += ox) {
+                        scf::TileDesc td;
+                        std::memset(&td, 0, sizeof td);
+                        td.chan = c;
+                        td.xb = x;
+                        td.yb = y;
+                        tl.push_back(td);
+                    }
+        }
+        if ((int64_t)walk.size() + (int64_t)tl.size() > lay.max_tiles) region_k = 0;
+        else walk.insert(walk.end(), tl.begin(), tl.end());
+    }
+
     // Blocks of a persistent launch: every CU filled to the kernel's occupancy (a multiple of 8
     // for the XCD order); 0 if the occupancy query fails.
     int persist_blocks(int bxv, int fz, int ord) const {
@@ -392,15 +474,27 @@ struct Engine {
         std::vector<scf::TileDesc> tl, tl2;
         std::vector<int32_t> f1, f2;
         int g1 = 0, g2 = 0;
+        narrow = false;
         if (ord & SCF_ORDER_PERSIST) {
             g1 = persist_blocks(bxv, 1, ord);
             g2 = persist_blocks(bxv, 2, ord);
             if (!g1 || !g2) return fail(SCF_EDEVICE, "occupancy query for the persistent schedule failed");
             make_tiles_persist(bxv, 2, g1, ord, tl, f1);
             make_tiles_persist(strip2(bxv), 6, g2, ord, tl2, f2);
+            narrow = !walk_forced(bxv, ord) && narrow_rows() <= kNarrowMaxRows;
+            if (narrow) {
+                band_tiles(strip2(64), narrow_rows(), tl2);
+                if (ord & SCF_ORDER_XCD) tl2 = deal_to_xcds(tl2);
+            }
         } else {
             tl = make_tiles(bxv, cyv, ord);
             tl2 = make_tiles(strip2(bxv), cyv, ord);
+        }
+        const int n2 = (int)tl2.size();
+        region_k = 0;
+        if (!walk_forced(bxv, ord)) {
+            std::vector<scf::TileDesc> rl;
+            plan_regions(rl, tl2);
         }
         if ((int)tl.size() > lay.max_tiles || (int)tl2.size() > lay.max_tiles)
             return fail(SCF_EINVAL, "tile list exceeds its reserved space");
@@ -414,7 +508,7 @@ struct Engine {
         }
         HIP_TRY(hipStreamSynchronize(stream));
         ntiles = (int)tl.size();
-        ntiles2 = (int)tl2.size();
+        ntiles2 = n2;
         grid1 = g1;
         grid2 = g2;
         bx = bxv;
@@ -423,17 +517,24 @@ struct Engine {
         return SCF_OK;
     }
 
-    // Steps one launch advances from parity src (two with fuse = 2 when n >= 2 are left).
-    int steps_of_launch(int64_t n) const {
-        return (variant == SCF_VARIANT_FUSED && fuse == 2 && n >= 2) ? 2 : 1;
+    // Most steps one launch advances: two with fuse = 2, or the node-parallel step's.
+    int max_steps() const {
+        if (variant != SCF_VARIANT_FUSED || fuse != 2) return 1;
+        return region_k > 0 ? region_k : 2;
     }
 
-    // One launch of `k` (1 or 2) steps reading buffer src and writing src ^ 1.
+    int steps_of_launch(int64_t n) const { return (int)std::min<int64_t>(n, max_steps()); }
+
+    // One launch of `k` <= max_steps() steps reading buffer src and writing src ^ 1.
     hipError_t launch_steps(hipStream_t s, int src, int k) const {
         const bool p = persistent();
+        if (variant == SCF_VARIANT_FUSED && fuse == 2 && region_k > 0)
+            return scf::launch_step_region(region, k, any_masked, chans[0], d_chans(),
+                                           nchan == 1 ? nullptr : d_tiles2() + region_first[k], region_tiles[k], base(),
+                                           src, s);
         if (k == 2)
-            return scf::launch_step_fused2(bx, any_masked, d_chans(), d_tiles2(), ntiles2,
-                                           p ? d_first2() : nullptr, grid2, base(), src, s);
+            return scf::launch_step_fused2(narrow ? 64 : bx, any_masked, d_chans(), d_tiles2(), ntiles2,
+                                           p && !narrow ? d_first2() : nullptr, narrow ? 0 : grid2, base(), src, s);
         if (variant == SCF_VARIANT_TWO_KERNEL)
             return scf::launch_step_two_kernel(d_chans(), d_rows(), lay.nrows, base(), src, s);
         return scf::launch_step_fused(bx, any_masked, d_chans(), d_tiles(), ntiles, p ? d_first() : nullptr,
@@ -442,7 +543,8 @@ struct Engine {
 
     // Launches that advance n steps (each flips the resident buffer once).
     int64_t launches_for(int64_t n) const {
-        return (variant == SCF_VARIANT_FUSED && fuse == 2) ? n / 2 + (n & 1) : n;
+        const int k = max_steps();
+        return n / k + (n % k != 0);
     }
 
     hipError_t launch_obs(hipStream_t s, int record) const {
@@ -648,7 +750,7 @@ struct Engine {
         hipEvent_t e0, e1;
         HIP_TRY(hipEventCreate(&e0));
         HIP_TRY(hipEventCreate(&e1));
-        const int saved_variant = variant;
+        const int saved_variant = variant, saved_fuse = fuse;
         variant = SCF_VARIANT_FUSED;
         bpc = 0;   // persistent candidates fill the CUs to the kernel's occupancy
         struct Cand { int bx, cy, ord, fuse; float ms; };   // ms per time step
@@ -663,19 +765,26 @@ struct Engine {
         for (int ord : {(int)SCF_ORDER_PERSIST, (int)(SCF_ORDER_PERSIST | SCF_ORDER_XCD)})
             for (int bxv : bxs)
                 for (int k = 1; k <= 2; ++k) cands.push_back({bxv, cy, ord, k, 0.0f});
+        // where the node-parallel step runs (see plan_regions) every two-step schedule is that kernel
+        if (region_count(scf::kRegionLarge, 2) <= region_max_tiles()) {
+            cands.erase(std::remove_if(cands.begin(), cands.end(), [](const Cand& c) { return c.fuse == 2; }), cands.end());
+            cands.push_back({256, 16, SCF_ORDER_PERSIST | SCF_ORDER_XCD, 2, 0.0f});
+        }
         // time every candidate with `trial` launches, then the best eight again with four
         // times as many, and keep the fastest of the second round
         auto time_cand = [&](Cand& cd, int launches) -> int {
             int rc = upload_tiles(cd.bx, cd.cy, cd.ord);
             if (rc) return rc;
-            for (int i = 0; i < 2; ++i) (void)launch_steps(stream, cur, cd.fuse);
+            fuse = cd.fuse;
+            const int k = max_steps();
+            for (int i = 0; i < 2; ++i) (void)launch_steps(stream, cur, k);
             (void)hipEventRecord(e0, stream);
-            for (int i = 0; i < launches; ++i) (void)launch_steps(stream, cur, cd.fuse);
+            for (int i = 0; i < launches; ++i) (void)launch_steps(stream, cur, k);
             (void)hipEventRecord(e1, stream);
             if (hipEventSynchronize(e1) != hipSuccess) return fail(SCF_EDEVICE, "autotune timing failed");
             float ms = 0.0f;
             (void)hipEventElapsedTime(&ms, e0, e1);
-            cd.ms = ms / (float)(launches * cd.fuse);
+            cd.ms = ms / (float)(launches * k);
             return SCF_OK;
         };
         int rc = SCF_OK;
@@ -691,7 +800,10 @@ struct Engine {
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         variant = saved_variant;
-        if (rc) return rc;
+        if (rc) {
+            fuse = saved_fuse;
+            return rc;
+        }
         drop_graphs();
         fuse = cands[0].fuse;
         tuned_ms = cands[0].ms;
