@@ -27,6 +27,12 @@ hipError_t output_layer(const float* Z, int width, int rows, const float* W, con
                         float* rowloss, float* dZ, __bf16* dZb, __bf16* dZbT, hipStream_t s);
 hipError_t output_grad(const float* Z, int width, int rows, const float* dY, float* dW, float* db,
                        hipStream_t s);
+// Widths whose whole network one block takes a few rows through (k_predict).
+inline bool predict_fits(int width) { return width <= 256; }
+// Rows of X (raw) to Y and, with `in`, the hull test (hull 0: all rows outside); one launch.
+hipError_t predict(const float* X, int64_t n, int d_in, int width, int depth, const float* mean, const float* stdv,
+                   const float* lo, const float* hi, int hull, const float* theta, const __bf16* Wb, float* Y,
+                   uint8_t* in, hipStream_t s);
 hipError_t loss_sum(const float* rowloss, int rows, float inv_n, float* out, hipStream_t s);
 hipError_t adam(float* theta, const float* grad, float* m1, float* m2, int64_t n, int64_t* step,
                 const float* lr, float b1, float b2, float eps, hipStream_t s);

@@ -36,6 +36,8 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 }
 
 constexpr int kThreads = 256;
+// Predictions of up to this many rows (16 per CU) take 16 rows per block.
+constexpr int64_t kPredictRows16 = 4096;
 
 // Fixed-order block reduction (kThreads threads).
 template <typename T>
@@ -57,9 +59,17 @@ __device__ __forceinline__ T block_sum(T v, T* sh) {
 // k, FP32 accumulation.  One wave per 16 x 16 output tile, four waves per block along n.
 // Lane l holds A[m0 + l%16][k0 + 8(l/16) .. +7] and B[n0 + l%16][k0 + 8(l/16) .. +7] and receives
 // C[m0 + 4(l/16) + i][n0 + l%16], i = 0..3 (layout checked on the device by the GEMM tests).
-// M, N multiples of 16 (N of 64 per block row), K multiple of 32.
+// M, N multiples of 16 (N of 64 per block row), K multiple of 32.  With FRAG, B is stored in
+// fragment order (frag_at) instead: a weight matrix, whose row-major tiles would be read as 16
+// half lines per load.
 // ---------------------------------------------------------------------------------------------
-template <class Epi>
+// Fragment order of an (N x K) operand: the 16 x 32 tiles one after the other along k, each as the
+// 64 lanes' eight values.
+__device__ __forceinline__ int64_t frag_at(int n, int k, int K) {
+    return ((int64_t)(n >> 4) * (K >> 5) + (k >> 5)) * 512 + (((k & 31) >> 3) * 16 + (n & 15)) * 8 + (k & 7);
+}
+
+template <bool FRAG, class Epi>
 __global__ void __launch_bounds__(256)
 k_gemm_nt(const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B, int ldb, int K,
           Epi epi) {
@@ -69,11 +79,11 @@ k_gemm_nt(const __bf16* __restrict__ A, int lda, const __bf16* __restrict__ B, i
     const int n0 = (blockIdx.y * 4 + wave) * 16;
     const int r = lane & 15, g = lane >> 4;
     const __bf16* a = A + (int64_t)(m0 + r) * lda + 8 * g;
-    const __bf16* b = B + (int64_t)(n0 + r) * ldb + 8 * g;
+    const __bf16* b = FRAG ? B + (int64_t)(n0 >> 4) * (K >> 5) * 512 + 8 * lane : B + (int64_t)(n0 + r) * ldb + 8 * g;
     f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int k0 = 0; k0 < K; k0 += 32) {
         const bf8 fa = *reinterpret_cast<const bf8*>(a + k0);
-        const bf8 fb = *reinterpret_cast<const bf8*>(b + k0);
+        const bf8 fb = *reinterpret_cast<const bf8*>(b + (FRAG ? 16 * k0 : k0));
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc, 0, 0, 0);
     }
     epi(m0 + 4 * g, n0 + r, acc);
@@ -293,7 +303,8 @@ __global__ void k_bump64(int64_t* c) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *c = *c + 1;
 }
 
-// BF16 copies of one (n_out x n_in) FP32 weight matrix, row-major and transposed.
+// BF16 copies of one (n_out x n_in) FP32 weight matrix and of its transpose, both in fragment order
+// (frag_at).
 __global__ void __launch_bounds__(kThreads)
 k_shadow(const float* __restrict__ W, int n_out, int n_in, __bf16* __restrict__ Wb,
          __bf16* __restrict__ WbT) {
@@ -301,8 +312,8 @@ k_shadow(const float* __restrict__ W, int n_out, int n_in, __bf16* __restrict__ 
     if (i >= (int64_t)n_out * n_in) return;
     const int o = (int)(i / n_in), k = (int)(i % n_in);
     const __bf16 v = (__bf16)W[i];
-    Wb[i] = v;
-    WbT[(int64_t)k * n_out + o] = v;
+    Wb[frag_at(o, k, n_in)] = v;
+    WbT[frag_at(k, o, n_out)] = v;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -420,6 +431,178 @@ k_init_params(float* __restrict__ theta, int64_t off, int n_out, int n_in, uint6
     theta[off + i] = v;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Whole-network kernels.  A block takes a few rows through every layer: the activations stay in
+// LDS (BF16, the next layer's A operand) and only the weights are read again, from L2.  The layer
+// kernels above spend a launch per layer and write pre-activations and two copies of the
+// activations to memory, of which a prediction needs nothing and a training step only what the
+// weight gradients read.  Each value is computed by the same operations in the same order as
+// there, so the results are the same bit for bit.
+// ---------------------------------------------------------------------------------------------
+// A wave owns 16 NT units; its slice of a layer's weights sits in NT W / 8 registers.
+template <int W, int NT>
+struct Slice {
+    bf8 k[NT][W / 32];
+    __device__ __forceinline__ void load(const __bf16* __restrict__ Wl, int n0) {
+        const __bf16* b = Wl + (int64_t)n0 * W + 8 * (threadIdx.x & 63);   // fragment order
+#pragma unroll
+        for (int j = 0; j < W / 32; ++j)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) k[nt][j] = *reinterpret_cast<const bf8*>(b + nt * 16 * W + 512 * j);
+    }
+};
+
+// acc[mt][nt] = rows 16 mt .. of the block's activations hb (LDS, row stride W + 8: eight lanes'
+// 16-byte reads fall on different banks) times the wave's slice, units 16 nt ...
+template <int W, int MT, int NT>
+__device__ __forceinline__ void layer_mma(const __bf16* hb, const Slice<W, NT>& b, f4 (&acc)[MT][NT]) {
+    const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int j = 0; j < W / 32; ++j)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const bf8 a = *reinterpret_cast<const bf8*>(hb + (mt * 16 + r) * (W + 8) + 32 * j + 8 * g);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b.k[nt][j], acc[mt][nt], 0, 0, 0);
+        }
+}
+
+// First layer (FP32) in the same tiles: acc = xs W1^T + b1 with xs the block's normalised rows and
+// w1 the layer's weights (LDS).
+template <int MT, int NT>
+__device__ __forceinline__ void layer_first(const float (*xs)[kMaxIn + 1], int d_in, const float* w1,
+                                            const float* __restrict__ b1, int u, f4 (&acc)[MT][NT]) {
+    const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const float bias = b1[u + 16 * nt];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = f4{bias, bias, bias, bias};
+    }
+    for (int k = 0; k < d_in; ++k)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const float w = w1[(u + 16 * nt) * d_in + k];
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[mt][nt][i] += xs[mt * 16 + 4 * g + i][k] * w;
+        }
+}
+
+// One row of the output layer by one wave: h (LDS, FP32 activations) times the two output rows,
+// summed as k_output sums them.
+template <int W>
+__device__ __forceinline__ void output_row(const float* h, const float* __restrict__ Wo, float& s0, float& s1) {
+    const int lane = threadIdx.x & 63;
+    s0 = 0.0f;
+    s1 = 0.0f;
+#pragma unroll
+    for (int k = lane; k < W; k += 64) {
+        s0 += h[k] * Wo[k];
+        s1 += h[k] * Wo[W + k];
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        s0 += __shfl_xor(s0, off);
+        s1 += __shfl_xor(s1, off);
+    }
+}
+
+// Prediction: rows [n] of X (raw inputs) to Y and, with `in`, the hull test (`hull` 0: all
+// outside).  16 MT rows per block of W / (16 NT) waves.  The first and last layers' weights wait in
+// LDS with the inputs, so that one trip to memory comes before the first barrier and only the
+// hidden layers' slices after it.  Bound by that chain for few rows (a block's 20 000 cycles: 3600
+// to the inputs, 4400 per hidden layer, half of it the weights' way from L2) and by the vector
+// work of SiLU for many (about 28 instructions per unit, exp and an IEEE division).  256 x 4, 5
+// inputs: 2048 device rows 10.1 us, for 35.9 with a launch per layer; 32064 rows 53 us, for 8 x
+// 62 us.  Weights in fragment order instead of row-major: 2250 cycles to load a layer for 7700.
+template <int W, int MT, int NT>
+__global__ void __launch_bounds__(4 * W / NT)
+k_predict(const float* __restrict__ X, int64_t n, int d_in, int depth, const float* __restrict__ mean,
+          const float* __restrict__ stdv, const float* __restrict__ lo, const float* __restrict__ hi, int hull,
+          const float* __restrict__ theta, const __bf16* __restrict__ Wb, float* __restrict__ Y,
+          uint8_t* __restrict__ in) {
+    constexpr int T = 4 * W / NT, M = 16 * MT, LDF = W + 4;
+    __shared__ __align__(16) float sh[M * LDF];   // first-layer weights, BF16 activations, FP32 ones
+    __shared__ float wo[2 * W + 2];
+    __shared__ float xs[M][kMaxIn + 1];
+    __shared__ uint8_t ok[M][kMaxIn];
+    __bf16* hb = reinterpret_cast<__bf16*>(sh);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+    const int64_t m0 = (int64_t)blockIdx.x * M;
+    const int n0 = wave * 16 * NT, u = n0 + r;
+    const float* bias = theta + (int64_t)W * d_in;   // biases of the current layer
+    const float* out = bias + (int64_t)depth * W + (int64_t)(depth - 1) * W * W;
+    Slice<W, NT> b, next;
+    if (depth > 1) b.load(Wb, n0);
+    float* w1 = sh;
+    const bool staged = W * d_in <= M * LDF;
+    if (staged)
+        for (int i = tid; i < W * d_in; i += T) w1[i] = theta[i];
+    for (int i = tid; i < 2 * W + 2; i += T) wo[i] = out[i];
+    for (int i = tid; i < M * d_in; i += T) {
+        const int m = i / d_in, k = i % d_in;
+        const float v = m0 + m < n ? X[(m0 + m) * d_in + k] : 0.0f;
+        xs[m][k] = m0 + m < n ? (v - mean[k]) / stdv[k] : 0.0f;
+        ok[m][k] = v >= lo[k] && v <= hi[k];
+    }
+    __syncthreads();
+    if (in && tid < M && m0 + tid < n) {
+        uint8_t all = hull ? 1 : 0;
+        for (int k = 0; k < d_in; ++k) all &= ok[tid][k];
+        in[m0 + tid] = all;
+    }
+    f4 acc[MT][NT];
+    layer_first<MT, NT>(xs, d_in, staged ? w1 : theta, bias, u, acc);
+    __syncthreads();
+    for (int l = 0; l + 1 < depth; ++l) {
+        // one unit tile per wave leaves the registers to load a layer ahead
+        if (NT == 1 && l + 2 < depth) next.load(Wb + (int64_t)(l + 1) * W * W, n0);
+        bias += W + (int64_t)W * W;
+        float add[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) add[nt] = bias[u + 16 * nt];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    hb[(mt * 16 + 4 * g + i) * (W + 8) + u + 16 * nt] = (__bf16)silu(acc[mt][nt][i]);
+        __syncthreads();
+        layer_mma<W, MT, NT>(hb, b, acc);
+        if (NT == 1) b = next;
+        else if (l + 2 < depth) b.load(Wb + (int64_t)(l + 1) * W * W, n0);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[mt][nt][i] += add[nt];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sh[(mt * 16 + 4 * g + i) * LDF + u + 16 * nt] = silu(acc[mt][nt][i]);
+    __syncthreads();
+    for (int m = wave; m < M; m += T / 64) {
+        float s0, s1;
+        output_row<W>(sh + m * LDF, wo, s0, s1);
+        if (lane == 0 && m0 + m < n) {
+            Y[2 * (m0 + m)] = s0 + wo[2 * W];
+            Y[2 * (m0 + m) + 1] = s1 + wo[2 * W + 1];
+        }
+    }
+}
+
 inline dim3 grid1(int64_t n) { return dim3((unsigned)((n + kThreads - 1) / kThreads)); }
 
 }  // namespace
@@ -427,7 +610,7 @@ inline dim3 grid1(int64_t n) { return dim3((unsigned)((n + kThreads - 1) / kThre
 hipError_t gemm_forward(const __bf16* Hprev, const __bf16* Wb, const float* bias, int rows, int width,
                         float* Z, __bf16* H, __bf16* HT, hipStream_t s) {
     EpiForward epi{bias, Z, H, HT, width, rows};
-    hipLaunchKernelGGL(k_gemm_nt<EpiForward>, dim3(rows / 16, width / 64), dim3(256), 0, s, Hprev,
+    hipLaunchKernelGGL((k_gemm_nt<true, EpiForward>), dim3(rows / 16, width / 64), dim3(256), 0, s, Hprev,
                        width, Wb, width, width, epi);
     return hipGetLastError();
 }
@@ -435,7 +618,7 @@ hipError_t gemm_forward(const __bf16* Hprev, const __bf16* Wb, const float* bias
 hipError_t gemm_backward(const __bf16* dZb, const __bf16* WbT, const float* Zprev, int rows,
                          int width, float* dZ, __bf16* dZbo, __bf16* dZbTo, hipStream_t s) {
     EpiBackward epi{Zprev, dZ, dZbo, dZbTo, width, rows};
-    hipLaunchKernelGGL(k_gemm_nt<EpiBackward>, dim3(rows / 16, width / 64), dim3(256), 0, s, dZb,
+    hipLaunchKernelGGL((k_gemm_nt<true, EpiBackward>), dim3(rows / 16, width / 64), dim3(256), 0, s, dZb,
                        width, WbT, width, width, epi);
     return hipGetLastError();
 }
@@ -443,9 +626,43 @@ hipError_t gemm_backward(const __bf16* dZb, const __bf16* WbT, const float* Zpre
 hipError_t gemm_weight_grad(const __bf16* dZbT, const __bf16* HT, int rows, int width, float* dW,
                             hipStream_t s) {
     EpiWeightGrad epi{dW, width};
-    hipLaunchKernelGGL(k_gemm_nt<EpiWeightGrad>, dim3(width / 16, width / 64), dim3(256), 0, s, dZbT,
+    hipLaunchKernelGGL((k_gemm_nt<false, EpiWeightGrad>), dim3(width / 16, width / 64), dim3(256), 0, s, dZbT,
                        rows, HT, rows, rows, epi);
     return hipGetLastError();
+}
+
+template <int W, int MT, int NT>
+static hipError_t predict_of(const float* X, int64_t n, int d_in, int depth, const float* mean, const float* stdv,
+                             const float* lo, const float* hi, int hull, const float* theta, const __bf16* Wb, float* Y,
+                             uint8_t* in, hipStream_t s) {
+    hipLaunchKernelGGL((k_predict<W, MT, NT>), dim3((unsigned)((n + 16 * MT - 1) / (16 * MT))), dim3(4 * W / NT), 0, s, X,
+                       n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in);
+    return hipGetLastError();
+}
+
+template <int W>
+static hipError_t predict_w(const float* X, int64_t n, int d_in, int depth, const float* mean, const float* stdv,
+                            const float* lo, const float* hi, int hull, const float* theta, const __bf16* Wb, float* Y,
+                            uint8_t* in, hipStream_t s) {
+    // Few rows: the smallest tile, 16 rows, over as many CUs as there are, one unit tile per wave
+    // (256 units: 16 waves).  More rows than 16 per CU: 32 rows per block of half the waves, two
+    // blocks per CU, so that one's activations overlap the other's products (256 x 4, us per
+    // launch: 5000 rows 16.1, against 25.7 with 64 rows per block; 32064 rows 53, against 59 with
+    // 64 rows and 68 with 32 rows and all the waves).
+    if (n <= kPredictRows16) return predict_of<W, 1, 1>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
+    return predict_of<W, 2, 2>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
+}
+
+hipError_t predict(const float* X, int64_t n, int d_in, int width, int depth, const float* mean, const float* stdv,
+                   const float* lo, const float* hi, int hull, const float* theta, const __bf16* Wb, float* Y,
+                   uint8_t* in, hipStream_t s) {
+    switch (width) {
+        case 64: return predict_w<64>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
+        case 128: return predict_w<128>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
+        case 192: return predict_w<192>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
+        case 256: return predict_w<256>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t first_forward(const float* Xn, int d_in, const float* W, const float* b, int width, int rows,

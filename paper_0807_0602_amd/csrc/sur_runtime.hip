@@ -451,6 +451,27 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
     if (!s || !X || !Y) return set_error(SCF_EINVAL, "NULL argument");
     if (n < 0) return set_error(SCF_EINVAL, "negative row count");
     const int din = s->cfg.d_in;
+    if (scf::sur::predict_fits(s->cfg.width)) {
+        // rows per launch: inputs, outputs and hull flags take the place of the activations
+        const size_t room = 4 * (size_t)s->cfg.max_batch * s->cfg.width * s->cfg.depth - 512;
+        const int64_t most = (int64_t)(room / (4 * (size_t)din + 9));
+        for (int64_t r0 = 0; r0 < n; r0 += most) {
+            const int64_t m = std::min(most, n - r0);
+            char* at = s->ws + s->p.Z;
+            float* Xd = reinterpret_cast<float*>(at);
+            float* Yd = reinterpret_cast<float*>(at + al(4 * (size_t)m * din));
+            uint8_t* in = reinterpret_cast<uint8_t*>(Yd + 2 * m);
+            SUR_TRY(hipMemcpyAsync(Xd, X + r0 * din, sizeof(float) * m * din, hipMemcpyHostToDevice, s->stream));
+            SUR_TRY(scf::sur::predict(Xd, m, din, s->cfg.width, s->cfg.depth, s->at<float>(s->p.mean),
+                                      s->at<float>(s->p.stdv), s->at<float>(s->p.lo), s->at<float>(s->p.hi),
+                                      s->have_stats, s->theta(), s->at<__bf16>(s->p.wb), Yd, in_hull ? in : nullptr,
+                                      s->stream));
+            SUR_TRY(hipMemcpyAsync(Y + 2 * r0, Yd, sizeof(float) * 2 * m, hipMemcpyDeviceToHost, s->stream));
+            if (in_hull) SUR_TRY(hipMemcpyAsync(in_hull + r0, in, (size_t)m, hipMemcpyDeviceToHost, s->stream));
+            SUR_TRY(hipStreamSynchronize(s->stream));
+        }
+        return SCF_OK;
+    }
     for (int64_t r0 = 0; r0 < n; r0 += s->cfg.max_batch) {
         const int m = (int)std::min<int64_t>(s->cfg.max_batch, n - r0);
         int rows = 0;
@@ -483,6 +504,12 @@ int scf_sur_predict_noalloc(scf_sur* s, const float* X, int64_t n, float* Y, uin
                                          " bytes of scratch; the allocation-free prediction has " +
                                          std::to_string(kNoAllocScratchBytes) + " (split the rows over calls)");
     if (!s->scratch_dev) return set_error(SCF_EDEVICE, "no scratch on this device: " + s->scratch_err);
+    if (scf::sur::predict_fits(Wd)) {
+        SUR_TRY(scf::sur::predict(X, n, din, Wd, D, s->at<float>(s->p.mean), s->at<float>(s->p.stdv),
+                                  s->at<float>(s->p.lo), s->at<float>(s->p.hi), s->have_stats, s->theta(),
+                                  s->at<__bf16>(s->p.wb), Y, in_hull, s->stream));
+        return SCF_OK;
+    }
     char* base = static_cast<char*>(s->scratch_dev);
     size_t off = 0;
     auto take = [&](size_t bytes) {
