@@ -10,6 +10,40 @@ namespace sur {
 
 constexpr int kMaxIn = 32;   // largest number of input features
 
+// What a training step's first kernel leaves for its second, per batch row (plane = rows x width):
+// HT[l], dZT[l] the transposed BF16 activations and dz of layer l, dZ[l] the FP32 dz.
+struct TrainWork {
+    float* Xn;
+    __bf16 *HT, *dZT;
+    float *dZ, *Hlast, *dY, *rowloss;
+};
+
+// Rows of a training step: drawn from src_rows stored rows (rng) or the first `rows` of them.
+struct TrainBatch {
+    const float *X, *T, *w;
+    int64_t src_rows;
+    int rng;
+    uint64_t seed;
+};
+
+struct TrainState {
+    float *theta, *grad, *m1, *m2;
+    __bf16 *Wb, *WbT;
+    float* loss;
+    int64_t* step;   // [0] steps done, [1] scratch
+    const float* lr;
+    float b1, b2, eps;
+};
+
+// Networks whose training step is train_pass (two launches): a block's waves own 16 units each and
+// keep every layer's silu' in registers, which ends at 256 units (1024 threads) and four layers.
+// Others take the layer kernels.
+inline bool train_fits(int width, int depth) { return (width == 128 || width == 256) && depth >= 2 && depth <= 4; }
+// Forward, loss and backward over `rows` (a multiple of 64) rows, then one Adam update (update) or
+// the gradient into st.grad; the mean loss into st.loss.
+hipError_t train_pass(const TrainBatch& b, int d_in, int width, int depth, int rows, float inv_n, const float* mean,
+                      const float* stdv, const TrainWork& wk, const TrainState& st, int update, hipStream_t s);
+
 // Launchers, asynchronous on stream s.  Matrices are row-major; "T" names a transposed copy.
 hipError_t gemm_forward(const __bf16* Hprev, const __bf16* Wb, const float* bias, int rows, int width,
                         float* Z, __bf16* H, __bf16* HT, hipStream_t s);

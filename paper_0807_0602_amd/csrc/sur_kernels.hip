@@ -603,6 +603,387 @@ k_predict(const float* __restrict__ X, int64_t n, int d_in, int depth, const flo
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// A training step in two launches.  k_train_rows takes 32 rows through the forward pass, the loss
+// and the backward pass, keeping silu'(z) of every layer in registers; it writes what the weight
+// gradients read: both transposed BF16 operands of every hidden layer, the FP32 dz of every layer
+// and the last activations.  k_train_grads reduces them over the batch, one block per 32 x 32 tile
+// of a hidden matrix or 16 columns of a sum, and applies Adam to what it has just summed (or
+// writes the gradient).  Every sum keeps the order of the layer kernels: a tile's products run
+// through the whole batch in one accumulator, a column's rows in 256 interleaved chains and a tree.
+// Measured, 256 x 4 with 5 inputs and 8192 rows: 42 + 45 us, for 28 launches and 594 us.  The first
+// is bound by its chain of barriers, one block of 16 waves per CU, and by 65 MB written; the second
+// by the 130 MB it reads (22 us for the tiles alone, 27 for the sums alone).
+// ---------------------------------------------------------------------------------------------
+struct TrainData {
+    const float *X, *T, *w;   // stored rows
+    int64_t src_rows;
+    int d_in, rng;            // rng: rows drawn by the hash of (seed, step, row), else row i itself
+    const float *mean, *stdv;
+    uint64_t seed;
+    int64_t* step;            // [0] steps done, [1] the step in progress
+};
+
+template <int W, int D>
+__global__ void __launch_bounds__(4 * W)
+k_train_rows(const TrainData d, const float* __restrict__ theta, const __bf16* __restrict__ Wb,
+             const __bf16* __restrict__ WbT, int rows, float inv_n, TrainWork wk) {
+    constexpr int T = 4 * W, MT = 2, M = 16 * MT, LDF = W + 4;
+    __shared__ __align__(16) float sh[M * LDF];   // first-layer weights, BF16 operands, FP32 activations
+    __shared__ float xs[M][kMaxIn + 1];
+    __shared__ float wo[2 * W + 2], dy[M][2], tw[M][3];
+    __shared__ int64_t row[M];
+    __bf16* hb = reinterpret_cast<__bf16*>(sh);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4;
+    const int m0 = blockIdx.x * M, n0 = wave * 16, u = n0 + r, din = d.d_in;
+    const int64_t plane = (int64_t)rows * W;
+    const float* bias = theta + (int64_t)W * din;
+    const float* out = bias + (int64_t)D * W + (int64_t)(D - 1) * W * W;
+    Slice<W, 1> b, next;
+    if (D > 1) b.load(Wb, n0);
+    if (tid < M) {
+        const int i = m0 + tid;
+        int64_t j = i;
+        if (d.rng) {
+            const uint64_t h = mix64(d.seed ^ mix64((uint64_t)(*d.step) * 0x100000001B3ull + (uint64_t)i));
+            j = (int64_t)(h % (uint64_t)d.src_rows);
+        }
+        row[tid] = j;
+        tw[tid][0] = d.T[2 * j];
+        tw[tid][1] = d.T[2 * j + 1];
+        tw[tid][2] = d.w[j];
+        if (i == 0) d.step[1] = d.step[0] + 1;
+    }
+    const bool staged = W * din <= M * LDF;
+    if (staged)
+        for (int i = tid; i < W * din; i += T) sh[i] = theta[i];
+    for (int i = tid; i < 2 * W + 2; i += T) wo[i] = out[i];
+    __syncthreads();
+    for (int i = tid; i < M * din; i += T) {
+        const int m = i / din, k = i % din;
+        const float v = (d.X[row[m] * din + k] - d.mean[k]) / d.stdv[k];
+        xs[m][k] = v;
+        wk.Xn[(int64_t)(m0 + m) * din + k] = v;
+    }
+    __syncthreads();
+    f4 acc[MT][1], sp[D][MT];
+    layer_first<MT, 1>(xs, din, staged ? sh : theta, bias, u, acc);
+    __syncthreads();
+#pragma unroll
+    for (int l = 0; l < D; ++l) {
+        const bool last = l == D - 1;
+        if (l + 2 < D) next.load(Wb + (int64_t)(l + 1) * W * W, n0);
+        else if (l + 2 == D) next.load(WbT + (int64_t)(D - 2) * W * W, n0);   // first backward product
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            bf4 t;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float z = acc[mt][0][i], s = sigmoid(z), h = z * s;
+                sp[l][mt][i] = s * (1.0f + z * (1.0f - s));
+                const int m = mt * 16 + 4 * g + i;
+                if (last) {
+                    sh[m * LDF + u] = h;
+                } else {
+                    t[i] = (__bf16)h;
+                    hb[m * (W + 8) + u] = t[i];
+                }
+            }
+            if (!last) *reinterpret_cast<bf4*>(wk.HT + l * plane + (int64_t)u * rows + m0 + mt * 16 + 4 * g) = t;
+        }
+        __syncthreads();
+        if (last) break;
+        layer_mma<W, MT, 1>(hb, b, acc);
+        b = next;
+        bias += W + (int64_t)W * W;
+        const float add = bias[u];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[mt][0][i] += add;
+        __syncthreads();
+    }
+    for (int m = wave; m < M; m += T / 64) {
+        float s0, s1;
+        const float* h = sh + m * LDF;
+        output_row<W>(h, wo, s0, s1);
+        for (int k = lane; k < W; k += 64) wk.Hlast[(int64_t)(m0 + m) * W + k] = h[k];
+        const float y0 = s0 + wo[2 * W], y1 = s1 + wo[2 * W + 1];
+        const float r0 = y0 - tw[m][0], r1 = y1 - tw[m][1];
+        const float wm = tw[m][2];
+        const float d0 = wm * r0 * inv_n, d1 = wm * r1 * inv_n;
+        if (lane == 0) {
+            dy[m][0] = d0;
+            dy[m][1] = d1;
+            wk.dY[2 * (m0 + m)] = d0;
+            wk.dY[2 * (m0 + m) + 1] = d1;
+            wk.rowloss[m0 + m] = 0.5f * wm * (r0 * r0 + r1 * r1);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int l = D - 1; l >= 0; --l) {
+        if (l < D - 1) {
+            layer_mma<W, MT, 1>(hb, b, acc);   // dh of layer l
+            b = next;
+            __syncthreads();
+        }
+        if (l >= 2) next.load(WbT + (int64_t)(l - 2) * W * W, n0);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            bf4 t;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m = mt * 16 + 4 * g + i;
+                const float dh = l == D - 1 ? dy[m][0] * wo[u] + dy[m][1] * wo[W + u] : acc[mt][0][i];
+                const float dz = dh * sp[l][mt][i];
+                wk.dZ[l * plane + (int64_t)(m0 + m) * W + u] = dz;
+                t[i] = (__bf16)dz;
+                if (l > 0) hb[m * (W + 8) + u] = t[i];
+            }
+            if (l > 0) *reinterpret_cast<bf4*>(wk.dZT + l * plane + (int64_t)u * rows + m0 + mt * 16 + 4 * g) = t;
+        }
+        if (l > 0) __syncthreads();
+    }
+}
+
+struct AdamArgs {
+    float *theta, *m1, *m2, *grad;   // grad: written instead of an update when update == 0
+    const int64_t* step;             // [1]: the step in progress
+    const float* lr;
+    float b1, b2, eps;
+    int update;
+};
+
+__device__ __forceinline__ float adam_one(const AdamArgs& a, int64_t i, float g, float lr, float c1, float c2) {
+    const float m = a.b1 * a.m1[i] + (1.0f - a.b1) * g;
+    const float v = a.b2 * a.m2[i] + (1.0f - a.b2) * g * g;
+    a.m1[i] = m;
+    a.m2[i] = v;
+    const float ah = m / c1;
+    const float vh = v / c2;
+    float th = a.theta[i];
+    th -= lr * ah / (sqrtf(vh) + a.eps);
+    a.theta[i] = th;
+    return th;
+}
+
+// Sum over the batch of NV values per (row, column), 16 columns and 16 classes of rows per block:
+// the thread of class c sums the rows c + 16 j (mod 256) in chain j, the chains are combined as a
+// tree over the 256 chains would (j and j + 8 first), then the classes.  `load` fetches a row's
+// values and `add` adds them; the loads of U x 16 rows are issued together (the rows come from
+// beyond L2 at 2-3 us a trip; with 16 in flight the sums took 139 us of a 8192-row step).
+template <int NV, int U, class V, class L, class A>
+__device__ __forceinline__ void column_sums(int rows, L load, A add, float (&sum)[NV], float (*sh)[16][NV]) {
+    const int c = threadIdx.x & 15, cls = threadIdx.x >> 4;
+    float a[16][NV];
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+#pragma unroll
+        for (int q = 0; q < NV; ++q) a[j][q] = 0.0f;
+    int m = cls;
+    for (const int end = rows - (rows % (256 * U)); m < end; m += 256 * U) {
+        V v[U][16];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) v[k][j] = load(m + 256 * k + 16 * j);
+        __builtin_amdgcn_sched_barrier(0);   // or the loads are spread over the sums again
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) add(a[j], v[k][j]);
+    }
+    for (; m < rows; m += 256)
+#pragma unroll
+        for (int j = 0; j < 16; ++j)
+            if (m + 16 * j < rows) add(a[j], load(m + 16 * j));
+#pragma unroll
+    for (int s = 8; s > 0; s >>= 1)
+#pragma unroll
+        for (int j = 0; j < s; ++j)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) a[j][q] += a[j + s][q];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) sh[cls][c][q] = a[0][q];
+    __syncthreads();
+    for (int s = 8; s > 0; s >>= 1) {
+        if (cls < s)
+#pragma unroll
+            for (int q = 0; q < NV; ++q) sh[cls][c][q] += sh[cls + s][c][q];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < NV; ++q) sum[q] = sh[0][c][q];
+}
+
+// Blocks: (D - 1) (W / 32)^2 tiles of the hidden matrices; W / 16 column groups for each of the
+// d_in + 1 first-layer sums, the D - 1 hidden biases and the output rows; one for the loss and the
+// output biases.
+template <int W>
+__global__ void __launch_bounds__(256)
+k_train_grads(int D, int d_in, int rows, float inv_n, TrainWork wk, AdamArgs ad, __bf16* __restrict__ Wb,
+              __bf16* __restrict__ WbT, float* __restrict__ loss, int64_t* __restrict__ step) {
+    constexpr int CH = 128, LD = CH + 8;   // eight lanes' 16-byte reads fall on different banks
+    __shared__ __align__(16) __bf16 sa[2][32 * LD], sb[2][32 * LD];
+    __shared__ float fs[16][16][2];
+    __shared__ double ds[kThreads];
+    __shared__ float corr[2];
+    const int tid = threadIdx.x;
+    if (ad.update && tid == 0) {
+        const float t = (float)ad.step[1];
+        corr[0] = 1.0f - powf(ad.b1, t);
+        corr[1] = 1.0f - powf(ad.b2, t);
+    }
+    const float lr = *ad.lr;
+    const int64_t plane = (int64_t)rows * W, hidden = (int64_t)W * W + W, first = (int64_t)W * d_in + W;
+    const int side = W / 32, tiles = (D - 1) * side * side, groups = W / 16;
+    int blk = blockIdx.x;
+    if (blk < tiles) {
+        const int l = 1 + blk / (side * side), o0 = (blk / side % side) * 32, k0 = (blk % side) * 32;
+        const int lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4, wm = (wave & 1) * 16, wn = (wave >> 1) * 16;
+        // chunks of CH batch rows: a thread brings 32 bytes of one row of each operand
+        const int row = tid >> 3, seg = (tid & 7) * 8;
+        const __bf16* pa = wk.dZT + l * plane + (int64_t)(o0 + row) * rows + seg;
+        const __bf16* pb = wk.HT + (l - 1) * plane + (int64_t)(k0 + row) * rows + seg;
+        constexpr int PF = 2;   // chunks in flight
+        const int nc = rows / CH;
+        bf8 ra[PF][2], rb[PF][2];
+        auto fetch = [&](int p, int c) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                ra[p][q] = *reinterpret_cast<const bf8*>(pa + CH * c + 64 * q);
+                rb[p][q] = *reinterpret_cast<const bf8*>(pb + CH * c + 64 * q);
+            }
+        };
+        f4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        // one barrier per chunk: the buffer written next was read before the last barrier
+        auto product = [&](int p, int n) {
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < n; j += 32) {
+                const bf8 fa = *reinterpret_cast<const bf8*>(&sa[p][(wm + r) * LD + j + 8 * g]);
+                const bf8 fb = *reinterpret_cast<const bf8*>(&sb[p][(wn + r) * LD + j + 8 * g]);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa, fb, acc, 0, 0, 0);
+            }
+        };
+        auto stage = [&](int p) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                *reinterpret_cast<bf8*>(&sa[p][row * LD + seg + 64 * q]) = ra[p][q];
+                *reinterpret_cast<bf8*>(&sb[p][row * LD + seg + 64 * q]) = rb[p][q];
+            }
+        };
+        int c0 = 0;
+        if (nc > 0) {
+#pragma unroll
+            for (int p = 0; p < PF; ++p) fetch(p, min(p, nc - 1));
+            for (; c0 + PF <= nc; c0 += PF)
+#pragma unroll
+                for (int p = 0; p < PF; ++p) {
+                    stage(p);
+                    // past the end the last chunk is loaded again: no branch, so the compiler keeps
+                    // count of the loads in flight
+                    fetch(p, min(c0 + p + PF, nc - 1));
+                    product(p, CH);
+                }
+            if (c0 < nc) {
+                stage(0);
+                product(0, CH);
+            }
+        }
+        if (rows % CH) {   // the last 64 rows
+            const bf8 la = *reinterpret_cast<const bf8*>(pa + CH * nc), lb = *reinterpret_cast<const bf8*>(pb + CH * nc);
+            __syncthreads();
+            *reinterpret_cast<bf8*>(&sa[0][row * LD + seg]) = la;
+            *reinterpret_cast<bf8*>(&sb[0][row * LD + seg]) = lb;
+            product(0, 64);
+        }
+        const int64_t at = first + (l - 1) * hidden;
+        const int o = o0 + wm + 4 * g, k = k0 + wn + r;
+        bf4 t;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t q = at + (int64_t)(o + i) * W + k;
+            if (!ad.update) {
+                ad.grad[q] = acc[i];
+                continue;
+            }
+            t[i] = (__bf16)adam_one(ad, q, acc[i], lr, corr[0], corr[1]);
+            Wb[(l - 1) * (int64_t)W * W + frag_at(o + i, k, W)] = t[i];
+        }
+        if (ad.update) *reinterpret_cast<bf4*>(WbT + (l - 1) * (int64_t)W * W + frag_at(k, o, W)) = t;
+        return;
+    }
+    blk -= tiles;
+    __syncthreads();   // corr
+    auto put = [&](int64_t q, float g) {
+        if (!ad.update) ad.grad[q] = g;
+        else (void)adam_one(ad, q, g, lr, corr[0], corr[1]);
+    };
+    const int c = tid & 15;
+    if (blk < groups * (d_in + D)) {
+        // first layer: inputs k < d_in and bias; then the biases of layers 1 .. D - 1
+        const int kind = blk / groups, n = (blk % groups) * 16 + c;
+        float s[1];
+        float (*sh)[16][1] = reinterpret_cast<float (*)[16][1]>(&fs[0][0][0]);
+        if (kind < d_in) {
+            const float* dz = wk.dZ + n;
+            const float* x = wk.Xn + kind;
+            struct V { float dz, x; };
+            column_sums<1, 2, V>(rows, [&](int m) { return V{dz[(int64_t)m * W], x[(int64_t)m * d_in]}; },
+                                 [](float (&a)[1], const V& v) { a[0] += v.dz * v.x; }, s, sh);
+        } else {
+            const float* dz = wk.dZ + (kind - d_in) * plane + n;
+            column_sums<1, 4, float>(rows, [&](int m) { return dz[(int64_t)m * W]; },
+                                     [](float (&a)[1], float v) { a[0] += v; }, s, sh);
+        }
+        if (tid < 16) {
+            if (kind < d_in) put((int64_t)n * d_in + kind, s[0]);
+            else if (kind == d_in) put((int64_t)W * d_in + n, s[0]);
+            else put(first + (kind - d_in - 1) * hidden + (int64_t)W * W + n, s[0]);
+        }
+        return;
+    }
+    blk -= groups * (d_in + D);
+    const int64_t out = first + (D - 1) * hidden;
+    if (blk < groups) {
+        const int k = blk * 16 + c;
+        const float* h = wk.Hlast + k;
+        const float* dy = wk.dY;
+        float s[2];
+        struct V { float h, d0, d1; };
+        column_sums<2, 2, V>(rows, [&](int m) { return V{h[(int64_t)m * W], dy[2 * m], dy[2 * m + 1]}; },
+                             [](float (&a)[2], const V& v) {
+                                 a[0] += v.d0 * v.h;
+                                 a[1] += v.d1 * v.h;
+                             }, s, fs);
+        if (tid < 16) {
+            put(out + k, s[0]);
+            put(out + W + k, s[1]);
+        }
+        return;
+    }
+    float* f = &fs[0][0][0];
+    float b0 = 0.0f, b1 = 0.0f;
+    double e = 0.0;
+#pragma unroll 8
+    for (int m = tid; m < rows; m += kThreads) {
+        b0 += wk.dY[2 * m];
+        b1 += wk.dY[2 * m + 1];
+        e += (double)wk.rowloss[m];
+    }
+    b0 = block_sum(b0, f);
+    b1 = block_sum(b1, f);
+    e = block_sum(e, ds);
+    if (tid == 0) {
+        put(out + 2 * W, b0);
+        put(out + 2 * W + 1, b1);
+        loss[0] = (float)(e * inv_n);
+        if (ad.update) step[0] = step[1];
+    }
+}
+
 inline dim3 grid1(int64_t n) { return dim3((unsigned)((n + kThreads - 1) / kThreads)); }
 
 }  // namespace
@@ -628,6 +1009,33 @@ hipError_t gemm_weight_grad(const __bf16* dZbT, const __bf16* HT, int rows, int 
     EpiWeightGrad epi{dW, width};
     hipLaunchKernelGGL((k_gemm_nt<false, EpiWeightGrad>), dim3(width / 16, width / 64), dim3(256), 0, s, dZbT,
                        rows, HT, rows, rows, epi);
+    return hipGetLastError();
+}
+
+hipError_t train_pass(const TrainBatch& b, int d_in, int W, int D, int rows, float inv_n, const float* mean, const float* stdv,
+                      const TrainWork& wk, const TrainState& st, int update, hipStream_t s) {
+    const TrainData d{b.X, b.T, b.w, b.src_rows, d_in, b.rng, mean, stdv, b.seed, st.step};
+    const dim3 grid(rows / 32), block(4 * W);
+#define ROWS_OF(WW, DD)                                                                                       \
+    case WW * 8 + DD:                                                                                         \
+        hipLaunchKernelGGL((k_train_rows<WW, DD>), grid, block, 0, s, d, st.theta, st.Wb, st.WbT, rows, inv_n, wk); \
+        break
+    switch (W * 8 + D) {
+        ROWS_OF(128, 2); ROWS_OF(128, 3); ROWS_OF(128, 4);
+        ROWS_OF(256, 2); ROWS_OF(256, 3); ROWS_OF(256, 4);
+        default: return hipErrorInvalidValue;
+    }
+#undef ROWS_OF
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const AdamArgs ad{st.theta, st.m1, st.m2, st.grad, st.step, st.lr, st.b1, st.b2, st.eps, update};
+    const int side = W / 32, blocks = (D - 1) * side * side + (W / 16) * (d_in + D + 1) + 1;
+    if (W == 256)
+        hipLaunchKernelGGL(k_train_grads<256>, dim3(blocks), dim3(256), 0, s, D, d_in, rows, inv_n, wk, ad, st.Wb, st.WbT,
+                           st.loss, st.step);
+    else
+        hipLaunchKernelGGL(k_train_grads<128>, dim3(blocks), dim3(256), 0, s, D, d_in, rows, inv_n, wk, ad, st.Wb, st.WbT,
+                           st.loss, st.step);
     return hipGetLastError();
 }
 

@@ -218,8 +218,38 @@ struct scf_sur {
         return e == hipSuccess ? shadows(s) : e;
     }
 
+    // Forward, backward and (update) Adam on `rows` rows of the staged batch or, with `stored`, on a
+    // random minibatch of the stored set; the gradient into grad otherwise.
+    hipError_t train_step(int rows, bool stored, float inv_n, bool update, hipStream_t s) const {
+        if (scf::sur::train_fits(cfg.width, cfg.depth)) {
+            scf::sur::TrainBatch b;
+            b.X = at<float>(stored ? p.Xd : p.Xs);
+            b.T = at<float>(stored ? p.Td : p.Ts);
+            b.w = at<float>(stored ? p.wd : p.wsb);
+            b.src_rows = stored ? n_data : rows;
+            b.rng = stored;
+            b.seed = cfg.seed;
+            // the layer kernels' buffers under other names: pre-activations hold dz, the row-major
+            // activations the transposed dz, the single FP32 dz the last activations
+            const scf::sur::TrainWork wk{at<float>(p.Xn), at<__bf16>(p.HT), at<__bf16>(p.H), at<float>(p.Z),
+                                         at<float>(p.dZ), at<float>(p.dY), at<float>(p.rowloss)};
+            const scf::sur::TrainState st{theta(), grad(), at<float>(p.m1), at<float>(p.m2), at<__bf16>(p.wb),
+                                          at<__bf16>(p.wbt), at<float>(p.loss), step(), at<float>(p.lr), cfg.beta1,
+                                          cfg.beta2, cfg.eps};
+            return scf::sur::train_pass(b, cfg.d_in, cfg.width, cfg.depth, rows, inv_n, at<float>(p.mean),
+                                        at<float>(p.stdv), wk, st, update, s);
+        }
+        hipError_t e = scf::sur::gather(at<float>(stored ? p.Xd : p.Xs), at<float>(stored ? p.Td : p.Ts),
+                                        at<float>(stored ? p.wd : p.wsb), stored ? n_data : rows, cfg.d_in, rows,
+                                        at<float>(p.mean), at<float>(p.stdv), at<float>(p.Xn), at<float>(p.Tb),
+                                        at<float>(p.wbb), stored, cfg.seed, step(), s);
+        if (e == hipSuccess) e = pass(rows, true, inv_n, s);
+        if (e == hipSuccess && update) e = adam_and_shadows(s);
+        return e;
+    }
+
     // Copy an explicit batch (host, n rows) into the staging area, padded to a multiple of 64
-    // rows with zero-weight rows, and normalise it.
+    // rows with zero-weight rows.
     int stage(const float* X, const float* T, const float* w, int n, int* rows_out) {
         const int rows = (n + 63) / 64 * 64;
         if (n < 1 || rows > cfg.max_batch) return set_error(SCF_EINVAL, "batch must have 1..max_batch rows");
@@ -231,9 +261,6 @@ struct scf_sur {
         SUR_TRY(hipMemcpyAsync(at<float>(p.Xs), x.data(), sizeof(float) * x.size(), hipMemcpyHostToDevice, stream));
         SUR_TRY(hipMemcpyAsync(at<float>(p.Ts), t.data(), sizeof(float) * t.size(), hipMemcpyHostToDevice, stream));
         SUR_TRY(hipMemcpyAsync(at<float>(p.wsb), ww.data(), sizeof(float) * ww.size(), hipMemcpyHostToDevice, stream));
-        SUR_TRY(scf::sur::gather(at<float>(p.Xs), at<float>(p.Ts), at<float>(p.wsb), rows, cfg.d_in, rows,
-                                 at<float>(p.mean), at<float>(p.stdv), at<float>(p.Xn), at<float>(p.Tb),
-                                 at<float>(p.wbb), 0, 0, step(), stream));
         SUR_TRY(hipStreamSynchronize(stream));   // the host vectors go out of scope
         *rows_out = rows;
         return SCF_OK;
@@ -392,7 +419,7 @@ int scf_sur_grad(scf_sur* s, const float* X, const float* T, const float* w, int
     int rows = 0;
     int rc = s->stage(X, T, w, n, &rows);
     if (rc) return rc;
-    SUR_TRY(s->pass(rows, true, 1.0f / (float)n, s->stream));
+    SUR_TRY(s->train_step(rows, false, 1.0f / (float)n, false, s->stream));
     if (loss) SUR_TRY(hipMemcpyAsync(loss, s->at<float>(s->p.loss), sizeof(float), hipMemcpyDeviceToHost, s->stream));
     if (grad) SUR_TRY(hipMemcpyAsync(grad, s->grad(), sizeof(float) * s->p.P, hipMemcpyDeviceToHost, s->stream));
     SUR_TRY(hipStreamSynchronize(s->stream));
@@ -404,8 +431,7 @@ int scf_sur_step(scf_sur* s, const float* X, const float* T, const float* w, int
     int rows = 0;
     int rc = s->stage(X, T, w, n, &rows);
     if (rc) return rc;
-    SUR_TRY(s->pass(rows, true, 1.0f / (float)n, s->stream));
-    SUR_TRY(s->adam_and_shadows(s->stream));
+    SUR_TRY(s->train_step(rows, false, 1.0f / (float)n, true, s->stream));
     if (loss) SUR_TRY(hipMemcpyAsync(loss, s->at<float>(s->p.loss), sizeof(float), hipMemcpyDeviceToHost, s->stream));
     SUR_TRY(hipStreamSynchronize(s->stream));
     return SCF_OK;
@@ -424,12 +450,7 @@ int scf_sur_train(scf_sur* s, int64_t steps, int32_t batch, float* last_loss) {
         if (!s->cap) SUR_TRY(hipStreamCreateWithFlags(&s->cap, hipStreamNonBlocking));
         hipGraph_t g = nullptr;
         SUR_TRY(hipStreamBeginCapture(s->cap, hipStreamCaptureModeRelaxed));
-        hipError_t e = scf::sur::gather(s->at<float>(s->p.Xd), s->at<float>(s->p.Td), s->at<float>(s->p.wd),
-                                        s->n_data, s->cfg.d_in, batch, s->at<float>(s->p.mean),
-                                        s->at<float>(s->p.stdv), s->at<float>(s->p.Xn), s->at<float>(s->p.Tb),
-                                        s->at<float>(s->p.wbb), 1, s->cfg.seed, s->step(), s->cap);
-        if (e == hipSuccess) e = s->pass(batch, true, 1.0f / (float)batch, s->cap);
-        if (e == hipSuccess) e = s->adam_and_shadows(s->cap);
+        hipError_t e = s->train_step(batch, true, 1.0f / (float)batch, true, s->cap);
         hipError_t end = hipStreamEndCapture(s->cap, &g);
         if (e != hipSuccess || end != hipSuccess) {
             if (g) (void)hipGraphDestroy(g);
@@ -477,6 +498,8 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
         int rows = 0;
         int rc = s->stage(X + r0 * din, nullptr, nullptr, m, &rows);
         if (rc) return rc;
+        SUR_TRY(scf::sur::normalise(s->at<float>(s->p.Xs), rows, din, rows, s->at<float>(s->p.mean),
+                                    s->at<float>(s->p.stdv), s->at<float>(s->p.Xn), s->stream));
         SUR_TRY(s->pass(rows, false, 1.0f, s->stream));
         SUR_TRY(hipMemcpyAsync(Y + 2 * r0, s->at<float>(s->p.Y), sizeof(float) * 2 * m, hipMemcpyDeviceToHost, s->stream));
         if (in_hull) {
@@ -504,7 +527,13 @@ int scf_sur_predict_noalloc(scf_sur* s, const float* X, int64_t n, float* Y, uin
                                          " bytes of scratch; the allocation-free prediction has " +
                                          std::to_string(kNoAllocScratchBytes) + " (split the rows over calls)");
     if (!s->scratch_dev) return set_error(SCF_EDEVICE, "no scratch on this device: " + s->scratch_err);
-    if (scf::sur::predict_fits(Wd)) {
+    // one launch reads and writes block by block, so outputs that lie over the inputs take the
+    // layer kernels, which read every input first
+    auto apart = [&](const void* q, size_t bytes) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(X), c = reinterpret_cast<uintptr_t>(q);
+        return !q || a + 4 * (size_t)n * din <= c || c + bytes <= a;
+    };
+    if (scf::sur::predict_fits(Wd) && apart(Y, 8 * (size_t)n) && apart(in_hull, (size_t)n)) {
         SUR_TRY(scf::sur::predict(X, n, din, Wd, D, s->at<float>(s->p.mean), s->at<float>(s->p.stdv),
                                   s->at<float>(s->p.lo), s->at<float>(s->p.hi), s->have_stats, s->theta(),
                                   s->at<__bf16>(s->p.wb), Y, in_hull, s->stream));
