@@ -37,11 +37,16 @@ struct Obs3 {
     int32_t flags, reserved;
 };
 
+// The buffer kernels address one component's 19 planes with unsigned 32-bit offsets.
+inline bool fused_fits(int64_t plane) { return (int64_t)19 * plane * (int64_t)sizeof(float) <= (int64_t)UINT32_MAX; }
+
 // `h` is the host copy of the device table entry `c` (launch geometry).
 hipError_t launch_init(const Chan3& h, const Chan3* c, float* ws, hipStream_t s);
-hipError_t launch_step(const Chan3& h, const Chan3* c, float* ws, int src, hipStream_t s);
-// One fused launch per step: 64 x 4 (x, z) tiles walking `cy` rows of y.
-hipError_t launch_step_fused(const Chan3& h, const Chan3* c, float* ws, int src, int cy, hipStream_t s);
+hipError_t launch_step(const Chan3& h, float* ws, int src, hipStream_t s);
+// One fused launch per step (boxes that fused_fits): tiles walking `cy` rows of y.
+hipError_t launch_step_fused(const Chan3& h, float* ws, int src, int cy, int cus, hipStream_t s);
+// The faster form for this box: rows of y per tile of the fused step, 0 for two kernels.
+int best_schedule(const Chan3& h, int cus);
 hipError_t launch_observe(const Chan3& h, const Chan3* c, float* ws, int src, Part3* parts, Obs3* out,
                           hipStream_t s);
 hipError_t launch_pull_out(const Chan3& h, const Chan3* c, float* ws, int src, hipStream_t s);

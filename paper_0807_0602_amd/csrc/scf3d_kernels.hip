@@ -11,6 +11,8 @@
 // Storage: FP32, f[k][i][z][y][pitch], x fastest, pitch = nx rounded up to 64.
 #include "scf3d_internal.h"
 
+#include <algorithm>
+
 // Every multiply-add is written out (no implicit contraction), as in the 2-D kernels.
 #pragma clang fp contract(off)
 
@@ -20,10 +22,10 @@ namespace {
 constexpr int kThreads = 256;
 
 // D3Q19 velocities: rest, six axis links, twelve edge links.
-__constant__ int kCX[19] = {0, 1, -1, 0, 0, 0, 0, 1, -1, 1, -1, 1, -1, 1, -1, 0, 0, 0, 0};
-__constant__ int kCY[19] = {0, 0, 0, 1, -1, 0, 0, 1, -1, -1, 1, 0, 0, 0, 0, 1, -1, 1, -1};
-__constant__ int kCZ[19] = {0, 0, 0, 0, 0, 1, -1, 0, 0, 0, 0, 1, -1, -1, 1, 1, -1, -1, 1};
-__constant__ int kOpp[19] = {0, 2, 1, 4, 3, 6, 5, 8, 7, 10, 9, 12, 11, 14, 13, 16, 15, 18, 17};
+constexpr __constant__ int kCX[19] = {0, 1, -1, 0, 0, 0, 0, 1, -1, 1, -1, 1, -1, 1, -1, 0, 0, 0, 0};
+constexpr __constant__ int kCY[19] = {0, 0, 0, 1, -1, 0, 0, 1, -1, -1, 1, 0, 0, 0, 0, 1, -1, 1, -1};
+constexpr __constant__ int kCZ[19] = {0, 0, 0, 0, 0, 1, -1, 0, 0, 0, 0, 1, -1, -1, 1, 1, -1, -1, 1};
+constexpr __constant__ int kOpp[19] = {0, 2, 1, 4, 3, 6, 5, 8, 7, 10, 9, 12, 11, 14, 13, 16, 15, 18, 17};
 
 // Interaction weights of the links (rest excluded): 1/18 (axis), 1/36 (edge).
 constexpr float kWA = 1.0f / 18.0f;
@@ -37,31 +39,124 @@ __device__ __forceinline__ float sixth(float v) { return __builtin_fmaf(v, kSixt
 
 __device__ __forceinline__ int wrapc(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
-__device__ __forceinline__ bool solid(const Chan3& c, int x, int y, int z) {
-    if ((unsigned)(x - c.x0) >= (unsigned)(c.x1 - c.x0)) return false;
+// v + d on the periodic axis of n nodes, d in {-1, 0, 1}.
+__device__ __forceinline__ int wrap_step(int v, int d, int n) {
+    return d > 0 ? (v == n - 1 ? 0 : v + 1) : d < 0 ? (v == 0 ? n - 1 : v - 1) : v;
+}
+
+__device__ __forceinline__ bool in_x(const Chan3& c, int x) { return (unsigned)(x - c.x0) < (unsigned)(c.x1 - c.x0); }
+
+// Row (y, z) is solid over the capillary; a row whose neighbours may be.
+__device__ __forceinline__ bool wall_row(const Chan3& c, int y, int z) {
     return (c.walls_y && (y == 0 || y == c.ny - 1)) || (c.walls_z && (z == 0 || z == c.nz - 1));
+}
+__device__ __forceinline__ bool near_wall_row(const Chan3& c, int y, int z) {
+    return (c.walls_y && (y <= 1 || y >= c.ny - 2)) || (c.walls_z && (z <= 1 || z >= c.nz - 2));
+}
+
+__device__ __forceinline__ bool solid(const Chan3& c, int x, int y, int z) { return wall_row(c, y, z) && in_x(c, x); }
+
+// Directions (bits) whose component along an axis (0 x, 1 y, 2 z) is d.
+constexpr uint32_t dirs_along(int axis, int d) {
+    constexpr int C[3][19] = {{0, 1, -1, 0, 0, 0, 0, 1, -1, 1, -1, 1, -1, 1, -1, 0, 0, 0, 0},
+                              {0, 0, 0, 1, -1, 0, 0, 1, -1, -1, 1, 0, 0, 0, 0, 1, -1, 1, -1},
+                              {0, 0, 0, 0, 0, 1, -1, 0, 0, 0, 0, 1, -1, -1, 1, 1, -1, -1, 1}};
+    uint32_t m = 0;
+    for (int i = 0; i < 19; ++i) m |= C[axis][i] == d ? 1u << i : 0u;
+    return m;
+}
+
+// Solid-neighbourhood code of node (x, y, z): bit i is set when x + c_i is solid (bit 0: the node
+// itself).  Population i streams in from x - c_i and bounces back when bit opp(i) is set.
+__device__ __forceinline__ uint32_t solid_code(const Chan3& c, int x, int y, int z) {
+    if (!near_wall_row(c, y, z)) return 0u;
+    uint32_t mx = 0, mw = 0;
+#pragma unroll
+    for (int d = -1; d <= 1; ++d) {
+        const int xn = wrap_step(x, d, c.nx), yn = wrap_step(y, d, c.ny), zn = wrap_step(z, d, c.nz);
+        mx |= in_x(c, xn) ? dirs_along(0, d) : 0u;
+        mw |= c.walls_y && (yn == 0 || yn == c.ny - 1) ? dirs_along(1, d) : 0u;
+        mw |= c.walls_z && (zn == 0 || zn == c.nz - 1) ? dirs_along(2, d) : 0u;
+    }
+    return mx & mw;
 }
 
 __device__ __forceinline__ int64_t idx(const Chan3& c, int x, int y, int z) {
     return ((int64_t)z * c.ny + y) * c.pitch + x;
 }
 
-// Populations f_i(x, t) of both components streaming into (x, y, z) from buffer g.
-__device__ __forceinline__ void pull(const float* __restrict__ g, const Chan3& c, int x, int y, int z,
-                                     float f[38]) {
+// Buffer-descriptor access: one descriptor per component of a buffer (19 planes) of at most 4 GiB,
+// unsigned 32-bit byte offsets.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const float* base, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)(uint32_t)bytes, 0x00020000);
+}
+__device__ __forceinline__ float bload(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0));
+}
+__device__ __forceinline__ unsigned row_bytes(const Chan3& c, int y, int z) {
+    return ((unsigned)z * (unsigned)c.ny + (unsigned)y) * (unsigned)c.pitch * 4u;
+}
+
+// The populations of a buffer, by descriptors.
+struct Pops {
+    __amdgpu_buffer_rsrc_t A, B;
+    unsigned Pb;   // plane bytes
+    __device__ __forceinline__ Pops(const Chan3& c, const float* ws, int b) {
+        const float* g = ws + c.off + (int64_t)b * 38 * c.plane;
+        const int64_t bytes = (int64_t)19 * c.plane * 4;
+        A = make_rsrc(g, bytes);
+        B = make_rsrc(g + 19 * c.plane, bytes);
+        Pb = (unsigned)(c.plane * 4);
+    }
+};
+
+// Populations f_i(x, t) of both components streaming into (x, y, z), whose solid code is `code`.
+// UNIFORM: y and z are the same in every lane of the wave, so the row offsets are scalar.
+template <bool UNIFORM>
+__device__ __forceinline__ void pull(const Pops& g, const Chan3& c, int x, int y, int z, uint32_t code, float f[38]) {
+    const unsigned xo[3] = {(unsigned)wrap_step(x, -1, c.nx) * 4u, (unsigned)x * 4u, (unsigned)wrap_step(x, 1, c.nx) * 4u};
+    const unsigned own = row_bytes(c, y, z) + xo[1];
+    if (__any(code != 0u)) {
+#pragma unroll
+        for (int i = 0; i < 19; ++i) {
+            // bounce-back lanes read their own node's opposite direction: the plane goes into the
+            // per-lane offset
+            const unsigned row = row_bytes(c, wrap_step(y, -kCY[i], c.ny), wrap_step(z, -kCZ[i], c.nz)) + (unsigned)i * g.Pb;
+            const unsigned o = i > 0 && ((code >> kOpp[i]) & 1u) ? own + (unsigned)kOpp[i] * g.Pb : xo[1 - kCX[i]] + row;
+            f[i] = bload(g.A, o, 0u);
+            f[19 + i] = bload(g.B, o, 0u);
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 19; ++i) {
+        const unsigned row = row_bytes(c, wrap_step(y, -kCY[i], c.ny), wrap_step(z, -kCZ[i], c.nz)) + (unsigned)i * g.Pb;
+        const unsigned xs = xo[1 - kCX[i]];
+        f[i] = UNIFORM ? bload(g.A, xs, row) : bload(g.A, xs + row, 0u);
+        f[19 + i] = UNIFORM ? bload(g.B, xs, row) : bload(g.B, xs + row, 0u);
+    }
+}
+
+// The same by 64-bit addresses, for components above 4 GiB.
+__device__ __forceinline__ void pull_wide(const float* __restrict__ g, const Chan3& c, int x, int y, int z, uint32_t code,
+                                          float f[38]) {
     const int64_t own = idx(c, x, y, z);
 #pragma unroll
     for (int i = 0; i < 19; ++i) {
-        const int xs = wrapc(x - kCX[i], c.nx), ys = wrapc(y - kCY[i], c.ny), zs = wrapc(z - kCZ[i], c.nz);
-        int pi = i;
-        int64_t src = idx(c, xs, ys, zs);
-        if (i > 0 && solid(c, xs, ys, zs)) {
-            pi = kOpp[i];
-            src = own;
-        }
-        f[i] = g[pi * c.plane + src];
-        f[19 + i] = g[(19 + pi) * c.plane + src];
+        const bool back = i > 0 && ((code >> kOpp[i]) & 1u);
+        const int64_t at = back ? kOpp[i] * c.plane + own
+                                : i * c.plane + idx(c, wrap_step(x, -kCX[i], c.nx), wrap_step(y, -kCY[i], c.ny),
+                                                    wrap_step(z, -kCZ[i], c.nz));
+        f[i] = g[at];
+        f[19 + i] = g[19 * c.plane + at];
     }
+}
+
+template <bool UNIFORM, bool WIDE>
+__device__ __forceinline__ void pull_from(const Chan3& c, const float* ws, int b, int x, int y, int z, uint32_t code,
+                                          float f[38]) {
+    if (WIDE) pull_wide(ws + c.off + (int64_t)b * 38 * c.plane, c, x, y, z, code, f);
+    else pull<UNIFORM>(Pops(c, ws, b), c, x, y, z, code, f);
 }
 
 __device__ __forceinline__ float sum19(const float* f) {
@@ -71,73 +166,112 @@ __device__ __forceinline__ float sum19(const float* f) {
     return s;
 }
 
+// The two-kernel step works on rows: a wave's 64 nodes lie on one row (y, z), so row addresses,
+// periodic wraps in y and z and the rows' wall tests are scalar.  Blocks of four waves cover 256
+// nodes of a row, or several rows where a row has fewer; XCD k (blocks b = k mod 8) takes the k-th
+// contiguous eighth of the rows, so that the densities of the rows around a row, which nine rows
+// read, come from one L2.
+struct Row {
+    int x, y, z;
+    bool in;
+};
+
+__device__ __forceinline__ Row row_of(const Chan3& c) {
+    const int wpr = min((c.nx + 63) / 64, kThreads / 64), per_block = kThreads / 64 / wpr;   // waves a row, rows a block
+    const int segs = (c.nx + kThreads - 1) / kThreads;
+    const int nb = gridDim.x, blk = blockIdx.x, xcd = blk & 7, per = nb >> 3, rem = nb & 7;
+    const int b = xcd * per + min(xcd, rem) + (blk >> 3);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row = (int64_t)(b / segs) * per_block + wave / wpr;
+    Row r;
+    r.x = (b % segs) * kThreads + (wave % wpr) * 64 + (threadIdx.x & 63);
+    r.in = wave < wpr * per_block && row < (int64_t)c.ny * c.nz && r.x < c.nx;
+    r.y = (int)(row % c.ny);
+    r.z = (int)(row / c.ny);
+    return r;
+}
+
+__device__ __forceinline__ int64_t row_at(const Chan3& c, int y, int z) { return ((int64_t)z * c.ny + y) * c.pitch; }
+
+template <bool WIDE>
 __global__ void __launch_bounds__(kThreads)
-k3_density(const Chan3* __restrict__ cp, float* __restrict__ ws, int src) {
-    const Chan3 c = *cp;
-    const int x = blockIdx.x * kThreads + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= c.nx) return;
-    const float* __restrict__ g = ws + c.off + (int64_t)src * 38 * c.plane;
-    float* __restrict__ dn = ws + c.off + 76 * c.plane;
-    float nA = 0.0f, nB = 0.0f;
-    if (!solid(c, x, y, z)) {
-        float f[38];
-        pull(g, c, x, y, z, f);
-        nA = sum19(f);
-        nB = sum19(f + 19);
-    }
-    dn[idx(c, x, y, z)] = nA;
-    dn[c.plane + idx(c, x, y, z)] = nB;
+k3_density(const Chan3 c, float* __restrict__ ws, int src) {
+    const Row r = row_of(c);
+    if (!r.in) return;
+    const uint32_t code = solid_code(c, r.x, r.y, r.z);
+    float* __restrict__ dn = ws + c.off + 76 * c.plane + row_at(c, r.y, r.z);
+    float f[38];
+    pull_from<true, WIDE>(c, ws, src, r.x, r.y, r.z, code, f);
+    dn[r.x] = code & 1u ? 0.0f : sum19(f);
+    dn[c.plane + r.x] = code & 1u ? 0.0f : sum19(f + 19);
+}
+
+// c_i . u and the accumulation of v c_i, without the terms of zero components: the sums of the
+// others come in the same order, so finite values are the same bit for bit.
+__device__ __forceinline__ float signed_of(int c, float v) { return c > 0 ? v : -v; }
+
+__device__ __forceinline__ float along(int i, float ux, float uy, float uz) {
+    float s = 0.0f;
+    bool any = false;
+    if (kCX[i]) { s = signed_of(kCX[i], ux); any = true; }
+    if (kCY[i]) { s = any ? s + signed_of(kCY[i], uy) : signed_of(kCY[i], uy); any = true; }
+    if (kCZ[i]) s = any ? s + signed_of(kCZ[i], uz) : signed_of(kCZ[i], uz);
+    return s;
+}
+
+__device__ __forceinline__ void add_along(int i, float v, float s[3]) {
+    if (kCX[i]) s[0] += signed_of(kCX[i], v);
+    if (kCY[i]) s[1] += signed_of(kCY[i], v);
+    if (kCZ[i]) s[2] += signed_of(kCZ[i], v);
 }
 
 // Deviation-form BGK of one component: D_i = (w_i n - f_i) + n w_i (3 c.u + 9/2 (c.u)^2 - 3/2 u.u)
-// for i > 0, D_0 = -sum D_i; f*_i = f_i + omega D_i.
-__device__ __forceinline__ void relax(const float* f, float n, float ux, float uy, float uz, float om,
-                                      float* __restrict__ out, int64_t P, int64_t at) {
+// for i > 0, D_0 = -sum D_i; out(q, f*) takes f*_i = f_i + omega D_i.
+template <class Out>
+__device__ __forceinline__ void relax(const float* f, float n, float ux, float uy, float uz, float om, const Out& out,
+                                      int qbase) {
     const float usq = __builtin_fmaf(ux, ux, __builtin_fmaf(uy, uy, uz * uz));
-    float D[19];
     float sumD = 0.0f;
 #pragma unroll
     for (int i = 1; i < 19; ++i) {
-        const float cu = (float)kCX[i] * ux + (float)kCY[i] * uy + (float)kCZ[i] * uz;
+        const float cu = along(i, ux, uy, uz);
         const bool axis = i < 7;
         const float w = axis ? kWA : kWE;
         const float odd = axis ? sixth(cu) : 0.5f * sixth(cu);            // 3 w_i c.u
         const float even = w * __builtin_fmaf(4.5f * cu, cu, -1.5f * usq);  // w_i (9/2 cu^2 - 3/2 u^2)
-        D[i] = __builtin_fmaf(n, odd + even, w * n - f[i]);
-        sumD += D[i];
+        const float D = __builtin_fmaf(n, odd + even, w * n - f[i]);
+        sumD += D;
+        out(qbase + i, __builtin_fmaf(om, D, f[i]));
+        if (i % 3 == 0) __builtin_amdgcn_sched_barrier(0);
     }
-    D[0] = -sumD;
-#pragma unroll
-    for (int i = 0; i < 19; ++i) out[i * P + at] = __builtin_fmaf(om, D[i], f[i]);
+    out(qbase, __builtin_fmaf(om, -sumD, f[0]));
 }
 
-__global__ void __launch_bounds__(kThreads)
-k3_collide(const Chan3* __restrict__ cp, float* __restrict__ ws, int src) {
-    const Chan3 c = *cp;
-    const int x = blockIdx.x * kThreads + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= c.nx || solid(c, x, y, z)) return;
-    const float* __restrict__ g = ws + c.off + (int64_t)src * 38 * c.plane;
-    float* __restrict__ d = ws + c.off + (int64_t)(src ^ 1) * 38 * c.plane;
-    const float* __restrict__ nAf = ws + c.off + 76 * c.plane;
-    const float* __restrict__ nBf = nAf + c.plane;
-    float f[38];
-    pull(g, c, x, y, z, f);
-    const float nA = sum19(f), nB = sum19(f + 19);
+// Forces, common velocity and collision of a node with pulled populations f and densities nA, nB;
+// out(q, v) takes population q (B's from 19), neighbour(i, a, b) gives the densities at x + c_i.  The
+// scheduling barriers keep the neighbour loads and the two relaxations from being spread over each
+// other: the walk holds two slices of populations, and its registers decide how many blocks a CU
+// takes.
+template <class Out, class N>
+__device__ __forceinline__ void collide(const Chan3& c, const float* f, float nA, float nB, uint32_t code, const Out& out,
+                                        N neighbour) {
     float jA[3] = {0.0f, 0.0f, 0.0f}, jB[3] = {0.0f, 0.0f, 0.0f};
     float sA[3] = {0.0f, 0.0f, 0.0f}, sB[3] = {0.0f, 0.0f, 0.0f}, sw[3] = {0.0f, 0.0f, 0.0f};
+    if (__any(code != 0u)) {
+#pragma unroll
+        for (int i = 1; i < 19; ++i) add_along(i, (code >> i) & 1u ? (i < 7 ? kWA : kWE) : 0.0f, sw);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 1; i < 19; ++i) {
-        const float cx = (float)kCX[i], cy = (float)kCY[i], cz = (float)kCZ[i];
-        jA[0] += cx * f[i]; jA[1] += cy * f[i]; jA[2] += cz * f[i];
-        jB[0] += cx * f[19 + i]; jB[1] += cy * f[19 + i]; jB[2] += cz * f[19 + i];
-        const int xn = wrapc(x + kCX[i], c.nx), yn = wrapc(y + kCY[i], c.ny), zn = wrapc(z + kCZ[i], c.nz);
-        const int64_t nb = idx(c, xn, yn, zn);
+        add_along(i, f[i], jA);
+        add_along(i, f[19 + i], jB);
         const float w = i < 7 ? kWA : kWE;
-        const float a = w * nAf[nb], b = w * nBf[nb];
-        const float s = solid(c, xn, yn, zn) ? w : 0.0f;
-        sA[0] += a * cx; sA[1] += a * cy; sA[2] += a * cz;
-        sB[0] += b * cx; sB[1] += b * cy; sB[2] += b * cz;
-        sw[0] += s * cx; sw[1] += s * cy; sw[2] += s * cz;
+        float a, b;
+        neighbour(i, a, b);
+        add_along(i, w * a, sA);
+        add_along(i, w * b, sB);
+        if (i % 6 == 0) __builtin_amdgcn_sched_barrier(0);
     }
     // accelerations a_k = F_k / n_k
     float aA[3], aB[3];
@@ -150,86 +284,87 @@ k3_collide(const Chan3* __restrict__ cp, float* __restrict__ ws, int src) {
     float U[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) U[q] = __builtin_fmaf(c.wm[0], jA[q], c.wm[1] * jB[q]) * inv;
-    const int64_t at = idx(c, x, y, z);
     relax(f, nA, __builtin_fmaf(c.tm[0], aA[0], U[0]), __builtin_fmaf(c.tm[0], aA[1], U[1]),
-          __builtin_fmaf(c.tm[0], aA[2], U[2]), c.omega[0], d, c.plane, at);
+          __builtin_fmaf(c.tm[0], aA[2], U[2]), c.omega[0], out, 0);
+    __builtin_amdgcn_sched_barrier(0);
     relax(f + 19, nB, __builtin_fmaf(c.tm[1], aB[0], U[0]), __builtin_fmaf(c.tm[1], aB[1], U[1]),
-          __builtin_fmaf(c.tm[1], aB[2], U[2]), c.omega[1], d + 19 * c.plane, c.plane, at);
+          __builtin_fmaf(c.tm[1], aB[2], U[2]), c.omega[1], out, 19);
+}
+
+template <bool WIDE, bool NT>
+__global__ void __launch_bounds__(kThreads)
+k3_collide(const Chan3 c, float* __restrict__ ws, int src) {
+    const Row r = row_of(c);
+    if (!r.in) return;
+    const int x = r.x, y = r.y, z = r.z;
+    const uint32_t code = solid_code(c, x, y, z);
+    if (code & 1u) return;
+    float* __restrict__ d = ws + c.off + (int64_t)(src ^ 1) * 38 * c.plane + row_at(c, y, z);
+    const float* __restrict__ nAf = ws + c.off + 76 * c.plane;
+    const int xs[3] = {wrap_step(x, -1, c.nx), x, wrap_step(x, 1, c.nx)};
+    float f[38];
+    pull_from<true, WIDE>(c, ws, src, x, y, z, code, f);
+    const float nA = sum19(f), nB = sum19(f + 19);
+    collide(c, f, nA, nB, code,
+            [&](int q, float v) {
+                if (NT) __builtin_nontemporal_store(v, d + q * c.plane + x);
+                else d[q * c.plane + x] = v;
+            },
+            [&](int i, float& a, float& b) {
+                const float* n = nAf + row_at(c, wrap_step(y, kCY[i], c.ny), wrap_step(z, kCZ[i], c.nz));
+                a = n[xs[1 + kCX[i]]];
+                b = n[c.plane + xs[1 + kCX[i]]];
+            });
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fused 3-D step.  A block of BX x BZ threads owns the columns x in [xb, xb + BX), z in
-// [zb, zb + BZ) and walks rows y upward through [yb, ye).  Iteration `it` pulls one y-slice of
-// the tile plus its one-node halo ring in x and z (the ring's nodes are pulled by the first
-// 2 (BX + 2) + 2 BZ threads), writes the slice's densities into a 4-slot LDS ring, and after
-// one barrier collides the previous slice, whose populations were kept in registers: all 18
-// neighbour densities of a node come from three ring slots.  The first and last slices pulled
-// are density-only halos.  A slot written at iteration it+1 was last read by the collision of
-// iteration it-1, finished by every thread before the barrier of iteration it.
+// Fused 3-D step (the walk).  A block of BX x BZ threads (BX a multiple of 64) owns the columns x in
+// [xb, xb + BX), z in [zb, zb + BZ) and walks rows y upward through [yb, ye).  Iteration `it` pulls
+// one y-slice of the tile plus its one-node halo ring in x and z, writes the slice's densities into
+// a 4-slot LDS ring, and after one barrier collides the previous slice, whose populations were kept
+// in registers: all 18 neighbour densities of a node come from three ring slots.  The first and
+// last slices pulled are density-only halos.  A slot written at iteration it+1 was last read by the
+// collision of iteration it-1, finished by every thread before the barrier of iteration it.
+//
+// A wave's 64 nodes lie on one row (y, z), so the row offsets of a pull, its periodic wraps and the
+// wall tests of its rows are scalar; per lane there are three byte offsets (x - 1, x, x + 1).  The
+// ring's z rows are pulled by waves 0 .. 2 BX / 64 - 1, its x columns and corners by the next wave.
+// Bound by the lines that reach L2 from beyond it (about 5.6 TB/s): the node's own 304 bytes, the
+// z rows and x columns of the ring.  Two slices of populations take 76 registers; the rest fits into
+// 128, which lets 16 waves share a CU (157 registers and three blocks of 64 x 4 before: 1.52 ms per
+// step of 512 x 182 x 182, 11.2 GLUPS; now 1.18 ms, 14.3).
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ bool in_x(const Chan3& c, int x) { return (unsigned)(x - c.x0) < (unsigned)(c.x1 - c.x0); }
-
-// True if a solid node may lie among (x, y, z) and its 18 neighbours (periodic in x).
-__device__ __forceinline__ bool near_solid(const Chan3& c, int x, int y, int z) {
-    if (!in_x(c, wrapc(x - 1, c.nx)) && !in_x(c, x) && !in_x(c, wrapc(x + 1, c.nx))) return false;
-    return (c.walls_y && (y <= 1 || y >= c.ny - 2)) || (c.walls_z && (z <= 1 || z >= c.nz - 2));
+// A value the compiler may not reason about: keeps what is derived from it inside the loop, where
+// recomputing it costs a few instructions and holding it a register for the whole walk.
+__device__ __forceinline__ int here_s(int v) {
+    v = __builtin_amdgcn_readfirstlane(v);
+    asm volatile("" : "+s"(v));
+    return v;
+}
+__device__ __forceinline__ int here_v(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
 }
 
-// Buffer-descriptor access for the fused step: one descriptor per component of the source buffer
-// (19 planes, at most 4 GiB, checked by the host), unsigned 32-bit byte offsets, plane offsets in
-// scalar registers.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const float* base, int64_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)(uint32_t)bytes, 0x00020000);
-}
-__device__ __forceinline__ float bload(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0));
-}
-
-__device__ __forceinline__ unsigned idx32(const Chan3& c, int x, int y, int z) {
-    return ((unsigned)z * (unsigned)c.ny + (unsigned)y) * (unsigned)c.pitch + (unsigned)x;
+// Densities of a node pulled for its densities only (0 on solid nodes).
+template <bool UNIFORM>
+__device__ __forceinline__ void halo_node(const Pops& g, const Chan3& c, int x, int y, int z, float& nA, float& nB) {
+    const uint32_t code = solid_code(c, x, y, z);
+    float h[38];
+    pull<UNIFORM>(g, c, x, y, z, code, h);
+    nA = code & 1u ? 0.0f : sum19(h);
+    nB = code & 1u ? 0.0f : sum19(h + 19);
 }
 
-// As pull, through the descriptors rA, rB of the two components (Pb = plane bytes); WALLS adds
-// the bounce-back tests.
-template <bool WALLS>
-__device__ __forceinline__ void pull_buf(__amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rB, unsigned Pb,
-                                         const Chan3& c, int x, int y, int z, float f[38]) {
-    const unsigned own = idx32(c, x, y, z) * 4u;
-#pragma unroll
-    for (int i = 0; i < 19; ++i) {
-        const int xs = wrapc(x - kCX[i], c.nx), ys = wrapc(y - kCY[i], c.ny), zs = wrapc(z - kCZ[i], c.nz);
-        const unsigned off = idx32(c, xs, ys, zs) * 4u;
-        if (WALLS && i > 0) {
-            // bounce-back lanes read their own node's opposite direction: the plane goes into the
-            // per-lane offset so the scalar offset stays uniform
-            const unsigned o = solid(c, xs, ys, zs) ? own + (unsigned)kOpp[i] * Pb : off + (unsigned)i * Pb;
-            f[i] = bload(rA, o, 0u);
-            f[19 + i] = bload(rB, o, 0u);
-        } else {
-            f[i] = bload(rA, off, (unsigned)i * Pb);
-            f[19 + i] = bload(rB, off, (unsigned)i * Pb);
-        }
-    }
-}
-
-__device__ __forceinline__ void pull_any(__amdgpu_buffer_rsrc_t rA, __amdgpu_buffer_rsrc_t rB, unsigned Pb,
-                                         const Chan3& c, int x, int y, int z, float f[38]) {
-    if (near_solid(c, x, y, z))
-        pull_buf<true>(rA, rB, Pb, c, x, y, z, f);
-    else
-        pull_buf<false>(rA, rB, Pb, c, x, y, z, f);
-}
-
-template <int BX, int BZ>
-__global__ void __launch_bounds__(BX * BZ)
-k3_fused(const Chan3* __restrict__ cp, float* __restrict__ ws, int src, int cy) {
-    constexpr int SX = BX + 2, SZ = BZ + 2;
-    constexpr int NH = 2 * SX + 2 * BZ;   // halo ring of the x-z tile
-    static_assert(NH <= BX * BZ, "one thread per halo node");
+template <int BX, int BZ, bool NT>
+__global__ void __launch_bounds__(BX * BZ) __attribute__((amdgpu_waves_per_eu(4)))
+k3_fused(const Chan3 c, float* __restrict__ ws, int src, int cy) {
+    constexpr int SX = BX + 2, SZ = BZ + 2, WX = BX / 64, NX = 2 * SZ;   // NX: x columns and corners
+    static_assert(BX % 64 == 0 && NX <= 64 && BZ * WX > 2 * WX, "one wave for the columns after the z rows");
     __shared__ float sn[2][4][SZ][SX];
-    const Chan3 c = *cp;
-    const int tid = threadIdx.x;
-    const int tx = tid % BX, tz = tid / BX;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tz = wave / WX, tx = (wave % WX) * 64 + lane;
     // Workgroups are dispatched to the eight XCDs in turn (block b to XCD b mod 8), each XCD with
     // its own L2.  Give XCD k the k-th contiguous eighth of the tiles (x fastest, then z, then
     // the row chunk), so that the tiles whose halos overlap share one L2.
@@ -243,100 +378,67 @@ k3_fused(const Chan3* __restrict__ cp, float* __restrict__ ws, int src, int cy) 
     // as needed when the box is narrower than the tile), so the LDS neighbours of every active
     // column are the true periodic neighbours; only active threads collide and store.
     const bool act = xb + tx < c.nx && zb + tz < c.nz;
-    const int x = (xb + tx) % c.nx, z = (zb + tz) % c.nz;
-    // halo node of this thread (ring position h = tid), in tile coordinates (hx, hz) in [0, SX) x [0, SZ)
-    int hx = 0, hz = 0;
-    if (tid < SX) {
-        hx = tid; hz = 0;
-    } else if (tid < 2 * SX) {
-        hx = tid - SX; hz = SZ - 1;
-    } else if (tid < 2 * SX + BZ) {
-        hx = 0; hz = 1 + tid - 2 * SX;
-    } else {
-        hx = SX - 1; hz = 1 + tid - 2 * SX - BZ;
-    }
-    const int hxg = (xb - 1 + hx + c.nx) % c.nx, hzg = (zb - 1 + hz + c.nz) % c.nz;
-    const bool halo = tid < NH;
-    const int64_t comp_bytes = (int64_t)19 * c.plane * 4;
-    const float* gsrc = ws + c.off + (int64_t)src * 38 * c.plane;
-    const __amdgpu_buffer_rsrc_t rA = make_rsrc(gsrc, comp_bytes);
-    const __amdgpu_buffer_rsrc_t rB = make_rsrc(gsrc + 19 * c.plane, comp_bytes);
-    const unsigned Pb = (unsigned)(c.plane * 4);
-    float* __restrict__ d = ws + c.off + (int64_t)(src ^ 1) * 38 * c.plane;
+    const int x0 = (xb + tx) % c.nx, z0 = (zb + tz) % c.nz;
+    // this wave's part of the halo ring: a stretch of a z row (UNIFORM), the x columns, or none
+    const int part = wave < 2 * WX ? 0 : wave == 2 * WX ? 1 : 2;
+    const int hz = part == 0 ? (wave < WX ? 0 : SZ - 1) : lane < SZ ? lane : lane - SZ;
+    const int hx = part == 0 ? tx + 1 : lane < SZ ? 0 : SX - 1;
+    const Pops g(c, ws, src), d(c, ws, src ^ 1);
     float q[38];
 #pragma unroll
     for (int i = 0; i < 38; ++i) q[i] = 0.0f;
     float qA = 0.0f, qB = 0.0f;
+    uint32_t qcode = 0;
     int y = wrapc(yb - 1, c.ny);
     const int niter = ye - yb + 2;
     for (int it = 0; it < niter; ++it) {
         const int slot = it & 3;
         // the halo ring first, so that its registers are free again before the slice's own pull
-        if (halo) {
-            float h[38];
-            float hA = 0.0f, hB = 0.0f;
-            if (!solid(c, hxg, y, hzg)) {
-                pull_any(rA, rB, Pb, c, hxg, y, hzg, h);
-                hA = sum19(h);
-                hB = sum19(h + 19);
-            }
+        if (part < 2 && (part == 0 || lane < NX)) {
+            const int xh = (xb - 1 + here_v(hx) + c.nx) % c.nx;
+            float hA, hB;
+            if (part == 0) halo_node<true>(g, c, xh, y, (zb - 1 + here_s(hz) + c.nz) % c.nz, hA, hB);
+            else halo_node<false>(g, c, xh, y, (zb - 1 + here_v(hz) + c.nz) % c.nz, hA, hB);
             sn[0][slot][hz][hx] = hA;
             sn[1][slot][hz][hx] = hB;
         }
+        const int x = here_v(x0), z = here_s(z0);
         float p[38];
         float nA = 0.0f, nB = 0.0f;
-        const bool sol = solid(c, x, y, z);
-        pull_any(rA, rB, Pb, c, x, y, z, p);
-        if (!sol) {
+        const uint32_t code = solid_code(c, x, y, z);
+        pull<true>(g, c, x, y, z, code, p);
+        if (!(code & 1u)) {
             nA = sum19(p);
             nB = sum19(p + 19);
         }
         sn[0][slot][tz + 1][tx + 1] = nA;
         sn[1][slot][tz + 1][tx + 1] = nB;
         __syncthreads();
-        const int yc = y == 0 ? c.ny - 1 : y - 1;   // the slice pulled one iteration ago
-        if (it >= 2 && act && !solid(c, x, yc, z)) {
-            const int sy[3] = {(it - 2) & 3, (it - 1) & 3, slot};   // slices yc - 1, yc, yc + 1
-            float jA[3] = {0.0f, 0.0f, 0.0f}, jB[3] = {0.0f, 0.0f, 0.0f};
-            float sA[3] = {0.0f, 0.0f, 0.0f}, sB[3] = {0.0f, 0.0f, 0.0f}, sw[3] = {0.0f, 0.0f, 0.0f};
-            const bool nw = near_solid(c, x, yc, z);
-#pragma unroll
-            for (int i = 1; i < 19; ++i) {
-                const float cx = (float)kCX[i], cyf = (float)kCY[i], cz = (float)kCZ[i];
-                jA[0] += cx * q[i]; jA[1] += cyf * q[i]; jA[2] += cz * q[i];
-                jB[0] += cx * q[19 + i]; jB[1] += cyf * q[19 + i]; jB[2] += cz * q[19 + i];
-                const int s = sy[kCY[i] + 1];
-                const float w = i < 7 ? kWA : kWE;
-                const float a = w * sn[0][s][tz + 1 + kCZ[i]][tx + 1 + kCX[i]];
-                const float b = w * sn[1][s][tz + 1 + kCZ[i]][tx + 1 + kCX[i]];
-                sA[0] += a * cx; sA[1] += a * cyf; sA[2] += a * cz;
-                sB[0] += b * cx; sB[1] += b * cyf; sB[2] += b * cz;
-                if (nw) {
-                    const float so = solid(c, wrapc(x + kCX[i], c.nx), wrapc(yc + kCY[i], c.ny),
-                                           wrapc(z + kCZ[i], c.nz)) ? w : 0.0f;
-                    sw[0] += so * cx; sw[1] += so * cyf; sw[2] += so * cz;
-                }
-            }
-            float aA[3], aB[3];
+        const int yc = here_s(y == 0 ? c.ny - 1 : y - 1);   // the slice pulled one iteration ago
+        if (it >= 2 && act && !(qcode & 1u)) {
+            const float* lA[3];
+            const float* lB[3];   // this node in slices yc - 1, yc, yc + 1
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                aA[k] = __builtin_fmaf(-c.G, sB[k], -(c.gw[0] * sw[k]));
-                aB[k] = __builtin_fmaf(-c.G, sA[k], -(c.gw[1] * sw[k]));
+                lA[k] = &sn[0][(it + 2 + k) & 3][tz + 1][tx + 1];
+                lB[k] = &sn[1][(it + 2 + k) & 3][tz + 1][tx + 1];
             }
-            const float inv = 1.0f / __builtin_fmaf(c.wm[0], qA, c.wm[1] * qB);
-            float U[3];
-#pragma unroll
-            for (int k = 0; k < 3; ++k) U[k] = __builtin_fmaf(c.wm[0], jA[k], c.wm[1] * jB[k]) * inv;
-            const int64_t at = idx(c, x, yc, z);
-            relax(q, qA, __builtin_fmaf(c.tm[0], aA[0], U[0]), __builtin_fmaf(c.tm[0], aA[1], U[1]),
-                  __builtin_fmaf(c.tm[0], aA[2], U[2]), c.omega[0], d, c.plane, at);
-            relax(q + 19, qB, __builtin_fmaf(c.tm[1], aB[0], U[0]), __builtin_fmaf(c.tm[1], aB[1], U[1]),
-                  __builtin_fmaf(c.tm[1], aB[2], U[2]), c.omega[1], d + 19 * c.plane, c.plane, at);
+            const unsigned row = row_bytes(c, yc, z);
+            collide(c, q, qA, qB, qcode,
+                    [&](int k, float v) {
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), k < 19 ? d.A : d.B, x * 4,
+                                                              (int)(row + (unsigned)(k < 19 ? k : k - 19) * d.Pb), NT ? 2 : 0);
+                    },
+                    [&](int i, float& a, float& b) {
+                        a = lA[kCY[i] + 1][kCZ[i] * SX + kCX[i]];
+                        b = lB[kCY[i] + 1][kCZ[i] * SX + kCX[i]];
+                    });
         }
 #pragma unroll
         for (int i = 0; i < 38; ++i) q[i] = p[i];
         qA = nA;
         qB = nB;
+        qcode = code;
         y = y == c.ny - 1 ? 0 : y + 1;
     }
 }
@@ -377,7 +479,7 @@ k3_pull_out(const Chan3* __restrict__ cp, float* __restrict__ ws, int src) {
     float* __restrict__ o = ws + c.off + (int64_t)(src ^ 1) * 38 * c.plane;
     float f[38];
     const bool sol = solid(c, x, y, z);
-    if (!sol) pull(g, c, x, y, z, f);
+    if (!sol) pull_wide(g, c, x, y, z, solid_code(c, x, y, z), f);
     const int64_t at = idx(c, x, y, z);
 #pragma unroll
     for (int i = 0; i < 38; ++i) o[i * c.plane + at] = sol ? 0.0f : f[i];
@@ -494,7 +596,39 @@ k3_obs_final(const Chan3* __restrict__ cp, const float* __restrict__ ws, const P
     }
 }
 
+// Blocks of the row kernels (row_of).
+int row_blocks(const Chan3& c) {
+    const int wpr = std::min((c.nx + 63) / 64, kThreads / 64), per_block = kThreads / 64 / wpr;
+    const int64_t rows = (int64_t)c.ny * c.nz, segs = (c.nx + kThreads - 1) / kThreads;
+    return (int)((rows + per_block - 1) / per_block * segs);
+}
+
 dim3 grid_of(const Chan3& c) { return dim3((c.nx + kThreads - 1) / kThreads, c.ny, c.nz); }
+
+// Both buffers' nodes beyond the 256 MB last-level cache: the stores of a step then go past L2,
+// which keeps the walk's halos (512 x 182 x 182: 1.39 ms per step for 1.49), and cost boxes that
+// fit what the next step would have found (200 x 60 x 60: 72 us for 65).
+bool streams(const Chan3& c) { return (int64_t)304 * c.nx * c.ny * c.nz > ((int64_t)256 << 20); }
+
+bool wide(const Chan3& c) { return !fused_fits(c.plane); }
+
+void density(const Chan3& h, float* ws, int src, hipStream_t s) {
+    if (wide(h)) hipLaunchKernelGGL(k3_density<true>, dim3(row_blocks(h)), dim3(kThreads), 0, s, h, ws, src);
+    else hipLaunchKernelGGL(k3_density<false>, dim3(row_blocks(h)), dim3(kThreads), 0, s, h, ws, src);
+}
+
+int64_t walk_tiles(const Chan3& c, int bx, int bz, int cy) {
+    return (int64_t)((c.nx + bx - 1) / bx) * ((c.nz + bz - 1) / bz) * ((c.ny + cy - 1) / cy);
+}
+
+template <int BX, int BZ>
+hipError_t launch_walk(const Chan3& h, float* ws, int src, int cy, hipStream_t s) {
+    const int64_t n = walk_tiles(h, BX, BZ, cy);
+    if (n > INT32_MAX) return hipErrorInvalidConfiguration;
+    if (streams(h)) hipLaunchKernelGGL((k3_fused<BX, BZ, true>), dim3((unsigned)n), dim3(BX * BZ), 0, s, h, ws, src, cy);
+    else hipLaunchKernelGGL((k3_fused<BX, BZ, false>), dim3((unsigned)n), dim3(BX * BZ), 0, s, h, ws, src, cy);
+    return hipGetLastError();
+}
 
 }  // namespace
 
@@ -503,26 +637,73 @@ hipError_t launch_init(const Chan3& h, const Chan3* c, float* ws, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_step(const Chan3& h, const Chan3* c, float* ws, int src, hipStream_t s) {
-    hipLaunchKernelGGL(k3_density, grid_of(h), dim3(kThreads), 0, s, c, ws, src);
+hipError_t launch_step(const Chan3& h, float* ws, int src, hipStream_t s) {
+    density(h, ws, src, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k3_collide, grid_of(h), dim3(kThreads), 0, s, c, ws, src);
+    const dim3 grid(row_blocks(h)), block(kThreads);
+    if (wide(h)) hipLaunchKernelGGL((k3_collide<true, true>), grid, block, 0, s, h, ws, src);
+    else if (streams(h)) hipLaunchKernelGGL((k3_collide<false, true>), grid, block, 0, s, h, ws, src);
+    else hipLaunchKernelGGL((k3_collide<false, false>), grid, block, 0, s, h, ws, src);
     return hipGetLastError();
 }
 
-hipError_t launch_step_fused(const Chan3& h, const Chan3* c, float* ws, int src, int cy, hipStream_t s) {
-    constexpr int BX = 64, BZ = 4;
+// The walk's tiles.  Registers allow 16 waves per CU: one block of 256 x 4, or two of 128 x 4 or
+// 64 x 8.  Wider tiles have fewer x-halo columns, which cost a cache line for each population of
+// one node (256 x 4 with 23 rows: 1.18 ms per step of 512 x 182 x 182, 128 x 4 1.22, 64 x 8 1.26),
+// unless the box leaves their columns idle.
+namespace {
+struct Walk {
+    int bx, bz, per_cu;
+    double speed;
+};
+constexpr Walk kWalks[3] = {{256, 4, 1, 1.0}, {128, 4, 2, 0.97}, {64, 8, 2, 0.94}};
+
+// Row iterations of a launch (of 1024 nodes per CU each), weighted by the shape's speed: whole
+// rounds of blocks, two density-only slices per tile.
+double walk_cost(const Chan3& c, const Walk& w, int cy, int cus) {
+    const int64_t slots = (int64_t)std::max(cus, 1) * w.per_cu;
+    return (double)((walk_tiles(c, w.bx, w.bz, cy) + slots - 1) / slots) * (cy + 2) / w.speed;
+}
+}  // namespace
+
+hipError_t launch_step_fused(const Chan3& h, float* ws, int src, int cy, int cus, hipStream_t s) {
     cy = cy < 1 ? 1 : (cy > h.ny ? h.ny : cy);
-    const int64_t ntiles = (int64_t)((h.nx + BX - 1) / BX) * ((h.nz + BZ - 1) / BZ) * ((h.ny + cy - 1) / cy);
-    if (ntiles > INT32_MAX) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL((k3_fused<BX, BZ>), dim3((unsigned)ntiles), dim3(BX * BZ), 0, s, c, ws, src, cy);
-    return hipGetLastError();
+    int best = 0;
+    for (int k = 1; k < 3; ++k)
+        if (walk_cost(h, kWalks[k], cy, cus) < walk_cost(h, kWalks[best], cy, cus)) best = k;
+    switch (best) {
+        case 0: return launch_walk<256, 4>(h, ws, src, cy, s);
+        case 1: return launch_walk<128, 4>(h, ws, src, cy, s);
+        default: return launch_walk<64, 8>(h, ws, src, cy, s);
+    }
+}
+
+// A walk's iteration takes about 16 us at full CUs and the two kernels 95 ps per node (LLC-resident
+// boxes 80): 96 x 24 x 24 11.7 us per step with two kernels, 27 with the walk at its best; 256 x 128
+// x 64 188 and 203; 300 x 120 x 90 377 and 280; 512 x 182 x 182 1628 and 1183.  Returns the rows per
+// tile, 0 for the two kernels.
+int best_schedule(const Chan3& h, int cus) {
+    if (wide(h)) return 0;
+    double best = 95e-6 * h.nx * (double)h.ny * h.nz;
+    int rows = 0;
+    for (int k = 1; k <= h.ny; ++k) {
+        const int cy = (h.ny + k - 1) / k;
+        if (cy < 4) break;
+        for (const Walk& w : kWalks) {
+            const double t = 16.0 * walk_cost(h, w, cy, cus);
+            if (t < best) {
+                best = t;
+                rows = cy;
+            }
+        }
+    }
+    return rows;
 }
 
 hipError_t launch_observe(const Chan3& h, const Chan3* c, float* ws, int src, Part3* parts, Obs3* out,
                           hipStream_t s) {
-    hipLaunchKernelGGL(k3_density, grid_of(h), dim3(kThreads), 0, s, c, ws, src);
+    density(h, ws, src, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k3_obs_rows, dim3(h.ny, h.nz), dim3(kThreads), 0, s, c, ws, parts);

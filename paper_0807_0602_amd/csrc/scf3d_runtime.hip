@@ -42,8 +42,7 @@ bool geom_ok(const scf3_geometry* g, std::string* why) {
 
 int pitch_of(int nx) { return (nx + 63) / 64 * 64; }
 
-// The fused kernel addresses one component's 19 planes with unsigned 32-bit buffer offsets.
-bool fused_fits(int64_t plane) { return (int64_t)19 * plane * (int64_t)sizeof(float) <= (int64_t)UINT32_MAX; }
+using scf3::fused_fits;
 
 Plan3 plan(const scf3_geometry& g) {
     Plan3 p;
@@ -69,7 +68,9 @@ struct scf3_ctx {
     hipStream_t stream = nullptr;
     int cur = 0;
     int64_t t = 0;
-    int fused = 1, cy = 16;
+    int fused = 1, cy = 16;   // the schedule as reported and as scf3_set_schedule sets it
+    int rows = 0;             // rows per tile that steps run with, 0: two kernels
+    int cus = 0;
     int32_t seen_flags = 0;   // flags of the last scf3_observe (see scf3_step)
     float* base() const { return reinterpret_cast<float*>(ws); }
     scf3::Chan3* d_chan() const { return reinterpret_cast<scf3::Chan3*>(ws + lay.chan); }
@@ -117,6 +118,11 @@ int scf3_init(scf3_ctx** out, const scf3_geometry* geom, const scf_params* p, co
     h.off = (int64_t)(lay.pop / sizeof(float));
     h.plane = (int64_t)geom->nz * geom->ny * h.pitch;
     c->fused = fused_fits(h.plane) ? 1 : 0;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        c->cus = 256;
+    c->rows = scf3::best_schedule(h, c->cus);   // until a schedule is set
     h.G = (float)p->G;
     for (int k = 0; k < 2; ++k) {
         h.gw[k] = (float)p->gw[k];
@@ -142,10 +148,10 @@ int scf3_init(scf3_ctx** out, const scf3_geometry* geom, const scf_params* p, co
 int scf3_step(scf3_ctx* c, int64_t nsteps) {
     if (!c || nsteps < 0) return fail(SCF_EINVAL, "bad context or negative step count");
     for (int64_t i = 0; i < nsteps; ++i) {
-        if (c->fused)
-            HIP_TRY3(scf3::launch_step_fused(c->chan, c->d_chan(), c->base(), c->cur, c->cy, c->stream));
+        if (c->rows)
+            HIP_TRY3(scf3::launch_step_fused(c->chan, c->base(), c->cur, c->rows, c->cus, c->stream));
         else
-            HIP_TRY3(scf3::launch_step(c->chan, c->d_chan(), c->base(), c->cur, c->stream));
+            HIP_TRY3(scf3::launch_step(c->chan, c->base(), c->cur, c->stream));
         c->cur ^= 1;
         c->t += 1;
     }
@@ -163,6 +169,7 @@ int scf3_set_schedule(scf3_ctx* c, int32_t fused, int32_t cy) {
         return fail(SCF_EINVAL, "box too large for the fused kernel (19 planes above 4 GiB)");
     c->fused = fused;
     if (fused) c->cy = cy;
+    c->rows = fused ? cy : 0;
     return SCF_OK;
 }
 
