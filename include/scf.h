@@ -340,11 +340,12 @@ void scf_sur_destroy(scf_sur* s);
  * (12 edge links); bulk and wall forces of eqs. forcing and forcingw with the same link weights;
  * common velocity, shifted equilibrium, BGK, pull streaming with half-way bounce-back.  The
  * weights' z-projection is D2Q9 with rest fraction 4/9, so a z-independent state evolves as the
- * 2-D model.  FP32 state.  By default one fused kernel per step: tiles of 64 x 4 (x, z) nodes walk
- * cy rows of y, keeping the densities of three y-slices in LDS; the two-kernel form (a density
- * field, then pull + collide) is selectable (scf3_set_schedule) and is the only one when one
- * component's 19 planes exceed 4 GiB (unsigned 32-bit buffer offsets).  Both give identical
- * results.
+ * 2-D model.  FP32 state.  Two step forms:
+ * one fused kernel per step, whose tiles of 256 x 4, 128 x 4 or 64 x 8 (x, z) nodes walk cy rows of
+ * y, keeping the densities of three y-slices in LDS; and two kernels (a density field, then pull +
+ * collide).  A new context takes the faster one for its size (two kernels up to about 2 M nodes);
+ * scf3_set_schedule chooses.  Two kernels are the only form when one component's 19 planes exceed
+ * 4 GiB (unsigned 32-bit buffer offsets).  Both give identical results.
  * ------------------------------------------------------------------------------------------- */
 
 typedef struct {
@@ -383,9 +384,10 @@ int scf3_init(scf3_ctx** out, const scf3_geometry* geom, const scf_params* param
  * stream).  SCF_EUNSTABLE (after enqueueing) when the last scf3_observe found flags bit1 set. */
 int scf3_step(scf3_ctx* ctx, int64_t nsteps);
 
-/* Step schedule: fused = 1 (one kernel, cy >= 1 rows of y per tile, default 16 or the two-kernel
- * form where the fused one does not fit) or fused = 0 (two kernels, cy ignored).  The state is
- * unchanged; results do not depend on the schedule.  *_get_* writes the current one.
+/* Step schedule: fused = 1 (one kernel, cy >= 1 rows of y per tile) or fused = 0 (two kernels, cy
+ * ignored).  The state is unchanged; results do not depend on the schedule.  *_get_* writes the
+ * current one; before any *_set_* it reports fused = 1 and cy = 16 (fused = 0 where the fused form
+ * does not fit) while the steps run with the form chosen for the box's size.
  * Errors: SCF_EINVAL (fused not 0/1, cy < 1, or fused = 1 where a component's 19 planes exceed
  * 4 GiB). */
 int scf3_set_schedule(scf3_ctx* ctx, int32_t fused, int32_t cy);
