@@ -489,35 +489,26 @@ k3_pull_out(const Chan3* __restrict__ cp, float* __restrict__ ws, int src) {
 // flag, then one block sums the rows in order and finds the centre-line front.  Block reductions
 // run in a fixed order: a butterfly over each wave's 64 lanes, then the wave results through LDS.
 constexpr int kWaves = kThreads / 64;
+// One block sums every row's partials and searches the centre line, a serial chain of loads per
+// thread: 1024 threads (512 x 182 x 182: 15 us for 39 with 256), one barrier for all reductions.
+constexpr int kFinalThreads = 1024, kFinalWaves = kFinalThreads / 64;
 
 template <typename T>
-__device__ __forceinline__ T bsum(T v, T* sh) {
+__device__ __forceinline__ T wsum(T v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    T r = sh[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) r += sh[w];
-    __syncthreads();
-    return r;
+    return v;
 }
 
-__device__ __forceinline__ int bmin(int v, int* sh) {
+__device__ __forceinline__ int wmin(int v) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off, 64));
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    int r = sh[0];
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) r = min(r, sh[w]);
-    __syncthreads();
-    return r;
+    return v;
 }
 
 __global__ void __launch_bounds__(kThreads)
 k3_obs_rows(const Chan3* __restrict__ cp, const float* __restrict__ ws, Part3* __restrict__ parts) {
-    __shared__ double sd[kWaves];
+    __shared__ double sd[2][kWaves];
     __shared__ int si[kWaves];
     const Chan3 c = *cp;
     const int y = blockIdx.x, z = blockIdx.y;
@@ -532,10 +523,21 @@ k3_obs_rows(const Chan3* __restrict__ cp, const float* __restrict__ ws, Part3* _
         mB += (double)b;
         if (!(a >= -1e-3f) || !(b >= -1e-3f) || !isfinite(a) || !isfinite(b)) bad = 1;
     }
-    mA = bsum(mA, sd);
-    mB = bsum(mB, sd);
-    bad = bsum(bad, si);
+    mA = wsum(mA);
+    mB = wsum(mB);
+    bad = wsum(bad);
+    if ((threadIdx.x & 63) == 0) {
+        sd[0][threadIdx.x >> 6] = mA;
+        sd[1][threadIdx.x >> 6] = mB;
+        si[threadIdx.x >> 6] = bad;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
+        for (int w = 1; w < kWaves; ++w) {
+            mA += sd[0][w];
+            mB += sd[1][w];
+            bad += si[w];
+        }
         Part3 p;
         p.mass[0] = mA;
         p.mass[1] = mB;
@@ -545,25 +547,22 @@ k3_obs_rows(const Chan3* __restrict__ cp, const float* __restrict__ ws, Part3* _
     }
 }
 
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kFinalThreads)
 k3_obs_final(const Chan3* __restrict__ cp, const float* __restrict__ ws, const Part3* __restrict__ parts,
              Obs3* __restrict__ out) {
-    __shared__ double sd[kWaves];
-    __shared__ int si[kWaves];
+    __shared__ double sd[2][kFinalWaves];
+    __shared__ int si[2][kFinalWaves];
     const Chan3 c = *cp;
     const int tid = threadIdx.x;
     const float* __restrict__ nAf = ws + c.off + 76 * c.plane;
     const float* __restrict__ nBf = nAf + c.plane;
     double mA = 0.0, mB = 0.0;
     int bad = 0;
-    for (int r = tid; r < c.ny * c.nz; r += kThreads) {
+    for (int r = tid; r < c.ny * c.nz; r += kFinalThreads) {
         mA += parts[r].mass[0];
         mB += parts[r].mass[1];
         bad |= parts[r].bad;
     }
-    mA = bsum(mA, sd);
-    mB = bsum(mB, sd);
-    bad = bsum(bad, si);
     // centre line: the (up to) four lines nearest (y, z) = ((ny-1)/2, (nz-1)/2)
     const int ys[2] = {(c.ny - 1) / 2, c.ny / 2}, zs[2] = {(c.nz - 1) / 2, c.nz / 2};
     auto phi = [&](int x) -> double {
@@ -576,10 +575,26 @@ k3_obs_final(const Chan3* __restrict__ cp, const float* __restrict__ ws, const P
     const int big = 0x7fffffff;
     int xz = big;
     const int xs0 = c.x0 / 2;
-    for (int x = xs0 + tid; x + 1 < c.nx; x += kThreads)
-        if (xz == big && phi(x) >= 0.0 && phi(x + 1) < 0.0) xz = x;
-    xz = bmin(xz, si);
+    for (int x = xs0 + tid; x + 1 < c.nx; x += kFinalThreads)
+        if (phi(x) >= 0.0 && phi(x + 1) < 0.0) xz = min(xz, x);
+    mA = wsum(mA);
+    mB = wsum(mB);
+    bad = wsum(bad);
+    xz = wmin(xz);
+    if ((tid & 63) == 0) {
+        sd[0][tid >> 6] = mA;
+        sd[1][tid >> 6] = mB;
+        si[0][tid >> 6] = bad;
+        si[1][tid >> 6] = xz;
+    }
+    __syncthreads();
     if (tid == 0) {
+        for (int w = 1; w < kFinalWaves; ++w) {
+            mA += sd[0][w];
+            mB += sd[1][w];
+            bad += si[0][w];
+            xz = min(xz, si[1][w]);
+        }
         Obs3 o;
         o.t = 0;
         o.mass[0] = mA;
@@ -593,6 +608,18 @@ k3_obs_final(const Chan3* __restrict__ cp, const float* __restrict__ ws, const P
         o.flags = (phi(xs0) < 0.0 ? 1 : 0) | (bad ? 2 : 0);
         o.reserved = 0;
         *out = o;
+    }
+}
+
+// The density field in FP64 without padding into `out` (n_A, then n_B), as the caller's arrays have it.
+__global__ void __launch_bounds__(kThreads)
+k3_density_out(Chan3 c, const float* __restrict__ ws, double* __restrict__ out) {
+    const int64_t row = (int64_t)blockIdx.y * c.ny + blockIdx.x, cells = (int64_t)c.nx * c.ny * c.nz;
+    const float* __restrict__ n = ws + c.off + 76 * c.plane + row * c.pitch;
+    double* o = out + row * c.nx;
+    for (int x = threadIdx.x; x < c.nx; x += kThreads) {
+        o[x] = n[x];
+        o[cells + x] = n[c.plane + x];
     }
 }
 
@@ -709,7 +736,12 @@ hipError_t launch_observe(const Chan3& h, const Chan3* c, float* ws, int src, Pa
     hipLaunchKernelGGL(k3_obs_rows, dim3(h.ny, h.nz), dim3(kThreads), 0, s, c, ws, parts);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k3_obs_final, dim3(1), dim3(kThreads), 0, s, c, ws, parts, out);
+    hipLaunchKernelGGL(k3_obs_final, dim3(1), dim3(kFinalThreads), 0, s, c, ws, parts, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_density_out(const Chan3& h, const float* ws, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(k3_density_out, dim3(h.ny, h.nz), dim3(kThreads), 0, s, h, ws, out);
     return hipGetLastError();
 }
 

@@ -201,19 +201,14 @@ int scf3_get_density(scf3_ctx* c, double* nA, double* nB) {
     scf3_obs o;
     int rc = scf3_observe(c, &o);   // also refreshes the density field
     if (rc && rc != SCF_EUNSTABLE) return rc;
+    // converted and compacted on the device, into the idle population buffer (the next step overwrites it)
     const scf3::Chan3& h = c->chan;
-    std::vector<float> buf((size_t)2 * h.plane);
-    HIP_TRY3(hipMemcpyAsync(buf.data(), c->base() + h.off + 76 * h.plane, sizeof(float) * buf.size(),
-                            hipMemcpyDeviceToHost, c->stream));
+    const size_t cells = (size_t)h.nx * h.ny * h.nz;
+    double* f = reinterpret_cast<double*>(c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane);
+    HIP_TRY3(scf3::launch_density_out(h, c->base(), f, c->stream));
+    HIP_TRY3(hipMemcpyAsync(nA, f, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY3(hipMemcpyAsync(nB, f + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY3(hipStreamSynchronize(c->stream));
-    for (int z = 0; z < h.nz; ++z)
-        for (int y = 0; y < h.ny; ++y)
-            for (int x = 0; x < h.nx; ++x) {
-                const size_t src = ((size_t)z * h.ny + y) * h.pitch + x;
-                const size_t dst = ((size_t)z * h.ny + y) * h.nx + x;
-                nA[dst] = buf[src];
-                nB[dst] = buf[h.plane + src];
-            }
     return SCF_OK;
 }
 

@@ -86,6 +86,8 @@ hipError_t launch_step_two_kernel(const Chan* chans, const RowRef* rows, int nro
 hipError_t launch_observe(const Chan* chans, const RowRef* rows, int nrows, int nchan, float* ws,
                           int src, RowPartial* partials, ObsRec* now, ObsRec* ring,
                           int32_t* counter, int max_samples, int record, hipStream_t s);
+// FP64 densities of channel ch (n_A, n_B, ny x nx each, unpadded) into `out`.
+hipError_t launch_density_out(const Chan* chans, int ch, int ny, const float* ws, int src, double* out, hipStream_t s);
 hipError_t launch_pull_out(const Chan* chans, const RowRef* rows, int nrows, float* ws, int src,
                            hipStream_t s);
 

@@ -889,16 +889,39 @@ k_pull_out(const Chan* __restrict__ chans, const RowRef* __restrict__ rows, floa
     }
 }
 
+// Densities of channel `ch` in FP64 into `out` (n_A, then n_B, ny rows of nx values without padding),
+// as the caller's arrays have them: the host then only copies.  One row per block, memory bound
+// (16384 x 1024: 0.31 ms, 4.7 TB/s); with FP32 rows converted on the host that read-out took 50 ms,
+// now 27, which is the copy into fresh pageable arrays.
+__global__ void __launch_bounds__(kRowThreads)
+k_density_out(const Chan* __restrict__ chans, int ch, const float* __restrict__ ws, int src, double* __restrict__ out) {
+    const Chan c = chans[ch];
+    const float* __restrict__ g = ws + c.off + (int64_t)src * 18 * c.plane;
+    const int y = blockIdx.x;
+    double* oA = out + (int64_t)y * c.nx;
+    double* oB = oA + (int64_t)c.nx * c.ny;
+    for (int x = threadIdx.x; x < c.nx; x += kRowThreads) {
+        float p[18];
+        const bool solid = pull_node(g, c, ws, x, y, p) & 1u;
+        oA[x] = solid ? 0.0 : (double)sum9(p);
+        oB[x] = solid ? 0.0 : (double)sum9(p + 9);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Observables.  Pass 1 (one block per row): densities of the row into the density field,
 // FP64 row sums of n_A and n_B over fluid nodes and a health flag.  Pass 2 (one block per
 // channel): the row sums in fixed order, then the centre-line front and the wall-row film
 // fronts by a parallel first-crossing search.  Both passes are deterministic.
 // ---------------------------------------------------------------------------------------------
-// Block reductions in a fixed order (results are bit-reproducible): a butterfly over the 64 lanes
-// of each wave by cross-lane swaps, then the kRowThreads / 64 wave results through LDS, summed by
-// every thread in wave order.  Two barriers per reduction.
+// Reductions in a fixed order (results are bit-reproducible): a butterfly over the 64 lanes of each
+// wave by cross-lane swaps, then the waves' results through LDS in wave order.  All of a kernel's
+// reductions share one barrier.
 constexpr int kRowWaves = kRowThreads / 64;
+// One block searches a channel's rows and lines, a serial chain of loads per thread: 1024 threads for
+// the longest lines (4096 x 202: 8 us for 28 with 256 threads and a barrier pair per reduction, 200 x
+// 24: 4 for 7).
+constexpr int kFinalThreads = 1024, kFinalWaves = kFinalThreads / 64;
 
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
@@ -913,33 +936,10 @@ __device__ __forceinline__ int wave_min(int v) {
     return v;
 }
 
-template <typename T>
-__device__ __forceinline__ T block_sum(T v, T* scratch) {
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-    __syncthreads();
-    T r = scratch[0];
-#pragma unroll
-    for (int w = 1; w < kRowWaves; ++w) r += scratch[w];
-    __syncthreads();
-    return r;
-}
-
-__device__ __forceinline__ int block_min(int v, int* scratch) {
-    v = wave_min(v);
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-    __syncthreads();
-    int r = scratch[0];
-#pragma unroll
-    for (int w = 1; w < kRowWaves; ++w) r = min(r, scratch[w]);
-    __syncthreads();
-    return r;
-}
-
 __global__ void __launch_bounds__(kRowThreads)
 k_obs_rows(const Chan* __restrict__ chans, const RowRef* __restrict__ rows, float* __restrict__ ws,
            int src, RowPartial* __restrict__ part) {
-    __shared__ double sd[kRowWaves];
+    __shared__ double sd[2][kRowWaves];
     __shared__ int si[kRowWaves];
     const RowRef r = rows[blockIdx.x];
     const Chan c = chans[r.chan];
@@ -961,10 +961,21 @@ k_obs_rows(const Chan* __restrict__ chans, const RowRef* __restrict__ rows, floa
         dn[r.y * c.pitch + x] = nA;
         dn[c.plane + r.y * c.pitch + x] = nB;
     }
-    mA = block_sum(mA, sd);
-    mB = block_sum(mB, sd);
-    bad = block_sum(bad, si);
+    mA = wave_sum(mA);
+    mB = wave_sum(mB);
+    bad = wave_sum(bad);
+    if ((threadIdx.x & 63) == 0) {
+        sd[0][threadIdx.x >> 6] = mA;
+        sd[1][threadIdx.x >> 6] = mB;
+        si[threadIdx.x >> 6] = bad;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
+        for (int w = 1; w < kRowWaves; ++w) {
+            mA += sd[0][w];
+            mB += sd[1][w];
+            bad += si[w];
+        }
         RowPartial o;
         o.mass[0] = mA;
         o.mass[1] = mB;
@@ -979,12 +990,12 @@ __device__ __forceinline__ double refine(double vx, double vx1, int x, double le
     return (double)x + (vx - level) / (vx - vx1) - (double)x0;
 }
 
-__global__ void __launch_bounds__(kRowThreads)
+__global__ void __launch_bounds__(kFinalThreads)
 k_obs_final(const Chan* __restrict__ chans, const float* __restrict__ ws,
             const RowPartial* __restrict__ part, ObsRec* __restrict__ now, ObsRec* __restrict__ ring,
             const int32_t* __restrict__ counter, int max_samples, int record) {
-    __shared__ double sd[kRowWaves];
-    __shared__ int si[kRowWaves];
+    __shared__ double sd[2][kFinalWaves];
+    __shared__ int si[4][kFinalWaves];
     const int ch = blockIdx.x;
     const Chan c = chans[ch];
     const int tid = threadIdx.x;
@@ -992,15 +1003,12 @@ k_obs_final(const Chan* __restrict__ chans, const float* __restrict__ ws,
     const float* __restrict__ nB = nA + c.plane;
     double mA = 0.0, mB = 0.0;
     int bad = 0;
-    for (int y = tid; y < c.ny; y += kRowThreads) {
+    for (int y = tid; y < c.ny; y += kFinalThreads) {
         const RowPartial p = part[c.row_base + y];
         mA += p.mass[0];
         mB += p.mass[1];
         bad |= p.bad;
     }
-    mA = block_sum(mA, sd);
-    mB = block_sum(mB, sd);
-    bad = block_sum(bad, si);
     // centre line: rows ny/2-1 and ny/2 averaged (ny even) or row (ny-1)/2
     const bool even = (c.ny & 1) == 0;
     const int ra = even ? c.ny / 2 - 1 : (c.ny - 1) / 2;
@@ -1011,21 +1019,41 @@ k_obs_final(const Chan* __restrict__ chans, const float* __restrict__ ws,
     };
     auto phi = [&](int x) -> double { return centre(nA, x) - centre(nB, x); };
     const int big = 0x7fffffff;
-    int xz = big;
-    for (int x = c.xs + tid; x + 1 < c.nx; x += kRowThreads)
-        if (xz == big && phi(x) >= 0.0 && phi(x + 1) < 0.0) xz = x;
-    xz = block_min(xz, si);
     const double level = centre(nA, c.xs) / 3.0;
     const float* rowlo = nA + 1 * c.pitch;
     const float* rowhi = nA + (c.ny - 2) * c.pitch;
-    int xlo = big, xhi = big;
-    for (int x = c.xs + tid; x + 1 < c.nx; x += kRowThreads) {
-        if (xlo == big && (double)rowlo[x] >= level && (double)rowlo[x + 1] < level) xlo = x;
-        if (xhi == big && (double)rowhi[x] >= level && (double)rowhi[x + 1] < level) xhi = x;
+    int xz = big, xlo = big, xhi = big;
+    for (int x = c.xs + tid; x + 1 < c.nx; x += kFinalThreads) {
+        const double p0 = phi(x), p1 = phi(x + 1), l0 = rowlo[x], l1 = rowlo[x + 1], h0 = rowhi[x], h1 = rowhi[x + 1];
+        if (p0 >= 0.0 && p1 < 0.0) xz = min(xz, x);
+        if (l0 >= level && l1 < level) xlo = min(xlo, x);
+        if (h0 >= level && h1 < level) xhi = min(xhi, x);
     }
-    xlo = block_min(xlo, si);
-    xhi = block_min(xhi, si);
+    mA = wave_sum(mA);
+    mB = wave_sum(mB);
+    bad = wave_sum(bad);
+    xz = wave_min(xz);
+    xlo = wave_min(xlo);
+    xhi = wave_min(xhi);
+    if ((tid & 63) == 0) {
+        const int w = tid >> 6;
+        sd[0][w] = mA;
+        sd[1][w] = mB;
+        si[0][w] = bad;
+        si[1][w] = xz;
+        si[2][w] = xlo;
+        si[3][w] = xhi;
+    }
+    __syncthreads();
     if (tid == 0) {
+        for (int w = 1; w < kFinalWaves; ++w) {
+            mA += sd[0][w];
+            mB += sd[1][w];
+            bad += si[0][w];
+            xz = min(xz, si[1][w]);
+            xlo = min(xlo, si[2][w]);
+            xhi = min(xhi, si[3][w]);
+        }
         ObsRec o;
         o.t = 0;
         o.mass[0] = mA;
@@ -1210,11 +1238,16 @@ hipError_t launch_observe(const Chan* chans, const RowRef* rows, int nrows, int 
                        partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_obs_final, dim3(nchan), dim3(kRowThreads), 0, s, chans, ws, partials, now,
+    hipLaunchKernelGGL(k_obs_final, dim3(nchan), dim3(kFinalThreads), 0, s, chans, ws, partials, now,
                        ring, counter, max_samples, record);
     e = hipGetLastError();
     if (e != hipSuccess || !record) return e;
     hipLaunchKernelGGL(k_bump, dim3(1), dim3(64), 0, s, counter);
+    return hipGetLastError();
+}
+
+hipError_t launch_density_out(const Chan* chans, int ch, int ny, const float* ws, int src, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_density_out, dim3(ny), dim3(kRowThreads), 0, s, chans, ch, ws, src, out);
     return hipGetLastError();
 }
 

@@ -881,20 +881,16 @@ struct Engine {
         return SCF_OK;
     }
 
+    // Converted and compacted on the device, into the idle population buffer (the next step overwrites
+    // it), and from there into the caller's arrays.
     int get_density(int c, double* nA, double* nB) {
         if (c < 0 || c >= nchan || !nA || !nB) return fail(SCF_EINVAL, "bad channel or NULL output");
-        HIP_TRY(launch_obs(stream, 0));
-        const scf_geometry& g = geom[c];
-        const int pitch = chans[c].pitch;
-        std::vector<float> h((size_t)2 * g.ny * pitch);
-        HIP_TRY(hipMemcpyAsync(h.data(), ws + lay.chan_off[c] + sizeof(float) * 36 * chans[c].plane,
-                               sizeof(float) * h.size(), hipMemcpyDeviceToHost, stream));
+        const size_t cells = (size_t)geom[c].nx * geom[c].ny;
+        double* out = reinterpret_cast<double*>(ws + lay.chan_off[c] + sizeof(float) * (size_t)(cur ^ 1) * 18 * chans[c].plane);
+        HIP_TRY(scf::launch_density_out(d_chans(), c, geom[c].ny, base(), cur, out, stream));
+        HIP_TRY(hipMemcpyAsync(nA, out, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
+        HIP_TRY(hipMemcpyAsync(nB, out + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
         HIP_TRY(hipStreamSynchronize(stream));
-        for (int y = 0; y < g.ny; ++y)
-            for (int x = 0; x < g.nx; ++x) {
-                nA[(size_t)y * g.nx + x] = h[(size_t)y * pitch + x];
-                nB[(size_t)y * g.nx + x] = h[(size_t)(g.ny + y) * pitch + x];
-            }
         return SCF_OK;
     }
 };

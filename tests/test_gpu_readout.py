@@ -1,0 +1,94 @@
+"""Density read-outs: converted and compacted on the device, through the idle population buffer.
+
+Against the populations of the same state (whose FP32 sum a density is, within 9 or 19 roundings),
+on odd and padded row lengths, masked boxes, several channels of a batch and 3-D boxes; and reading a
+density between steps leaves every later population as it was, bit for bit.
+"""
+import numpy as np
+import pytest
+
+from paper_0807_0602_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def scf():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_0807_0602_amd import scf as S
+    return S
+
+
+def _check(density, pops, solid, terms):
+    """n = sum f within `terms` roundings of the running FP32 sum; 0 on solid nodes."""
+    for n, f in zip(density, pops):
+        assert n.shape == f.shape[1:] and n.dtype == np.float64
+        assert np.array_equal(n, n.astype(np.float32).astype(np.float64))
+        assert (np.abs(n - f.sum(0)) <= terms * EPS * np.abs(f).sum(0)).all()
+        assert (n[solid] == 0.0).all()
+
+
+CASES = [
+    ("tiny", inputs.Case(inputs.Geometry(3, 3, 1, 2), inputs.Params(gw=(0.1, -0.1)), seed=1, liquid_x1=1)),
+    ("odd", inputs.Case(inputs.Geometry(131, 17, 20, 111), inputs.Params(gw=(-0.3, 0.3)), seed=2, liquid_x1=40)),
+    ("wide", inputs.Case(inputs.Geometry(2049, 40, 64, 2000), inputs.Params(gw=(-0.2, 0.2)), seed=3, liquid_x1=700)),
+    ("rough", inputs.capillary_rough(seed=1)),
+]
+
+
+@pytest.mark.parametrize("name,case", CASES, ids=[c[0] for c in CASES])
+@pytest.mark.parametrize("steps", [6, 7])
+def test_density_of_a_channel(scf, name, case, steps):
+    print(f"case: density read-out {name}, {steps} steps", flush=True)
+    a, b = scf.Channel.from_case(case), scf.Channel.from_case(case)
+    solid = case.geom.solid_mask()
+    for n in (0, steps, 1):
+        a.step(n)
+        b.step(n)
+        _check(a.density(), a.populations(), solid, 9)
+        a.density()
+        assert np.array_equal(a.populations(), b.populations())
+
+
+def test_density_of_a_batch(scf):
+    print("case: density read-out of a batch", flush=True)
+    cases = [c for _, c in CASES]
+    b = scf.Batch(cases, sample_every=5, max_samples=4)
+    ref = scf.Batch(cases, sample_every=5, max_samples=4)
+    for n in (5, 8):
+        b.step(n)
+        ref.step(n)
+        for c in reversed(range(len(cases))):
+            first, again = b.density(c), b.density(c)
+            assert all(np.array_equal(x, y) for x, y in zip(first, again))
+    for c, case in enumerate(cases):
+        one = scf.Channel.from_case(case)
+        one.step(13)
+        for x, y, z in zip(b.density(c), ref.density(c), one.density()):
+            assert np.array_equal(x, y) and np.array_equal(x, z)
+    assert b.observe()[1] == ref.observe()[1] == 3
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(3, 3, 3), (65, 9, 14), (300, 20, 11)])
+def test_density_of_a_3d_channel(scf, nx, ny, nz):
+    print(f"case: density read-out {nx} x {ny} x {nz}", flush=True)
+    rng = np.random.default_rng(4)
+    left = np.arange(nx) < max(1, nx // 3)
+    fields = [np.where(left, u, v) + rng.uniform(-1e-3, 1e-3, (nz, ny, nx)) for u, v in ((2.0, 0.06), (0.06, 2.0))]
+    solid = np.zeros((nz, ny, nx), bool)
+    x0, x1 = nx // 3, nx - nx // 4
+    solid[:, [0, -1], x0:x1] = True
+    for f in fields:
+        f[solid] = 0.0
+    a, b = (scf.Channel3(nx, ny, nz, x0, x1, inputs.Params(gw=(-0.2, 0.2)), *fields, walls_y=True, walls_z=False)
+            for _ in range(2))
+    for n in (0, 3, 4):
+        a.step(n)
+        b.step(n)
+        _check(a.density(), a.populations(), solid, 19)
+        a.density()
+        assert np.array_equal(a.populations(), b.populations())
