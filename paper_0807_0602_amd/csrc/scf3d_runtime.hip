@@ -2,6 +2,7 @@
 // the 2-D library it allocates no device memory: it carves the caller's workspace.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstring>
@@ -10,6 +11,7 @@
 #include <vector>
 
 #include "scf.h"
+#include "host_stage.h"
 #include "scf3d_internal.h"
 
 namespace {
@@ -72,6 +74,7 @@ struct scf3_ctx {
     int rows = 0;             // rows per tile that steps run with, 0: two kernels
     int cus = 0;
     int32_t seen_flags = 0;   // flags of the last scf3_observe (see scf3_step)
+    scf::HostStage stage;     // the record and a small density field on their way to the caller
     float* base() const { return reinterpret_cast<float*>(ws); }
     scf3::Chan3* d_chan() const { return reinterpret_cast<scf3::Chan3*>(ws + lay.chan); }
 };
@@ -123,6 +126,10 @@ int scf3_init(scf3_ctx** out, const scf3_geometry* geom, const scf_params* p, co
         hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         c->cus = 256;
     c->rows = scf3::best_schedule(h, c->cus);   // until a schedule is set
+    {
+        const size_t f = 2 * sizeof(double) * (size_t)geom->nx * geom->ny * geom->nz;
+        c->stage.reserve(f <= scf::kStageBytes ? std::max(f, sizeof(scf3::Obs3)) : sizeof(scf3::Obs3));
+    }
     h.G = (float)p->G;
     for (int k = 0; k < 2; ++k) {
         h.gw[k] = (float)p->gw[k];
@@ -183,11 +190,13 @@ int scf3_get_schedule(const scf3_ctx* c, int32_t* fused, int32_t* cy) {
 int scf3_observe(scf3_ctx* c, scf3_obs* out) {
     if (!c || !out) return fail(SCF_EINVAL, "NULL argument");
     auto* parts = reinterpret_cast<scf3::Part3*>(c->ws + c->lay.parts);
-    auto* obs = reinterpret_cast<scf3::Obs3*>(c->ws + c->lay.obs);
+    const bool staged = c->stage.holds(sizeof(scf3::Obs3));
+    auto* obs = reinterpret_cast<scf3::Obs3*>(staged ? c->stage.p : c->ws + c->lay.obs);
     HIP_TRY3(scf3::launch_observe(c->chan, c->d_chan(), c->base(), c->cur, parts, obs, c->stream));
     scf3::Obs3 r;
-    HIP_TRY3(hipMemcpyAsync(&r, obs, sizeof r, hipMemcpyDeviceToHost, c->stream));
+    if (!staged) HIP_TRY3(hipMemcpyAsync(&r, obs, sizeof r, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY3(hipStreamSynchronize(c->stream));
+    if (staged) std::memcpy(&r, obs, sizeof r);
     static_assert(sizeof(scf3::Obs3) == sizeof(scf3_obs), "record layout");
     std::memcpy(out, &r, sizeof r);
     out->t = c->t;
@@ -201,14 +210,23 @@ int scf3_get_density(scf3_ctx* c, double* nA, double* nB) {
     scf3_obs o;
     int rc = scf3_observe(c, &o);   // also refreshes the density field
     if (rc && rc != SCF_EUNSTABLE) return rc;
-    // converted and compacted on the device, into the idle population buffer (the next step overwrites it)
+    // converted and compacted on the device: a small field straight into page-locked memory, others into
+    // the idle population buffer (the next step overwrites it) and copied from there
     const scf3::Chan3& h = c->chan;
     const size_t cells = (size_t)h.nx * h.ny * h.nz;
-    double* f = reinterpret_cast<double*>(c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane);
+    const bool staged = c->stage.holds(2 * sizeof(double) * cells);
+    double* f = staged ? reinterpret_cast<double*>(c->stage.p)
+                       : reinterpret_cast<double*>(c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane);
     HIP_TRY3(scf3::launch_density_out(h, c->base(), f, c->stream));
-    HIP_TRY3(hipMemcpyAsync(nA, f, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY3(hipMemcpyAsync(nB, f + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
+    if (!staged) {
+        HIP_TRY3(hipMemcpyAsync(nA, f, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY3(hipMemcpyAsync(nB, f + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
+    }
     HIP_TRY3(hipStreamSynchronize(c->stream));
+    if (staged) {
+        std::memcpy(nA, f, sizeof(double) * cells);
+        std::memcpy(nB, f + cells, sizeof(double) * cells);
+    }
     return SCF_OK;
 }
 

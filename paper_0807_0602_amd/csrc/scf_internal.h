@@ -88,6 +88,8 @@ hipError_t launch_observe(const Chan* chans, const RowRef* rows, int nrows, int 
                           int32_t* counter, int max_samples, int record, hipStream_t s);
 // FP64 densities of channel ch (n_A, n_B, ny x nx each, unpadded) into `out`.
 hipError_t launch_density_out(const Chan* chans, int ch, int ny, const float* ws, int src, double* out, hipStream_t s);
+// The first `have` (>= 1) records of every channel's ring, packed into `out`.
+hipError_t launch_pack_ring(const ObsRec* ring, int nchan, int max_samples, int have, ObsRec* out, hipStream_t s);
 hipError_t launch_pull_out(const Chan* chans, const RowRef* rows, int nrows, float* ws, int src,
                            hipStream_t s);
 

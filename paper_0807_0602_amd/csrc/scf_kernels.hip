@@ -1074,6 +1074,16 @@ k_obs_final(const Chan* __restrict__ chans, const float* __restrict__ ws,
     }
 }
 
+// The first `have` records of every channel, one channel after the other, into `out`.
+__global__ void __launch_bounds__(64)
+k_pack_ring(const ObsRec* __restrict__ ring, int max_samples, int have, ObsRec* __restrict__ out) {
+    constexpr int W = sizeof(ObsRec) / sizeof(int64_t);
+    const int64_t n = (int64_t)have * W, c = blockIdx.x;
+    const int64_t* r = reinterpret_cast<const int64_t*>(ring + c * max_samples);
+    int64_t* o = reinterpret_cast<int64_t*>(out + c * have);
+    for (int64_t i = threadIdx.x; i < n; i += 64) o[i] = r[i];
+}
+
 __global__ void k_bump(int32_t* counter) {
     if (threadIdx.x == 0 && blockIdx.x == 0) *counter = *counter + 1;
 }
@@ -1248,6 +1258,11 @@ hipError_t launch_observe(const Chan* chans, const RowRef* rows, int nrows, int 
 
 hipError_t launch_density_out(const Chan* chans, int ch, int ny, const float* ws, int src, double* out, hipStream_t s) {
     hipLaunchKernelGGL(k_density_out, dim3(ny), dim3(kRowThreads), 0, s, chans, ch, ws, src, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_ring(const ObsRec* ring, int nchan, int max_samples, int have, ObsRec* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_pack_ring, dim3(nchan), dim3(64), 0, s, ring, max_samples, have, out);
     return hipGetLastError();
 }
 

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "scf.h"
+#include "host_stage.h"
 #include "scf_internal.h"
 
 namespace {
@@ -195,6 +196,7 @@ struct Engine {
     int sample_every = 0, max_samples = 1;
     int64_t recorded = 0;
     bool batch = false;
+    scf::HostStage stage;   // records and small density fields on their way to the caller
     // flags of the last observation copied to the host (scf_observe, scf_batch_observe); a
     // later step reports bit 1 as SCF_EUNSTABLE without synchronising
     int32_t seen_flags = 0;
@@ -547,9 +549,10 @@ struct Engine {
         return n / k + (n % k != 0);
     }
 
-    hipError_t launch_obs(hipStream_t s, int record) const {
+    // Observation of the current state into `now` (nchan records), nothing recorded.
+    hipError_t launch_obs(scf::ObsRec* now) const {
         return scf::launch_observe(d_chans(), d_rows(), lay.nrows, nchan, base(), cur,
-                                   d_parts(), d_now(), d_ring(), d_counter(), max_samples, record, s);
+                                   d_parts(), now, d_ring(), d_counter(), max_samples, 0, stream);
     }
 
     // Capture `n` steps starting from parity p, optionally followed by a recorded observation.
@@ -656,6 +659,16 @@ struct Engine {
             int dev = 0;
             HIP_TRY(hipGetDevice(&dev));
             HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+        }
+        {
+            // room for every channel's record, and for the fields and rings that are small enough
+            size_t want = sizeof(scf::ObsRec) * nch;
+            for (int c = 0; c < nch; ++c) {
+                const size_t f = 2 * sizeof(double) * (size_t)g[c].nx * g[c].ny;
+                if (f <= scf::kStageBytes) want = std::max(want, f);
+            }
+            if (samp_every > 0) want = std::max(want, std::min(scf::kStageBytes, sizeof(scf::ObsRec) * nch * (size_t)max_samp));
+            stage.reserve(want);
         }
         nchan = nch;
         geom.assign(g, g + nch);
@@ -881,16 +894,24 @@ struct Engine {
         return SCF_OK;
     }
 
-    // Converted and compacted on the device, into the idle population buffer (the next step overwrites
-    // it), and from there into the caller's arrays.
+    // Converted and compacted on the device: small fields straight into page-locked memory, others
+    // into the idle population buffer (the next step overwrites it) and copied from there.
     int get_density(int c, double* nA, double* nB) {
         if (c < 0 || c >= nchan || !nA || !nB) return fail(SCF_EINVAL, "bad channel or NULL output");
         const size_t cells = (size_t)geom[c].nx * geom[c].ny;
-        double* out = reinterpret_cast<double*>(ws + lay.chan_off[c] + sizeof(float) * (size_t)(cur ^ 1) * 18 * chans[c].plane);
+        const bool staged = stage.holds(2 * sizeof(double) * cells);
+        double* out = reinterpret_cast<double*>(
+            staged ? stage.p : ws + lay.chan_off[c] + sizeof(float) * (size_t)(cur ^ 1) * 18 * chans[c].plane);
         HIP_TRY(scf::launch_density_out(d_chans(), c, geom[c].ny, base(), cur, out, stream));
-        HIP_TRY(hipMemcpyAsync(nA, out, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
-        HIP_TRY(hipMemcpyAsync(nB, out + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
+        if (!staged) {
+            HIP_TRY(hipMemcpyAsync(nA, out, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
+            HIP_TRY(hipMemcpyAsync(nB, out + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
+        }
         HIP_TRY(hipStreamSynchronize(stream));
+        if (staged) {
+            std::memcpy(nA, out, sizeof(double) * cells);
+            std::memcpy(nB, out + cells, sizeof(double) * cells);
+        }
         return SCF_OK;
     }
 };
@@ -939,11 +960,13 @@ int scf_step(scf_ctx* ctx, int64_t nsteps) {
 int scf_observe(scf_ctx* ctx, scf_obs* out) {
     if (!ctx || !out) return fail(SCF_EINVAL, "NULL argument");
     Engine& e = ctx->e;
-    HIP_TRY(e.launch_obs(e.stream, 0));
-    scf::ObsRec r;
-    HIP_TRY(hipMemcpyAsync(&r, e.d_now(), sizeof r, hipMemcpyDeviceToHost, e.stream));
-    HIP_TRY(hipStreamSynchronize(e.stream));
     static_assert(sizeof(scf::ObsRec) == sizeof(scf_obs), "record layout");
+    const bool staged = e.stage.holds(sizeof(scf::ObsRec) * e.nchan);
+    HIP_TRY(e.launch_obs(staged ? reinterpret_cast<scf::ObsRec*>(e.stage.p) : e.d_now()));
+    scf::ObsRec r;
+    if (!staged) HIP_TRY(hipMemcpyAsync(&r, e.d_now(), sizeof r, hipMemcpyDeviceToHost, e.stream));
+    HIP_TRY(hipStreamSynchronize(e.stream));
+    if (staged) std::memcpy(&r, e.stage.p, sizeof r);
     std::memcpy(out, &r, sizeof r);
     out->t = e.t;
     e.seen_flags = out->flags;
@@ -1116,17 +1139,28 @@ int scf_batch_step(scf_batch* b, int64_t nsteps) {
 int scf_batch_observe(scf_batch* b, scf_obs* out, int64_t* nsamples) {
     if (!b || !out || !nsamples) return fail(SCF_EINVAL, "NULL argument");
     Engine& e = b->e;
-    const size_t n = (size_t)e.nchan * e.max_samples;
-    std::vector<scf::ObsRec> h(n);
-    HIP_TRY(hipMemcpyAsync(h.data(), e.d_ring(), sizeof(scf::ObsRec) * n, hipMemcpyDeviceToHost, e.stream));
-    HIP_TRY(hipStreamSynchronize(e.stream));
+    // the recorded part of every channel's ring, packed
     const int64_t have = std::min<int64_t>(e.recorded, e.max_samples);
+    const size_t n = (size_t)e.nchan * have;
+    std::vector<scf::ObsRec> h;
+    const scf::ObsRec* rec = nullptr;
+    if (n > 0 && e.stage.holds(sizeof(scf::ObsRec) * n)) {
+        auto* to = reinterpret_cast<scf::ObsRec*>(e.stage.p);
+        HIP_TRY(scf::launch_pack_ring(e.d_ring(), e.nchan, e.max_samples, (int)have, to, e.stream));
+        rec = to;
+    } else if (n > 0) {
+        h.resize(n);
+        HIP_TRY(hipMemcpy2DAsync(h.data(), sizeof(scf::ObsRec) * have, e.d_ring(), sizeof(scf::ObsRec) * e.max_samples,
+                                 sizeof(scf::ObsRec) * have, e.nchan, hipMemcpyDeviceToHost, e.stream));
+        rec = h.data();
+    }
+    HIP_TRY(hipStreamSynchronize(e.stream));
     bool unstable = false;
     for (int c = 0; c < e.nchan; ++c)
         for (int64_t s = 0; s < e.max_samples; ++s) {
             scf_obs& o = out[(size_t)c * e.max_samples + s];
-            std::memcpy(&o, &h[(size_t)c * e.max_samples + s], sizeof o);
             if (s < have) {
+                std::memcpy(&o, &rec[(size_t)c * have + s], sizeof o);
                 o.t = s * (int64_t)e.sample_every;
                 if (o.flags & 2) unstable = true;
             } else {

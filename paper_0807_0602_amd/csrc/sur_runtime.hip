@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "scf.h"
+#include "host_stage.h"
 #include "sur_internal.h"
 
 namespace scf {
@@ -153,6 +154,7 @@ struct scf_sur {
     int train_rows = 0;
     void* scratch_dev = nullptr;     // this device's address of `scratch` (NULL: see scratch_err)
     std::string scratch_err;
+    scf::HostStage host;             // rows and predictions of host calls
 
     template <class T>
     T* at(size_t off) const { return reinterpret_cast<T*>(ws + off); }
@@ -311,6 +313,7 @@ int scf_sur_create(scf_sur** out, const scf_sur_cfg* cfg, void* dev_ws, size_t w
     if (e == hipSuccess) e = s->shadows(st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail("surrogate initialisation", e);
+    if (scf::sur::predict_fits(cfg->width)) s->host.reserve(scf::kStageBytes);
     // address of the allocation-free prediction's scratch on the current device (the one that
     // holds the workspace); a failure only disables scf_sur_predict_noalloc
     int dev = -1;
@@ -478,18 +481,29 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
         const int64_t most = (int64_t)(room / (4 * (size_t)din + 9));
         for (int64_t r0 = 0; r0 < n; r0 += most) {
             const int64_t m = std::min(most, n - r0);
+            // results and, where both fit, rows go through page-locked memory (501 rows: 27 us for 50 with
+            // copies, 32064 rows: 86 for 118)
+            const size_t xb = 4 * (size_t)m * din, yb = 8 * (size_t)m;
+            const bool sy = s->host.holds(yb + m), sx = s->host.holds(al(xb) + yb + m);
             char* at = s->ws + s->p.Z;
-            float* Xd = reinterpret_cast<float*>(at);
-            float* Yd = reinterpret_cast<float*>(at + al(4 * (size_t)m * din));
+            float* Xd = reinterpret_cast<float*>(sx ? s->host.p : at);
+            float* Yd = reinterpret_cast<float*>(sy ? s->host.p + (sx ? al(xb) : 0) : at + al(xb));
             uint8_t* in = reinterpret_cast<uint8_t*>(Yd + 2 * m);
-            SUR_TRY(hipMemcpyAsync(Xd, X + r0 * din, sizeof(float) * m * din, hipMemcpyHostToDevice, s->stream));
+            if (sx) std::memcpy(Xd, X + r0 * din, xb);
+            else SUR_TRY(hipMemcpyAsync(Xd, X + r0 * din, xb, hipMemcpyHostToDevice, s->stream));
             SUR_TRY(scf::sur::predict(Xd, m, din, s->cfg.width, s->cfg.depth, s->at<float>(s->p.mean),
                                       s->at<float>(s->p.stdv), s->at<float>(s->p.lo), s->at<float>(s->p.hi),
                                       s->have_stats, s->theta(), s->at<__bf16>(s->p.wb), Yd, in_hull ? in : nullptr,
                                       s->stream));
-            SUR_TRY(hipMemcpyAsync(Y + 2 * r0, Yd, sizeof(float) * 2 * m, hipMemcpyDeviceToHost, s->stream));
-            if (in_hull) SUR_TRY(hipMemcpyAsync(in_hull + r0, in, (size_t)m, hipMemcpyDeviceToHost, s->stream));
+            if (!sy) {
+                SUR_TRY(hipMemcpyAsync(Y + 2 * r0, Yd, yb, hipMemcpyDeviceToHost, s->stream));
+                if (in_hull) SUR_TRY(hipMemcpyAsync(in_hull + r0, in, (size_t)m, hipMemcpyDeviceToHost, s->stream));
+            }
             SUR_TRY(hipStreamSynchronize(s->stream));
+            if (sy) {
+                std::memcpy(Y + 2 * r0, Yd, yb);
+                if (in_hull) std::memcpy(in_hull + r0, in, (size_t)m);
+            }
         }
         return SCF_OK;
     }

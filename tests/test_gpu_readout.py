@@ -92,3 +92,46 @@ def test_density_of_a_3d_channel(scf, nx, ny, nz):
         _check(a.density(), a.populations(), solid, 19)
         a.density()
         assert np.array_equal(a.populations(), b.populations())
+
+
+@pytest.mark.parametrize("nx,ny", [(256, 256), (257, 256)])
+def test_density_around_the_staged_size(scf, nx, ny):
+    """65536 nodes are the most whose two fields go through page-locked memory."""
+    print(f"case: density read-out {nx} x {ny}", flush=True)
+    case = inputs.Case(inputs.Geometry(nx, ny, 64, 192), inputs.Params(gw=(-0.2, 0.2)), seed=6, liquid_x1=80)
+    a = scf.Channel.from_case(case)
+    a.step(3)
+    _check(a.density(), a.populations(), case.geom.solid_mask(), 9)
+
+
+def test_records_beyond_the_staged_size(scf):
+    """40 channels x 500 records of 64 bytes exceed the page-locked 1 MB; 40 x 100 do not."""
+    print("case: 20000 and 4000 records", flush=True)
+    cases = [inputs.Case(inputs.Geometry(24 + k, 8, 6, 16), inputs.Params(gw=(-0.2, 0.2)), seed=k, liquid_x1=8)
+             for k in range(40)]
+    few, many = (scf.Batch(cases, sample_every=1, max_samples=m) for m in (100, 500))
+    few.step(99)
+    many.step(499)
+    (ra, na), (rb, nb) = few.observe(allow_unstable=True), many.observe(allow_unstable=True)
+    assert (na, nb) == (100, 500)
+    for a, b in zip(ra, rb):
+        assert [s["t"] for s in b] == list(range(500))
+        assert repr(a) == repr(b[:100])
+
+
+@pytest.mark.parametrize("rows", [1, 36152, 36153, 117000])
+def test_predictions_around_the_staged_sizes(scf, rows):
+    """Rows and results both staged (up to 36152 rows of 5 inputs), results only, neither: the same
+    bits as in pieces of 1000."""
+    from paper_0807_0602_amd.surrogate import Network
+    print(f"case: predict {rows} rows", flush=True)
+    rng = np.random.default_rng(8)
+    net = Network(5, 128, 3, max_batch=8192, max_data=64)
+    net.set_norm(np.zeros(5, np.float32), np.ones(5, np.float32), -np.ones(5, np.float32), np.ones(5, np.float32))
+    X = rng.uniform(-1.2, 1.2, (rows, 5)).astype(np.float32)
+    Y, inside = net.predict(X)
+    for r in range(0, rows, 1000):
+        y, i = net.predict(X[r:r + 1000])
+        assert np.array_equal(y, Y[r:r + 1000]) and np.array_equal(i, inside[r:r + 1000])
+    assert np.array_equal(inside.astype(bool), (np.abs(X) <= 1.0).all(1))
+    net.close()
