@@ -115,10 +115,10 @@ typedef struct {
     int32_t blocks_per_cu; /* persistent schedules: blocks launched per compute unit, 0 = as many
                              as the kernel's occupancy allows; scf_get_tile reports the number
                              the two-step (fuse = 2) or single-step list uses.  With fuse = 2 and 0
-                             (or, persistent, the full occupancy) boxes of up to about 0.86 M nodes
+                             (or, persistent, the full occupancy) boxes of up to about 0.7 M nodes
                              in all run a node-parallel kernel of up to four steps per launch in
-                             place of the tiles above, and persistent ones of up to about 2 M nodes
-                             64-column tiles; any other number keeps the tiles as given. */
+                             place of the tiles above, and larger ones (higher than about 9 rows) a
+                             pipelined one of four; any other number keeps the tiles as given. */
 } scf_tile;
 
 enum { SCF_ORDER_STRIPS = 0, SCF_ORDER_BANDS = 1, SCF_ORDER_XCD = 2, SCF_ORDER_PERSIST = 4 };

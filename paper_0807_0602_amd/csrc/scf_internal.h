@@ -70,6 +70,15 @@ hipError_t launch_step_fused(int bx, bool masked, const Chan* chans, const TileD
 hipError_t launch_step_fused2(int bx, bool masked, const Chan* chans, const TileDesc* tiles,
                               int ntiles, const int32_t* first, int grid, float* ws, int src,
                               hipStream_t s);
+// k = 2..4 time steps of a large box per pass, k wavefront groups of kPipeCols columns (see
+// k_step_pipe): `grid` blocks, block b runs tiles [first[b], first[b+1]), each at most
+// pipe_out_x(kPipeSteps) columns wide.
+constexpr int kPipeCols = 256, kPipeSteps = 4;
+// Rows of a tile's stream: its own, 2k - 1 before and after, and one more for an even number.
+__host__ __device__ inline int pipe_rows(int rows, int k) { return (rows + 2 * (2 * k - 1) + 1) & ~1; }
+constexpr int pipe_out_x(int k) { return kPipeCols - 2 * (2 * k - 1); }
+hipError_t launch_step_pipe(int k, bool masked, const Chan* chans, const TileDesc* tiles, const int32_t* first, int grid,
+                            float* ws, int src, hipStream_t s);
 // k = 1..4 time steps of a small tile per launch, one thread per node (see k_step_region).  The
 // block's region of nodes is 22 x 23 or 32 x 32; its output tile is 2 (2k - 1) nodes smaller each
 // way.  `one` holds a single channel's constants, its tiles following from the block index; with

@@ -246,28 +246,43 @@ __device__ __forceinline__ void relax_store(const float* f, float n, float ux, f
     for (int i = 0; i < 9; ++i) out(qbase + i, __builtin_fmaf(om, D[i], f[i]));
 }
 
-// Collide one fluid node: f holds its pulled populations (A then B), nA/nB their sums,
-// sAx.. the weighted neighbour sums of n_A and n_B, swx/swy the weighted solid-neighbour sum.
-template <class Out>
-__device__ __forceinline__ void collide_store(const Chan& c, const float f[18], float nA, float nB,
-                                              float sAx, float sAy, float sBx, float sBy, float swx,
-                                              float swy, const Out& out) {
+// Common velocity U of a node's pulled populations f (A then B) with sums nA, nB.
+__device__ __forceinline__ void common_velocity(const Chan& c, const float f[18], float nA, float nB, float& Ux,
+                                                float& Uy) {
     const float jAx = (f[1] - f[3]) + (f[5] - f[6]) + (f[8] - f[7]);
     const float jAy = (f[2] - f[4]) + (f[5] - f[7]) + (f[6] - f[8]);
     const float jBx = (f[10] - f[12]) + (f[14] - f[15]) + (f[17] - f[16]);
     const float jBy = (f[11] - f[13]) + (f[14] - f[16]) + (f[15] - f[17]);
+    const float den = __builtin_fmaf(c.wm[0], nA, c.wm[1] * nB);
+    Ux = __builtin_fmaf(c.wm[0], jAx, c.wm[1] * jBx) / den;
+    Uy = __builtin_fmaf(c.wm[0], jAy, c.wm[1] * jBy) / den;
+}
+
+// Collide one fluid node: f holds its pulled populations (A then B), nA/nB their sums, Ux/Uy their
+// common velocity, sAx.. the weighted neighbour sums of n_A and n_B, swx/swy the weighted
+// solid-neighbour sum.
+template <class Out>
+__device__ __forceinline__ void force_relax(const Chan& c, const float f[18], float nA, float nB, float Ux, float Uy,
+                                            float sAx, float sAy, float sBx, float sBy, float swx, float swy,
+                                            const Out& out) {
     // a_k = F_k / n_k: -G sum w n_kbar(x+c) c  -  G_kw sum w s(x+c) c
     const float aAx = __builtin_fmaf(-c.G, sBx, -(c.gw[0] * swx));
     const float aAy = __builtin_fmaf(-c.G, sBy, -(c.gw[0] * swy));
     const float aBx = __builtin_fmaf(-c.G, sAx, -(c.gw[1] * swx));
     const float aBy = __builtin_fmaf(-c.G, sAy, -(c.gw[1] * swy));
-    const float den = __builtin_fmaf(c.wm[0], nA, c.wm[1] * nB);
-    const float Ux = __builtin_fmaf(c.wm[0], jAx, c.wm[1] * jBx) / den;
-    const float Uy = __builtin_fmaf(c.wm[0], jAy, c.wm[1] * jBy) / den;
     relax_store(f, nA, __builtin_fmaf(c.tm[0], aAx, Ux), __builtin_fmaf(c.tm[0], aAy, Uy), c.c1[0],
                 c.omega[0], out, 0);
     relax_store(f + 9, nB, __builtin_fmaf(c.tm[1], aBx, Ux), __builtin_fmaf(c.tm[1], aBy, Uy),
                 c.c1[1], c.omega[1], out, 9);
+}
+
+template <class Out>
+__device__ __forceinline__ void collide_store(const Chan& c, const float f[18], float nA, float nB,
+                                              float sAx, float sAy, float sBx, float sBy, float swx,
+                                              float swy, const Out& out) {
+    float Ux, Uy;
+    common_velocity(c, f, nA, nB, Ux, Uy);
+    force_relax(c, f, nA, nB, Ux, Uy, sAx, sAy, sBx, sBy, swx, swy, out);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -647,6 +662,193 @@ k_step_fused2(const Chan* __restrict__ chans, const TileDesc* __restrict__ tiles
         }
         __syncthreads();
     }
+}
+
+// ---------------------------------------------------------------------------------------------
+// K time steps per pass of a large box, one wavefront group per step.  A block of K x kPipeCols lanes
+// walks a strip upward; group st (kPipeCols lanes, one column each) computes step st of row after
+// row, three rows behind the group before it, and hands the post-collision populations of a row to
+// the next group through LDS, so that only the first group reads the source buffer and only the last
+// one writes.  An iteration of a group pulls its next row (the first from registers that a load an
+// iteration ahead has filled, the others from the rows that the group before has left), forms its
+// densities and the velocity of the row pulled before, and after a barrier collides that row; a
+// second barrier ends it.  LDS keeps a row only as long as its pull needs it: populations with c_y =
+// -1 and 0 two rows, with c_y = +1 three (a node that bounces back looks for its own row), densities
+// three; 600 bytes per column at K = 4, which fills the CU with one block of 16 wavefronts, one of
+// each step on every SIMD.  A tile's first and last 2K - 1 rows and columns are only its neighbours'
+// values, taken one step less far by each group, and a block's tiles follow one another without a
+// drain.  All columns compute alike, those whose neighbours are not there included: what they get
+// wrong spreads two columns per step and stays within the halo.
+//
+// Bound by its vector arithmetic: 245 instructions per node and step, 85-90 % of the cycles at 16384
+// x 1024, where it moves 4.2 TB/s.  us per step there against the two-step walk (5.0 TB/s, 159 bytes
+// per node and pass): 157 for 272; K = 3 208, K = 2 over 350.  One code path per role: with the roles
+// decided per row, copies and waits for loads just issued took it to 222.
+// ---------------------------------------------------------------------------------------------
+template <int K>
+struct PipeLds {
+    static constexpr int BX = kPipeCols;
+    float2 front[8];             // x - 1 of the first column
+    float2 n[K][3][BX];          // densities (A, B) of the last three rows pulled by each step
+    // post-collision populations between step b and b + 1, by the row their pull looks for them in:
+    // c_y = -1, 0, +1, three directions each
+    float2 m[K - 1][2][3][BX], z[K - 1][2][3][BX], p[K - 1][3][3][BX];
+    float2 back[8];
+};
+
+// Row group of direction i (-1: m, 0: z, 1: p) and its place there.
+__device__ constexpr int kPipeRow[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
+__device__ constexpr int kPipeSlot[9] = {0, 1, 0, 2, 0, 1, 2, 1, 2};
+
+// The role of one wavefront group: step `st` of the K.  FIRST pulls from the source buffer, LAST
+// stores to the destination; the others work from LDS to LDS.
+template <int K, bool MASK, bool FIRST, bool LAST>
+__device__ __forceinline__ void pipe_role(PipeLds<K>& s, int st, const Chan* __restrict__ chans,
+                                          const TileDesc* __restrict__ tiles, int t_beg, int t_end,
+                                          float* __restrict__ ws, int src) {
+    constexpr int BX = kPipeCols, H = 2 * K - 1, LAG = 3;
+    const int opp[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
+    const int dx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
+    const int col = (int)threadIdx.x % BX;
+    float fa[18], fb[18];   // the row pulled in this iteration and the one before, in turn
+#pragma unroll
+    for (int i = 0; i < 18; ++i) fa[i] = fb[i] = 0.0f;
+    float qA = 0.0f, qB = 0.0f;
+    uint32_t qcode = 0;
+    int k2 = st & 1, k3 = 0;   // iteration number mod 2 and mod 3
+    for (int i = 0; i < LAG * st; ++i) {
+        __syncthreads();
+        __syncthreads();
+    }
+    for (int t = t_beg; t < t_end; ++t) {
+        const TileDesc td = tiles[t];
+        const Chan c = chans[td.chan];
+        const int len = pipe_rows(td.ye - td.yb, K), w = min(td.w, c.nx - td.xb);
+        const int x = wrap_mod(td.xb - H + col, c.nx);
+        const bool in = col >= H && col < H + w;
+        const bool masked = MASK && c.masked;
+        const int64_t buf_bytes = (int64_t)18 * c.plane * 4;
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(ws + c.off + (int64_t)src * 18 * c.plane, buf_bytes);
+        const __amdgpu_buffer_rsrc_t rd = make_rsrc(ws + c.off + (int64_t)(src ^ 1) * 18 * c.plane, buf_bytes);
+        const uint32_t Pb = (uint32_t)(c.plane * 4);
+        int y = wrap_mod(td.yb - H, c.ny), yq = y;
+        // codes of row y and of the row after it
+        bool wall = masked || near_wall(c, y), qwall = false;
+        uint32_t code = 0, code1 = 0;
+        if (masked) {
+            code = mask_code(c, ws, x, y);
+            code1 = mask_code(c, ws, x, inc_wrap(y, c.ny));
+        } else if (wall) {
+            code = rows_code(c, x, y);
+        }
+        float pn[18];
+        auto fetch = [&]() {
+            if (wall) pull18_buf<true>(rs, Pb, c, x, y, code, pn);
+            else pull18_buf<false>(rs, Pb, c, x, y, 0u, pn);
+        };
+        if (FIRST) fetch();
+        auto row = [&](int pos, float (&f)[18], const float (&q)[18]) {
+            const int k3p = k3 == 2 ? 0 : k3 + 1, k3m = k3 == 0 ? 2 : k3 - 1;
+            __syncthreads();
+            if (FIRST) {
+#pragma unroll
+                for (int i = 0; i < 18; ++i) f[i] = pn[i];
+            } else {
+                const float2* fm = &s.m[st - 1][k2 ^ 1][0][col];
+                const float2* fz = &s.z[st - 1][k2][0][col];
+                const float2* fp = &s.p[st - 1][k3][0][col];
+#pragma unroll
+                for (int i = 0; i < 9; ++i) {
+                    const float2 v = (kPipeRow[i] < 0 ? fm : kPipeRow[i] > 0 ? fp : fz)[kPipeSlot[i] * BX - dx[i]];
+                    f[i] = v.x;
+                    f[9 + i] = v.y;
+                }
+                if (wall) {
+                    // bounced populations: the node's own, of the opposite direction
+                    const float2* om = &s.m[st - 1][k2][0][col];
+                    const float2* op = &s.p[st - 1][k3p][0][col];
+#pragma unroll
+                    for (int i = 1; i < 9; ++i) {
+                        const int d = opp[i];
+                        const float2 v = (kPipeRow[d] < 0 ? om : kPipeRow[d] > 0 ? op : fz)[kPipeSlot[d] * BX];
+                        const bool b = (code >> d) & 1u;
+                        f[i] = b ? v.x : f[i];
+                        f[9 + i] = b ? v.y : f[9 + i];
+                    }
+                }
+            }
+            float Ux, Uy;
+            common_velocity(c, q, qA, qB, Ux, Uy);
+            asm volatile("" : "+v"(Ux), "+v"(Uy));   // before the barrier: the row's loads are on their way
+            float nA = sum9(f), nB = sum9(f + 9);
+            if (wall) {
+                nA = code & 1u ? 0.0f : nA;
+                nB = code & 1u ? 0.0f : nB;
+            }
+            s.n[st][k3][col] = make_float2(nA, nB);
+            __syncthreads();
+            const int yc = yq;
+            const uint32_t ccode = qcode;
+            const bool cwall = qwall;
+            yq = y;
+            qcode = code;
+            qwall = wall;
+            y = inc_wrap(y, c.ny);
+            wall = masked || near_wall(c, y);
+            code = 0;
+            if (masked) {
+                code = code1;
+                code1 = mask_code(c, ws, x, inc_wrap(y, c.ny));
+            } else if (wall) {
+                code = rows_code(c, x, y);
+            }
+            if (FIRST) fetch();   // in flight for the rest of the iteration
+            // the row pulled one iteration ago
+            const float2 *nm = &s.n[st][k3p][col], *no = &s.n[st][k3m][col], *np = &s.n[st][k3][col];
+            const float2 E = no[1], W = no[-1], N = np[0], S = nm[0], NE = np[1], NW = np[-1], SW = nm[-1], SE = nm[1];
+            const float sAx = link_sum(E.x, W.x, NE.x, SW.x, SE.x, NW.x), sAy = link_sum(N.x, S.x, NE.x, SW.x, NW.x, SE.x);
+            const float sBx = link_sum(E.y, W.y, NE.y, SW.y, SE.y, NW.y), sBy = link_sum(N.y, S.y, NE.y, SW.y, NW.y, SE.y);
+            float swx = 0.0f, swy = 0.0f;
+            if (cwall) wall_sum(ccode, swx, swy);
+            if (!LAST) {
+                float g[18];
+                force_relax(c, q, qA, qB, Ux, Uy, sAx, sAy, sBx, sBy, swx, swy, RegOut{g});
+                float2* om = &s.m[LAST ? 0 : st][k2][0][col];
+                float2* oz = &s.z[LAST ? 0 : st][k2][0][col];
+                float2* op = &s.p[LAST ? 0 : st][k3][0][col];
+#pragma unroll
+                for (int i = 0; i < 9; ++i)
+                    (kPipeRow[i] < 0 ? om : kPipeRow[i] > 0 ? op : oz)[kPipeSlot[i] * BX] = make_float2(g[i], g[9 + i]);
+            } else if (in && pos > H && pos <= H + td.ye - td.yb && !(ccode & 1u)) {
+                force_relax(c, q, qA, qB, Ux, Uy, sAx, sAy, sBx, sBy, swx, swy,
+                            BufferOutCached{rd, Pb, ((uint32_t)yc * (uint32_t)c.pitch + (uint32_t)x) * 4u});
+            }
+            qA = nA;
+            qB = nB;
+            k2 ^= 1;
+            k3 = k3p;
+        };
+        for (int r = 0; r < len; r += 2) {
+            row(r, fa, fb);
+            row(r + 1, fb, fa);
+        }
+    }
+    for (int i = 0; i < LAG * (K - 1 - st); ++i) {
+        __syncthreads();
+        __syncthreads();
+    }
+}
+
+template <int K, bool MASK>
+__global__ void __launch_bounds__(K * kPipeCols)
+k_step_pipe(const Chan* __restrict__ chans, const TileDesc* __restrict__ tiles, const int32_t* __restrict__ first,
+            float* __restrict__ ws, int src) {
+    __shared__ PipeLds<K> s;
+    const int st = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kPipeCols);
+    const int t_beg = first[blockIdx.x], t_end = first[blockIdx.x + 1];
+    if (st == 0) pipe_role<K, MASK, true, false>(s, 0, chans, tiles, t_beg, t_end, ws, src);
+    else if (st == K - 1) pipe_role<K, MASK, false, true>(s, K - 1, chans, tiles, t_beg, t_end, ws, src);
+    else pipe_role<K, MASK, false, false>(s, st, chans, tiles, t_beg, t_end, ws, src);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1142,6 +1344,14 @@ hipError_t launch_region_k(bool masked, const Chan& one, const Chan* chans, cons
     return hipGetLastError();
 }
 
+template <int K>
+hipError_t launch_pipe_k(bool masked, const Chan* chans, const TileDesc* tiles, const int32_t* first, int grid, float* ws,
+                         int src, hipStream_t s) {
+    if (masked) hipLaunchKernelGGL((k_step_pipe<K, true>), dim3(grid), dim3(K * kPipeCols), 0, s, chans, tiles, first, ws, src);
+    else hipLaunchKernelGGL((k_step_pipe<K, false>), dim3(grid), dim3(K * kPipeCols), 0, s, chans, tiles, first, ws, src);
+    return hipGetLastError();
+}
+
 template <int RX, int RY, int T>
 hipError_t launch_region_of(int k, bool masked, const Chan& one, const Chan* chans, const TileDesc* tiles, int ntiles,
                             float* ws, int src, hipStream_t s) {
@@ -1219,6 +1429,17 @@ int resident_blocks_per_cu(int bx, bool masked, int fuse) {
         case 256: return resident_bx<256>(masked, fuse);
         case 512: return resident_bx<512>(masked, fuse);
         default: return 0;
+    }
+}
+
+hipError_t launch_step_pipe(int k, bool masked, const Chan* chans, const TileDesc* tiles, const int32_t* first, int grid,
+                            float* ws, int src, hipStream_t s) {
+    if (grid <= 0) return hipErrorInvalidValue;
+    switch (k) {
+        case 2: return launch_pipe_k<2>(masked, chans, tiles, first, grid, ws, src, s);
+        case 3: return launch_pipe_k<3>(masked, chans, tiles, first, grid, ws, src, s);
+        case 4: return launch_pipe_k<4>(masked, chans, tiles, first, grid, ws, src, s);
+        default: return hipErrorInvalidValue;
     }
 }
 

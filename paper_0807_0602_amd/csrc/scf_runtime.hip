@@ -43,11 +43,13 @@ constexpr int kMaxRowsPerGeom = 1 << 20;
 // rows where a channel is taller (each band pays the pipeline's start-up rows once).
 constexpr int kMaxPersistBlocks = 8192;
 constexpr int kMinRange = 16;
-constexpr double kNarrowBlocksPerCu = 7.25;
-constexpr double kNarrowMaxRows = 21.0;
+constexpr int kPipeMinRows = 8;        // fewest rows a block of the pipelined step takes of a strip
+constexpr int kPipeLead = 2 * (2 * scf::kPipeSteps - 1);   // rows of a tile's stream beyond its own
+constexpr int kPipeWide = 240, kPipeAligned = 224;         // strip widths
+static_assert(kPipeWide <= scf::pipe_out_x(scf::kPipeSteps), "a strip and its halo fit the block");
 // Version of the schedule space and kernels in the autotuner cache key (a cached schedule from
 // another version is timed again).
-constexpr int kTuneVersion = 6;
+constexpr int kTuneVersion = 7;
 constexpr int kPlanesPerChannel = 38;   // 2 x 18 population planes + 2 density planes
 
 // Float planes of one channel: populations and densities, plus one for the uint16 codes of a
@@ -188,7 +190,7 @@ struct Engine {
     // steps per launch of the node-parallel step (0: the row-walking kernels run), its region and,
     // per step count, its tiles (in d_tiles2() from entry region_first when nchan > 1)
     int region_k = 0, region = 0;
-    bool narrow = false;   // the two-step list holds 64-lane tiles (see narrow_rows)
+    bool pipe = false;   // the two-step list holds the tiles of the pipelined step, which runs instead
     int region_tiles[scf::kRegionMaxSteps + 1] = {}, region_first[scf::kRegionMaxSteps + 1] = {};
     float tuned_ms = 0.0f;   // time per step of the last autotuned schedule
     hipGraphExec_t g_steps[2] = {nullptr, nullptr};
@@ -302,6 +304,31 @@ struct Engine {
         return nb;
     }
 
+    // Run j of the nb runs (tiles [starts[j], starts[j+1]) of t0) goes to block b; with the XCD order, XCD
+    // x's runs [nb x / 8, nb (x + 1) / 8) are spread evenly over its nblocks / 8 slots.
+    static void deal_runs(const std::vector<scf::TileDesc>& t0, const std::vector<int32_t>& starts, int nb, int nblocks,
+                          int ord, std::vector<scf::TileDesc>& tl, std::vector<int32_t>& first) {
+        const bool xcd = (ord & SCF_ORDER_XCD) && nblocks % 8 == 0;
+        tl.clear();
+        first.assign((size_t)nblocks + 1, 0);
+        for (int b = 0; b < nblocks; ++b) {
+            first[b] = (int32_t)tl.size();
+            int64_t j0, j1;
+            if (xcd) {
+                const int x = b % 8, i = b / 8, per = nblocks / 8;
+                const int64_t e0 = (int64_t)nb * x / 8, e1 = (int64_t)nb * (x + 1) / 8;
+                j0 = e0 + (e1 - e0) * i / per;
+                j1 = e0 + (e1 - e0) * (i + 1) / per;
+            } else {
+                j0 = (int64_t)nb * b / nblocks;
+                j1 = (int64_t)nb * (b + 1) / nblocks;
+            }
+            for (int64_t j = j0; j < j1; ++j)
+                for (int32_t t = starts[(size_t)j]; t < starts[(size_t)j + 1]; ++t) tl.push_back(t0[(size_t)t]);
+        }
+        first[nblocks] = (int32_t)tl.size();
+    }
+
     // Persistent schedule over strips `stripw` wide for `nblocks` blocks (one round: every block
     // resident at once).  Each block runs a contiguous run of the (channel, band, strip) list, so
     // horizontally adjacent tiles run at the same time and share the cache lines at their edges.
@@ -347,27 +374,53 @@ struct Engine {
         std::vector<int32_t> starts;
         const int nb = pack_tiles(t0, best, warm, &starts);
         starts.push_back((int32_t)t0.size());
-        // run j of the nb runs goes to block b; with the XCD order, XCD x's runs
-        // [nb x / 8, nb (x + 1) / 8) are spread evenly over its nblocks / 8 slots
-        const bool xcd = (ord & SCF_ORDER_XCD) && nblocks % 8 == 0;
-        tl.clear();
-        first.assign((size_t)nblocks + 1, 0);
-        for (int b = 0; b < nblocks; ++b) {
-            first[b] = (int32_t)tl.size();
-            int64_t j0, j1;
-            if (xcd) {
-                const int x = b % 8, i = b / 8, per = nblocks / 8;
-                const int64_t e0 = (int64_t)nb * x / 8, e1 = (int64_t)nb * (x + 1) / 8;
-                j0 = e0 + (e1 - e0) * i / per;
-                j1 = e0 + (e1 - e0) * (i + 1) / per;
-            } else {
-                j0 = (int64_t)nb * b / nblocks;
-                j1 = (int64_t)nb * (b + 1) / nblocks;
-            }
-            for (int64_t j = j0; j < j1; ++j)
-                for (int32_t t = starts[(size_t)j]; t < starts[(size_t)j + 1]; ++t) tl.push_back(t0[(size_t)t]);
+        deal_runs(t0, starts, nb, nblocks, ord, tl, first);
+    }
+
+    // Tiles of the pipelined step: the channels' strips one after the other, cut wherever a block is
+    // full, so that every block goes through about the same number of rows (a tile's own and kPipeLead;
+    // whole bands of equal height left the blocks 12 % longer runs at 16384 x 1024).  The XCDs take
+    // contiguous eighths of the runs.
+    void make_tiles_pipe(int stripw, int nblocks, std::vector<scf::TileDesc>& tl, std::vector<int32_t>& first) const {
+        std::vector<scf::TileDesc> t0;
+        std::vector<int32_t> starts;
+        auto pack = [&](int64_t cap, bool keep) {
+            int64_t nb = 1, room = cap;
+            if (keep) starts.assign(1, 0);
+            for (int c = 0; c < nchan; ++c)
+                for (int xb = 0; xb < geom[c].nx; xb += stripw)
+                    for (int y = 0; y < geom[c].ny;) {
+                        const int64_t rows = std::min<int64_t>(geom[c].ny - y, room - kPipeLead);
+                        if (rows < std::min(kPipeMinRows, geom[c].ny - y)) {
+                            ++nb;
+                            room = cap;
+                            if (keep) starts.push_back((int32_t)t0.size());
+                            continue;
+                        }
+                        if (keep) {
+                            scf::TileDesc td;
+                            std::memset(&td, 0, sizeof td);
+                            td.chan = c;
+                            td.xb = xb;
+                            td.yb = y;
+                            td.ye = y + (int)rows;
+                            td.w = stripw;
+                            t0.push_back(td);
+                        }
+                        y += (int)rows;
+                        room -= kPipeLead + rows;
+                    }
+            return nb;
+        };
+        int64_t lo = kPipeMinRows + kPipeLead, hi = lo;
+        while (pack(hi, false) > nblocks) hi *= 2;
+        while (lo < hi) {
+            const int64_t mid = lo + (hi - lo) / 2;
+            if (pack(mid, false) <= nblocks) hi = mid; else lo = mid + 1;
         }
-        first[nblocks] = (int32_t)tl.size();
+        const int nb = (int)pack(lo, true);
+        starts.push_back((int32_t)t0.size());
+        deal_runs(t0, starts, nb, nblocks, SCF_ORDER_XCD, tl, first);
     }
 
     // Schedules that ask for the row-walking kernels as they are: an explicit number of blocks per
@@ -378,16 +431,32 @@ struct Engine {
         return bpc < scf::resident_blocks_per_cu(bxv, any_masked, 2);
     }
 
-    // Narrow two-step walk for boxes whose persistent bands would be short (every band pays six
-    // start-up rows): one 64-lane block per tile, dispatched in list order, 7.25 blocks per CU.
-    // Measured, us per step, against the persistent 256-lane bands: 8192 x 130 19.4 for 32.4,
-    // 8192 x 202 26.6 for 36.9, 8192 x 256 (19.6 rows per band) 41.3 for 45.3; 8192 x 300 (23 rows)
-    // 50.9 for 48.9: past about 1.8 M nodes both buffers leave the last-level cache, and the narrow
-    // strips' partial lines cost more than the short bands.
-    double narrow_rows() const {
-        double strip_rows = 0.0;
-        for (const scf_geometry& g : geom) strip_rows += (double)((g.nx + 57) / 58) * g.ny;
-        return std::max(2.0, strip_rows / (kNarrowBlocksPerCu * cus));
+    // The pipelined step takes every box the node-parallel one leaves (us per step, against the
+    // two-step walk: 4096 x 202 14.1 for 35.7, 8192 x 202 19.2 for 36.9, 4096 x 640 30 for 49, 16384 x
+    // 1024 157 for 272) but those so low that the rows before and after a strip cost more than its four
+    // steps per pass save: 1048000 x 20 278 for 411, x 14 219 for 288; from there a height of 9, 2.5
+    // rows gone through per row, is where the two would meet.
+    bool pipe_pays() const {
+        double rows = 0.0, strips = 0.0;
+        for (const scf_geometry& g : geom) {
+            const double n = (g.nx + kPipeWide - 1) / kPipeWide;
+            rows += n * g.ny;
+            strips += n;
+        }
+        return cus > 0 && cus <= kMaxPersistBlocks && rows + kPipeLead * strips <= 2.5 * rows;
+    }
+
+    // Strips of 240 columns, or of 224, whose edges fall on 128-byte lines.  A line that two strips
+    // share is written by both; where the neighbour strip is high it comes to it after the line has
+    // left the caches (us per step with 240 and with 224: 16384 x 1024 166 and 158, 16384 x 512 87 and
+    // 84, 32768 x 320 102 and 103, 65536 x 160 101 and 105, 4096 x 640 30.4 and 31.6).
+    int pipe_strip() const {
+        double nodes = 0.0, cols = 0.0;
+        for (const scf_geometry& g : geom) {
+            nodes += (double)g.nx * g.ny;
+            cols += g.nx;
+        }
+        return nodes > 4e6 && nodes >= 400.0 * cols ? kPipeAligned : kPipeWide;
     }
 
     // The XCD order: block b runs on XCD b mod 8, so the list is permuted to give each XCD a
@@ -407,7 +476,7 @@ struct Engine {
         return out;
     }
 
-    int64_t region_max_tiles() const { return 5 * (int64_t)cus; }
+    int64_t region_max_tiles() const { return 4 * (int64_t)cus; }
 
     int64_t region_count(int rg, int k) const {
         const int ox = scf::region_out_x(rg, k), oy = scf::region_out_y(rg, k);
@@ -421,8 +490,8 @@ struct Engine {
     // K stages whatever the box.  The most steps per launch whose tiles all run at once, one block
     // per CU, are the fastest per step (200 x 24: 2.1 us with 75 small regions of 4 steps, 2.8 with
     // large ones; 4096 x 22: 3.5 us with 187 regions of 3 steps, 5.8 with 456 of 4).  Beyond, two
-    // steps per launch, up to five blocks per CU: at 4096 x 202 (4.9) 15.8 us against 16.9 for the
-    // walk, at 8192 x 202 (9.9) 27.9 against 26.6.
+    // steps per launch, up to four blocks per CU: at 2048 x 300 (3.7) 11.8 us against 12.7 for the
+    // pipelined step, at 4096 x 202 (4.9) 14.4 against 14.1.
     void plan_regions(std::vector<scf::TileDesc>& tl, std::vector<scf::TileDesc>& walk) {
         region_k = 0;
         struct Pick { int region, k; int64_t most; };
@@ -476,27 +545,32 @@ struct Engine {
         std::vector<scf::TileDesc> tl, tl2;
         std::vector<int32_t> f1, f2;
         int g1 = 0, g2 = 0;
-        narrow = false;
         if (ord & SCF_ORDER_PERSIST) {
             g1 = persist_blocks(bxv, 1, ord);
             g2 = persist_blocks(bxv, 2, ord);
             if (!g1 || !g2) return fail(SCF_EDEVICE, "occupancy query for the persistent schedule failed");
             make_tiles_persist(bxv, 2, g1, ord, tl, f1);
             make_tiles_persist(strip2(bxv), 6, g2, ord, tl2, f2);
-            narrow = !walk_forced(bxv, ord) && narrow_rows() <= kNarrowMaxRows;
-            if (narrow) {
-                band_tiles(strip2(64), narrow_rows(), tl2);
-                if (ord & SCF_ORDER_XCD) tl2 = deal_to_xcds(tl2);
-            }
         } else {
             tl = make_tiles(bxv, cyv, ord);
             tl2 = make_tiles(strip2(bxv), cyv, ord);
         }
-        const int n2 = (int)tl2.size();
+        int n2 = (int)tl2.size();
         region_k = 0;
+        pipe = false;
         if (!walk_forced(bxv, ord)) {
-            std::vector<scf::TileDesc> rl;
-            plan_regions(rl, tl2);
+            std::vector<scf::TileDesc> more;
+            plan_regions(more, tl2);
+            if (!region_k && pipe_pays()) {
+                std::vector<int32_t> f;
+                make_tiles_pipe(pipe_strip(), cus, more, f);
+                pipe = (int)more.size() <= lay.max_tiles;
+                if (pipe) {
+                    tl2 = more;
+                    n2 = (int)tl2.size();
+                    f2 = f;
+                }
+            }
         }
         if ((int)tl.size() > lay.max_tiles || (int)tl2.size() > lay.max_tiles)
             return fail(SCF_EINVAL, "tile list exceeds its reserved space");
@@ -504,10 +578,10 @@ struct Engine {
                                hipMemcpyHostToDevice, stream));
         HIP_TRY(hipMemcpyAsync(d_tiles2(), tl2.data(), sizeof(scf::TileDesc) * tl2.size(),
                                hipMemcpyHostToDevice, stream));
-        if (ord & SCF_ORDER_PERSIST) {
+        if (!f1.empty())
             HIP_TRY(hipMemcpyAsync(d_first(), f1.data(), sizeof(int32_t) * f1.size(), hipMemcpyHostToDevice, stream));
+        if (!f2.empty())
             HIP_TRY(hipMemcpyAsync(d_first2(), f2.data(), sizeof(int32_t) * f2.size(), hipMemcpyHostToDevice, stream));
-        }
         HIP_TRY(hipStreamSynchronize(stream));
         ntiles = (int)tl.size();
         ntiles2 = n2;
@@ -519,10 +593,10 @@ struct Engine {
         return SCF_OK;
     }
 
-    // Most steps one launch advances: two with fuse = 2, or the node-parallel step's.
+    // Most steps one launch advances: two with fuse = 2, or the node-parallel or pipelined step's.
     int max_steps() const {
         if (variant != SCF_VARIANT_FUSED || fuse != 2) return 1;
-        return region_k > 0 ? region_k : 2;
+        return region_k > 0 ? region_k : pipe ? scf::kPipeSteps : 2;
     }
 
     int steps_of_launch(int64_t n) const { return (int)std::min<int64_t>(n, max_steps()); }
@@ -534,9 +608,11 @@ struct Engine {
             return scf::launch_step_region(region, k, any_masked, chans[0], d_chans(),
                                            nchan == 1 ? nullptr : d_tiles2() + region_first[k], region_tiles[k], base(),
                                            src, s);
+        if (k >= 2 && pipe)
+            return scf::launch_step_pipe(k, any_masked, d_chans(), d_tiles2(), d_first2(), cus, base(), src, s);
         if (k == 2)
-            return scf::launch_step_fused2(narrow ? 64 : bx, any_masked, d_chans(), d_tiles2(), ntiles2,
-                                           p && !narrow ? d_first2() : nullptr, narrow ? 0 : grid2, base(), src, s);
+            return scf::launch_step_fused2(bx, any_masked, d_chans(), d_tiles2(), ntiles2, p ? d_first2() : nullptr,
+                                           grid2, base(), src, s);
         if (variant == SCF_VARIANT_TWO_KERNEL)
             return scf::launch_step_two_kernel(d_chans(), d_rows(), lay.nrows, base(), src, s);
         return scf::launch_step_fused(bx, any_masked, d_chans(), d_tiles(), ntiles, p ? d_first() : nullptr,
@@ -778,8 +854,8 @@ struct Engine {
         for (int ord : {(int)SCF_ORDER_PERSIST, (int)(SCF_ORDER_PERSIST | SCF_ORDER_XCD)})
             for (int bxv : bxs)
                 for (int k = 1; k <= 2; ++k) cands.push_back({bxv, cy, ord, k, 0.0f});
-        // where the node-parallel step runs (see plan_regions) every two-step schedule is that kernel
-        if (region_count(scf::kRegionLarge, 2) <= region_max_tiles()) {
+        // where the node-parallel or the pipelined step runs, every two-step schedule is that kernel
+        if (region_count(scf::kRegionLarge, 2) <= region_max_tiles() || pipe_pays()) {
             cands.erase(std::remove_if(cands.begin(), cands.end(), [](const Cand& c) { return c.fuse == 2; }), cands.end());
             cands.push_back({256, 16, SCF_ORDER_PERSIST | SCF_ORDER_XCD, 2, 0.0f});
         }

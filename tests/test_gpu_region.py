@@ -1,6 +1,6 @@
-"""The node-parallel step of small boxes (1-4 steps per launch, see k_step_region) and the narrow
-two-step walk of middle ones, bit for bit against the two-kernel step: every number of steps per
-launch, remainders, tiles ragged at the box edge, boxes smaller than a region, masks and batches.
+"""The node-parallel step of small boxes (1-4 steps per launch, see k_step_region), bit for bit
+against the two-kernel step: every number of steps per launch, remainders, tiles ragged at the box
+edge, boxes smaller than a region, masks and batches; and boxes just past it.
 The row-walking kernels, which small boxes reach only with an explicit number of blocks per CU,
 keep their own cases here."""
 import numpy as np
@@ -35,8 +35,8 @@ def _reference(S, case, steps):
 
 
 # (box, mask, steps): small regions with four steps per launch (3 x 3 up to their 256 tiles), large
-# regions with four, three and two steps, the two-step limit of 5 x 256 tiles and one box past it
-# (the narrow walk); steps leave every remainder
+# regions with four, three and two steps, and boxes past the two-step limit of 4 x 256 tiles; steps
+# leave every remainder
 @pytest.mark.parametrize("nx,ny,x0,x1,mask", [
     (3, 3, 1, 2, False), (8, 9, 2, 6, False), (9, 10, 0, 9, False), (131, 17, 20, 111, True), (200, 24, 50, 150, False),
     (64, 288, 16, 48, True), (72, 289, 10, 60, False), (400, 97, 0, 400, True), (4096, 22, 1024, 3072, False),
