@@ -611,9 +611,10 @@ k_predict(const float* __restrict__ X, int64_t n, int d_in, int depth, const flo
 // of a hidden matrix or 16 columns of a sum, and applies Adam to what it has just summed (or
 // writes the gradient).  Every sum keeps the order of the layer kernels: a tile's products run
 // through the whole batch in one accumulator, a column's rows in 256 interleaved chains and a tree.
-// Measured, 256 x 4 with 5 inputs and 8192 rows: 42 + 45 us, for 28 launches and 594 us.  The first
-// is bound by its chain of barriers, one block of 16 waves per CU, and by 65 MB written; the second
-// by the 130 MB it reads (22 us for the tiles alone, 27 for the sums alone).
+// Measured, 256 x 4 with 5 inputs and 8192 rows: 42 + 38 us, for 28 launches and 594 us.  The first
+// is bound by its chain of barriers, one block of 16 waves per CU, in the forward half, and in the
+// backward half by the 65 MB it writes; the second by what it reads from beyond L2 and the time a
+// trip there takes (61 MB with tiles and sums dealt to the XCDs by operand, 44 us in block order).
 // ---------------------------------------------------------------------------------------------
 struct TrainData {
     const float *X, *T, *w;   // stored rows
@@ -837,10 +838,15 @@ k_train_grads(int D, int d_in, int rows, float inv_n, TrainWork wk, AdamArgs ad,
     }
     const float lr = *ad.lr;
     const int64_t plane = (int64_t)rows * W, hidden = (int64_t)W * W + W, first = (int64_t)W * d_in + W;
-    const int side = W / 32, tiles = (D - 1) * side * side, groups = W / 16;
+    constexpr int side = W / 32, groups = W / 16;
+    const int tiles = (D - 1) * side * side;
     int blk = blockIdx.x;
     if (blk < tiles) {
-        const int l = 1 + blk / (side * side), o0 = (blk / side % side) * 32, k0 = (blk % side) * 32;
+        // an XCD (block b runs on XCD b mod 8) takes the same patch of every matrix, two tiles wide, and
+        // so reads six of a layer's 16 operand strips through its L2; a column of tiles would be nine
+        constexpr int PER = side * side / 8, KG = side / 2;
+        const int x = blk & 7, i = blk >> 3, j = i % PER;
+        const int l = 1 + i / PER, o0 = (x / KG * (PER / 2) + j / 2) * 32, k0 = (x % KG * 2 + (j & 1)) * 32;
         const int lane = tid & 63, wave = tid >> 6, r = lane & 15, g = lane >> 4, wm = (wave & 1) * 16, wn = (wave >> 1) * 16;
         // chunks of CH batch rows: a thread brings 32 bytes of one row of each operand
         const int row = tid >> 3, seg = (tid & 7) * 8;
@@ -922,9 +928,10 @@ k_train_grads(int D, int d_in, int rows, float inv_n, TrainWork wk, AdamArgs ad,
         else (void)adam_one(ad, q, g, lr, corr[0], corr[1]);
     };
     const int c = tid & 15;
-    if (blk < groups * (d_in + D)) {
+    // an XCD takes the same columns of every sum (the first layer's read the same dz)
+    const int kind = (blk >> 3) / (groups / 8), n = ((blk & 7) * (groups / 8) + (blk >> 3) % (groups / 8)) * 16 + c;
+    if (kind < d_in + D) {
         // first layer: inputs k < d_in and bias; then the biases of layers 1 .. D - 1
-        const int kind = blk / groups, n = (blk % groups) * 16 + c;
         float s[1];
         float (*sh)[16][1] = reinterpret_cast<float (*)[16][1]>(&fs[0][0][0]);
         if (kind < d_in) {
@@ -945,10 +952,9 @@ k_train_grads(int D, int d_in, int rows, float inv_n, TrainWork wk, AdamArgs ad,
         }
         return;
     }
-    blk -= groups * (d_in + D);
     const int64_t out = first + (D - 1) * hidden;
-    if (blk < groups) {
-        const int k = blk * 16 + c;
+    if (kind == d_in + D) {
+        const int k = n;
         const float* h = wk.Hlast + k;
         const float* dy = wk.dY;
         float s[2];
