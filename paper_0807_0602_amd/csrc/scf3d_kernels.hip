@@ -182,12 +182,12 @@ __device__ __forceinline__ Row row_of(const Chan3& c) {
     const int nb = gridDim.x, blk = blockIdx.x, xcd = blk & 7, per = nb >> 3, rem = nb & 7;
     const int b = xcd * per + min(xcd, rem) + (blk >> 3);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row = (int64_t)(b / segs) * per_block + wave / wpr;
+    const uint32_t row = (uint32_t)(b / segs) * per_block + wave / wpr, rows = (uint32_t)c.ny * (uint32_t)c.nz;   // < 2^32
     Row r;
     r.x = (b % segs) * kThreads + (wave % wpr) * 64 + (threadIdx.x & 63);
-    r.in = wave < wpr * per_block && row < (int64_t)c.ny * c.nz && r.x < c.nx;
-    r.y = (int)(row % c.ny);
-    r.z = (int)(row / c.ny);
+    r.in = wave < wpr * per_block && row < rows && r.x < c.nx;
+    r.z = __builtin_amdgcn_readfirstlane((int)(row / (uint32_t)c.ny));
+    r.y = __builtin_amdgcn_readfirstlane((int)(row - (uint32_t)r.z * (uint32_t)c.ny));
     return r;
 }
 
@@ -299,21 +299,43 @@ k3_collide(const Chan3 c, float* __restrict__ ws, int src) {
     const int x = r.x, y = r.y, z = r.z;
     const uint32_t code = solid_code(c, x, y, z);
     if (code & 1u) return;
-    float* __restrict__ d = ws + c.off + (int64_t)(src ^ 1) * 38 * c.plane + row_at(c, y, z);
-    const float* __restrict__ nAf = ws + c.off + 76 * c.plane;
     const int xs[3] = {wrap_step(x, -1, c.nx), x, wrap_step(x, 1, c.nx)};
-    float f[38];
+    float f[38], a[19], b[19];
     pull_from<true, WIDE>(c, ws, src, x, y, z, code, f);
+    // all neighbour densities with the populations: small boxes have one wave per SIMD, which waited
+    // for them in three more turns
+    const float* __restrict__ field = ws + c.off + 76 * c.plane;
+    const __amdgpu_buffer_rsrc_t fr = make_rsrc(field, (int64_t)2 * c.plane * 4);
+    const unsigned Pb = (unsigned)(c.plane * 4);
+#pragma unroll
+    for (int i = 1; i < 19; ++i) {
+        const int yn = wrap_step(y, kCY[i], c.ny), zn = wrap_step(z, kCZ[i], c.nz), xn = xs[1 + kCX[i]];
+        if (WIDE) {
+            const float* n = field + row_at(c, yn, zn);
+            a[i] = n[xn];
+            b[i] = n[c.plane + xn];
+        } else {
+            const unsigned at = __builtin_amdgcn_readfirstlane(row_bytes(c, yn, zn));
+            a[i] = bload(fr, (unsigned)xn * 4u, at);
+            b[i] = bload(fr, (unsigned)xn * 4u, at + Pb);
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
     const float nA = sum19(f), nB = sum19(f + 19);
+    float* __restrict__ d = ws + c.off + (int64_t)(src ^ 1) * 38 * c.plane + row_at(c, y, z);
+    const Pops to(c, ws, src ^ 1);
+    const unsigned row = __builtin_amdgcn_readfirstlane(row_bytes(c, y, z));
     collide(c, f, nA, nB, code,
             [&](int q, float v) {
-                if (NT) __builtin_nontemporal_store(v, d + q * c.plane + x);
-                else d[q * c.plane + x] = v;
+                if (WIDE)
+                    __builtin_nontemporal_store(v, d + q * c.plane + x);
+                else
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), q < 19 ? to.A : to.B, x * 4,
+                                                          (int)(row + (unsigned)(q % 19) * Pb), NT ? 2 : 0);
             },
-            [&](int i, float& a, float& b) {
-                const float* n = nAf + row_at(c, wrap_step(y, kCY[i], c.ny), wrap_step(z, kCZ[i], c.nz));
-                a = n[xs[1 + kCX[i]]];
-                b = n[c.plane + xs[1 + kCX[i]]];
+            [&](int i, float& p, float& q) {
+                p = a[i];
+                q = b[i];
             });
 }
 
