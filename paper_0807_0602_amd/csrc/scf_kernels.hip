@@ -741,9 +741,12 @@ __device__ __forceinline__ void pipe_role(PipeLds<K>& s, int st, const Chan* __r
         } else if (wall) {
             code = rows_code(c, x, y);
         }
+        // a masked channel may have solid nodes in any row: the wavefronts without one pass by (4096 x 640
+        // with rough walls: 37.0 us per step for 39.2)
+        auto touches = [](uint32_t codes) { return !MASK || __any(codes != 0u); };
         float pn[18];
         auto fetch = [&]() {
-            if (wall) pull18_buf<true>(rs, Pb, c, x, y, code, pn);
+            if (wall && touches(code)) pull18_buf<true>(rs, Pb, c, x, y, code, pn);
             else pull18_buf<false>(rs, Pb, c, x, y, 0u, pn);
         };
         if (FIRST) fetch();
@@ -763,7 +766,7 @@ __device__ __forceinline__ void pipe_role(PipeLds<K>& s, int st, const Chan* __r
                     f[i] = v.x;
                     f[9 + i] = v.y;
                 }
-                if (wall) {
+                if (wall && touches(code)) {
                     // bounced populations: the node's own, of the opposite direction
                     const float2* om = &s.m[st - 1][k2][0][col];
                     const float2* op = &s.p[st - 1][k3p][0][col];
@@ -809,7 +812,7 @@ __device__ __forceinline__ void pipe_role(PipeLds<K>& s, int st, const Chan* __r
             const float sAx = link_sum(E.x, W.x, NE.x, SW.x, SE.x, NW.x), sAy = link_sum(N.x, S.x, NE.x, SW.x, NW.x, SE.x);
             const float sBx = link_sum(E.y, W.y, NE.y, SW.y, SE.y, NW.y), sBy = link_sum(N.y, S.y, NE.y, SW.y, NW.y, SE.y);
             float swx = 0.0f, swy = 0.0f;
-            if (cwall) wall_sum(ccode, swx, swy);
+            if (cwall && touches(ccode)) wall_sum(ccode, swx, swy);
             if (!LAST) {
                 float g[18];
                 force_relax(c, q, qA, qB, Ux, Uy, sAx, sAy, sBx, sBy, swx, swy, RegOut{g});
