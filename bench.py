@@ -7,7 +7,7 @@ densities, bulk and wall forces, common velocity, shifted equilibrium, BGK colli
 over every node.  The metric is MLUPS (million lattice-node updates per second, both
 components); the roofline object prices the dominant kernel against HBM bandwidth with its
 algorithmic traffic per launch: 144 bytes per node (2 components x 9 populations x 4 bytes, read
-once and written once) whether the launch advances one time step or two (temporal blocking keeps
+once and written once) whether the launch advances one time step or four (temporal blocking keeps
 the intermediate populations on chip).  `single_step_equiv_gbs` gives the same launch priced at
 144 bytes per node update, the bandwidth a one-step-per-launch kernel would need for the same
 MLUPS (it can pass the HBM peak).
@@ -21,7 +21,7 @@ the fraction of channels within 1 lattice unit of the LBM front and the largest 
 Prints ONE JSON line.  Options: --steps K (timed), --warmup W, --gpus N (only 1 is supported),
 --variant fused|two_kernel, --no-cpu-baseline, --calibrate-copy (runs only a plain copy kernel,
 for counter calibration under rocprofv3), --tile BX CY ORDER [FUSE] (skip the autotuner; FUSE 2
-runs two time steps per launch), --cy3 N (duct3d: rows of y per tile, 0 = two kernels),
+runs several time steps per launch), --cy3 N (duct3d: rows of y per tile, 0 = two kernels),
 --summarize-counters (fold rocprofv3 FETCH_SIZE / WRITE_SIZE CSVs into the committed traffic
 summaries), --no-sweep (skip the sweep and surrogate sub-objects).  `traffic` gives the measured
 HBM bytes per launch from the committed counter summary of the same kernel source, and
@@ -38,7 +38,7 @@ network's points/hour come from timed inference of the same curves.
 
 --workload sweep measures the batched calibration sweep instead: 64 channels with H in
 {20, 40, 80, 160}, L in {512, ..., 4096}, G_wA uniform in [-0.3, 0.3] (G_wB = -G_wA) and a
-viscosity-ratio tau pair, advanced together (one launch per step or per two steps over all their
+viscosity-ratio tau pair, advanced together (one launch per step or per four steps over all their
 tiles, HIP graphs of 100 steps plus the recorded observation), 50 000 steps with z(t) and the precursor
 recorded every 100 steps.  The value is sweep points per hour (one point = one channel's whole
 trajectory).
@@ -100,7 +100,13 @@ def measured_traffic(cells: int, schedule: dict, path: Optional[str] = None, src
 
 
 def kernel_name(fuse: int) -> str:
-    return "k_step_fused2" if fuse == 2 else "k_step_fused"
+    """The kernel of a schedule as set here (blocks_per_cu as the occupancy gives it): with fuse = 2
+    boxes of this size run the pipelined step."""
+    return "k_step_pipe" if fuse == 2 else "k_step_fused"
+
+
+def steps_per_launch(fuse: int) -> int:
+    return 4 if fuse == 2 else 1
 
 
 def parse_tile(vals):
@@ -121,6 +127,11 @@ def _counter_mean(path: str, kernel: str, counter: str) -> float:
     return sum(vals) / len(vals)
 
 
+def _has_kernel(path: str, kernel: str) -> bool:
+    import csv
+    return any(kernel in r["Kernel_Name"] for r in csv.DictReader(open(path)))
+
+
 def summarize_counters(args) -> int:
     """Fold rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE CSVs of the fused step and of the 1 GiB
     calibration copy into TRAFFIC_FILE (one entry per schedule).  Each counter is scaled by
@@ -134,7 +145,7 @@ def summarize_counters(args) -> int:
         cells, workload = nx * ny * nz, "duct3d_%dx%dx%d" % (nx, ny, nz)
         sched = {"cy": min(args.cy3, ny)}
     else:
-        path, src, label = TRAFFIC_FILE, None, "k_step_fused / k_step_fused2"
+        path, src, label = TRAFFIC_FILE, None, "k_step_fused / k_step_pipe"
         from paper_0807_0602_amd import inputs
         case = inputs.capillary_roofline(seed=1)
         cells, workload = case.geom.nx * case.geom.ny, case.name
@@ -145,7 +156,10 @@ def summarize_counters(args) -> int:
             if not args.tile:
                 raise SystemExit("--summarize-counters needs --tile BX CY ORDER")
             bx, cy, order, fuse = args.tile
-            kname = kernel_name(fuse) + "<"    # template instantiations only (not the other kernel)
+            # template instantiations only; the two-step walk where the pipelined step did not run
+            kname = kernel_name(fuse) + "<"
+            if fuse == 2 and not _has_kernel(fetch, kname):
+                kname = "k_step_fused2<"
             sched = {"bx": bx, "cy": cy, "order": order, "fuse": fuse}
     copy_kib = (1 << 30) / 1024.0
     f_scale = copy_kib / _counter_mean(fetch_copy, "copyBuffer", "FETCH_SIZE")
@@ -330,9 +344,10 @@ def sweep(args) -> int:
     sw = run_sweep(steps, args.tile)
     cells, tile = sw["cells"], sw["schedule"]
     step_s = sw["event_step_s"]
-    launch_s = step_s * tile["fuse"]
+    spl = steps_per_launch(tile["fuse"])
+    launch_s = step_s * spl
     # algorithmic bytes of one launch: 144 B per node (one read and one write of both population
-    # sets), whether it advances one step or two
+    # sets), whether it advances one step or four
     achieved = 144 * cells / launch_s / 1e9
     summ = sweep_summary(sw, steps)
     line = {
@@ -348,7 +363,7 @@ def sweep(args) -> int:
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,
                      "kernel": kernel_name(tile["fuse"]) + " (all channels per launch) + observation every 100 steps",
-                     "bytes_per_node_per_launch": 144, "steps_per_launch": tile["fuse"],
+                     "bytes_per_node_per_launch": 144, "steps_per_launch": spl,
                      "single_step_equiv_gbs": round(144 * cells / step_s / 1e9, 1)},
     }
     print(json.dumps(line), flush=True)
@@ -433,7 +448,7 @@ def duct3d(args) -> int:
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_gbs": round(traffic / step_s / 1e9, 1) if traffic else None,
                      "traffic_frac": round(traffic / step_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
-                     "kernel": ("k3_fused, %d rows of y per 64 x 4 tile" % sched["cy"]) if fused
+                     "kernel": ("k3_fused, %d rows of y per tile" % sched["cy"]) if fused
                      else "k3_density + k3_collide", "bytes_per_node_update": bpl,
                      "event_ms_per_step": round(step_s * 1e3, 5)},
         "health": {"flags": obs["flags"], "z": obs["z"], "mass": list(obs["mass"])},
@@ -603,12 +618,13 @@ def main() -> int:
 
     mlups = cells * args.steps / wall / 1e6
     step_s = ev_ms / 1e3 / args.steps
-    launch_s = step_s * fuse                   # one launch advances `fuse` steps
+    spl = steps_per_launch(fuse)
+    launch_s = step_s * spl
     bpl = BYTES_PER_LUP[args.variant]
     # algorithmic bytes of one launch: 144 B per node for the fused kernels (one read and one
-    # write of both population sets, for one step or two), 232 B per node for the two-kernel step
+    # write of both population sets, for one step or four), 232 B per node for the two-kernel step
     achieved = bpl * cells / launch_s / 1e9
-    single_equiv = bpl * cells * fuse / launch_s / 1e9
+    single_equiv = bpl * cells * spl / launch_s / 1e9
     if args.variant == "fused":
         traffic = measured_traffic(cells, tile)
     else:
@@ -624,9 +640,9 @@ def main() -> int:
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "kernel": kernel_name(fuse) if args.variant == "fused" else "k_density+k_collide",
-                     "bytes_per_node_per_launch": bpl, "steps_per_launch": fuse,
+                     "bytes_per_node_per_launch": bpl, "steps_per_launch": spl,
                      "event_ms_per_launch": round(launch_s * 1e3, 5),
-                     # the same launch priced per node update (two steps share one read and one
+                     # the same launch priced per node update (its steps share one read and one
                      # write, so this can pass the HBM peak)
                      "single_step_equiv_gbs": round(single_equiv, 1),
                      "traffic_gbs": round(traffic / launch_s / 1e9, 1) if traffic else None,

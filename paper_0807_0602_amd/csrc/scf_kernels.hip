@@ -680,10 +680,12 @@ k_step_fused2(const Chan* __restrict__ chans, const TileDesc* __restrict__ tiles
 // drain.  All columns compute alike, those whose neighbours are not there included: what they get
 // wrong spreads two columns per step and stays within the halo.
 //
-// Bound by its vector arithmetic: 245 instructions per node and step, 85-90 % of the cycles at 16384
-// x 1024, where it moves 4.2 TB/s.  us per step there against the two-step walk (5.0 TB/s, 159 bytes
-// per node and pass): 157 for 272; K = 3 208, K = 2 over 350.  One code path per role: with the roles
-// decided per row, copies and waits for loads just issued took it to 222.
+// Bound by memory at 16384 x 1024, 172 bytes per node and pass at 4.5 TB/s (a plain copy reaches
+// 4.7), and next to it by its vector arithmetic, 245 instructions per node and step: an iteration of
+// 1.93 us there, 1.45 in boxes that fit the last-level cache.  us per step against the two-step walk
+// (159 bytes, 4.9 TB/s): 157 for 272; K = 3 209, K = 2 298.  One code path per role: with the roles
+// decided per row, copies and waits for loads just issued took it to 222.  Strips start on 128-byte
+// lines: shifted by 16 columns the pulls span fewer lines, but two strips write the shared ones (181).
 // ---------------------------------------------------------------------------------------------
 template <int K>
 struct PipeLds {
