@@ -38,6 +38,8 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 constexpr int kThreads = 256;
 // Predictions of up to this many rows (16 per CU) take 16 rows per block.
 constexpr int64_t kPredictRows16 = 4096;
+// So do training batches of 256 units; of 128, whose blocks have half the threads, twice as many.
+constexpr int kTrainRows16 = 4096;
 
 // Fixed-order block reduction (kThreads threads).
 template <typename T>
@@ -604,7 +606,7 @@ k_predict(const float* __restrict__ X, int64_t n, int d_in, int depth, const flo
 }
 
 // ---------------------------------------------------------------------------------------------
-// A training step in two launches.  k_train_rows takes 32 rows through the forward pass, the loss
+// A training step in two launches.  k_train_rows takes 16 or 32 rows through the forward pass, the loss
 // and the backward pass, keeping silu'(z) of every layer in registers; it writes what the weight
 // gradients read: both transposed BF16 operands of every hidden layer, the FP32 dz of every layer
 // and the last activations.  k_train_grads reduces them over the batch, one block per 32 x 32 tile
@@ -615,6 +617,9 @@ k_predict(const float* __restrict__ X, int64_t n, int d_in, int depth, const flo
 // is bound by its chain of barriers, one block of 16 waves per CU, in the forward half, and in the
 // backward half by the 65 MB it writes; the second by what it reads from beyond L2 and the time a
 // trip there takes (61 MB with tiles and sums dealt to the XCDs by operand, 44 us in block order).
+// Where 16 rows per block fill the CUs no more than once, the chain is shorter with them: us per step
+// with 32 and with 16, 256 x 4: 64 rows 43.8 and 30.7, 1024 49.1 and 36.1, 4096 62.4 and 49.3, 6144
+// 73.4 and 75.0; 128 x 3: 64 rows 22.6 and 19.2, 4096 40.5 and 37.4, 8192 48.2 and 47.1.
 // ---------------------------------------------------------------------------------------------
 struct TrainData {
     const float *X, *T, *w;   // stored rows
@@ -625,12 +630,12 @@ struct TrainData {
     int64_t* step;            // [0] steps done, [1] the step in progress
 };
 
-template <int W, int D>
+template <int W, int D, int MT>
 __global__ void __launch_bounds__(4 * W)
 k_train_rows(const TrainData d, const float* __restrict__ theta, const __bf16* __restrict__ Wb,
              const __bf16* __restrict__ WbT, int rows, float inv_n, TrainWork wk) {
-    constexpr int T = 4 * W, MT = 2, M = 16 * MT, LDF = W + 4;
-    __shared__ __align__(16) float sh[M * LDF];   // first-layer weights, BF16 operands, FP32 activations
+    constexpr int T = 4 * W, M = 16 * MT, LDF = W + 4;
+    __shared__ __align__(16) float sh[32 * LDF];   // first-layer weights, BF16 operands, FP32 activations
     __shared__ float xs[M][kMaxIn + 1];
     __shared__ float wo[2 * W + 2], dy[M][2], tw[M][3];
     __shared__ int64_t row[M];
@@ -655,7 +660,7 @@ k_train_rows(const TrainData d, const float* __restrict__ theta, const __bf16* _
         tw[tid][2] = d.w[j];
         if (i == 0) d.step[1] = d.step[0] + 1;
     }
-    const bool staged = W * din <= M * LDF;
+    const bool staged = W * din <= 32 * LDF;
     if (staged)
         for (int i = tid; i < W * din; i += T) sh[i] = theta[i];
     for (int i = tid; i < 2 * W + 2; i += T) wo[i] = out[i];
@@ -1021,10 +1026,14 @@ hipError_t gemm_weight_grad(const __bf16* dZbT, const __bf16* HT, int rows, int 
 hipError_t train_pass(const TrainBatch& b, int d_in, int W, int D, int rows, float inv_n, const float* mean, const float* stdv,
                       const TrainWork& wk, const TrainState& st, int update, hipStream_t s) {
     const TrainData d{b.X, b.T, b.w, b.src_rows, d_in, b.rng, mean, stdv, b.seed, st.step};
-    const dim3 grid(rows / 32), block(4 * W);
-#define ROWS_OF(WW, DD)                                                                                       \
-    case WW * 8 + DD:                                                                                         \
-        hipLaunchKernelGGL((k_train_rows<WW, DD>), grid, block, 0, s, d, st.theta, st.Wb, st.WbT, rows, inv_n, wk); \
+    const bool small = rows <= kTrainRows16 * 256 / W;
+    const dim3 grid(rows / (small ? 16 : 32)), block(4 * W);
+#define ROWS_OF(WW, DD)                                                                                                \
+    case WW * 8 + DD:                                                                                                  \
+        if (small) hipLaunchKernelGGL((k_train_rows<WW, DD, 1>), grid, block, 0, s, d, st.theta, st.Wb, st.WbT, rows,  \
+                                      inv_n, wk);                                                                      \
+        else hipLaunchKernelGGL((k_train_rows<WW, DD, 2>), grid, block, 0, s, d, st.theta, st.Wb, st.WbT, rows, inv_n, \
+                                wk);                                                                                   \
         break
     switch (W * 8 + D) {
         ROWS_OF(128, 2); ROWS_OF(128, 3); ROWS_OF(128, 4);

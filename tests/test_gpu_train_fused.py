@@ -52,6 +52,27 @@ def test_gradients(sur, d_in, width, depth, n):
     assert np.array_equal(net.grad(X, T, w)[1], g) and np.array_equal(net.params(), theta)
 
 
+# 16 rows per block up to 4096 rows (256 units) or 8192 (128 units), 32 beyond
+@pytest.mark.parametrize("d_in,width,depth,n", [(5, 256, 4, 4096), (5, 256, 3, 4097), (4, 128, 2, 8192), (5, 128, 3, 8200)])
+def test_gradients_of_large_batches(sur, d_in, width, depth, n):
+    print(f"case: train gradients d_in={d_in} width={width} depth={depth} rows={n}", flush=True)
+    rng = np.random.default_rng(n + width + depth)
+    theta = _theta(rng, d_in, width, depth)
+    net = sur.Network(d_in, width, depth, max_batch=8256, max_data=64, seed=3)
+    net.set_params(theta)
+    X, T, w = _problem(rng, n, d_in)
+    loss, g = net.grad(X, T, w)
+    lo, go = mlp.loss_and_grad(theta.astype(np.float64), *(a.astype(np.float64) for a in (X, T, w)), d_in, width, depth)
+    assert abs(loss - lo) <= 2e-2 * lo
+    p = 0
+    for o, i in mlp.layer_shapes(d_in, width, depth):
+        for size in (o * i, o):
+            a, b = g[p:p + size].astype(np.float64), go[p:p + size]
+            p += size
+            assert a @ b > 0.999 * np.linalg.norm(a) * np.linalg.norm(b)
+            assert np.linalg.norm(a - b) < 2e-2 * np.linalg.norm(b)
+
+
 @pytest.mark.parametrize("d_in,width,depth,n", [(5, 256, 4, 192), (4, 128, 2, 64), (5, 320, 2, 64)])
 def test_update_follows_adam(sur, d_in, width, depth, n):
     rng = np.random.default_rng(n)
