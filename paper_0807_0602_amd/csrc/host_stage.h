@@ -4,17 +4,21 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include <mutex>
+
 namespace scf {
 
 // One per context, allocated with it and freed with it.  A copy between the device and pageable
 // memory takes 24 us at 64 bytes and 43 at 64 KB; a kernel that writes here, the synchronisation that
 // is needed anyway and a host copy into the caller's array take 13 and 17.  Beyond about 1 MB the host
 // copy costs what it saves.  `p` is NULL where the memory was not to be had; transfers are then copies.
+// A call holds `mu` from its launch to the end of its host copy: threads may read from one context.
 constexpr size_t kStageBytes = (size_t)1 << 20;
 
 struct HostStage {
     char* p = nullptr;
     size_t bytes = 0;
+    std::mutex mu;
 
     HostStage() = default;
     HostStage(const HostStage&) = delete;

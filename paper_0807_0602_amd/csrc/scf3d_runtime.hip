@@ -191,6 +191,8 @@ int scf3_observe(scf3_ctx* c, scf3_obs* out) {
     if (!c || !out) return fail(SCF_EINVAL, "NULL argument");
     auto* parts = reinterpret_cast<scf3::Part3*>(c->ws + c->lay.parts);
     const bool staged = c->stage.holds(sizeof(scf3::Obs3));
+    std::unique_lock<std::mutex> hold(c->stage.mu, std::defer_lock);
+    if (staged) hold.lock();
     auto* obs = reinterpret_cast<scf3::Obs3*>(staged ? c->stage.p : c->ws + c->lay.obs);
     HIP_TRY3(scf3::launch_observe(c->chan, c->d_chan(), c->base(), c->cur, parts, obs, c->stream));
     scf3::Obs3 r;
@@ -215,6 +217,8 @@ int scf3_get_density(scf3_ctx* c, double* nA, double* nB) {
     const scf3::Chan3& h = c->chan;
     const size_t cells = (size_t)h.nx * h.ny * h.nz;
     const bool staged = c->stage.holds(2 * sizeof(double) * cells);
+    std::unique_lock<std::mutex> hold(c->stage.mu, std::defer_lock);
+    if (staged) hold.lock();
     double* f = staged ? reinterpret_cast<double*>(c->stage.p)
                        : reinterpret_cast<double*>(c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane);
     HIP_TRY3(scf3::launch_density_out(h, c->base(), f, c->stream));

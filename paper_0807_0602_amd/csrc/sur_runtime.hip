@@ -485,6 +485,8 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
             // copies, 32064 rows: 86 for 118)
             const size_t xb = 4 * (size_t)m * din, yb = 8 * (size_t)m;
             const bool sy = s->host.holds(yb + m), sx = s->host.holds(al(xb) + yb + m);
+            std::unique_lock<std::mutex> hold(s->host.mu, std::defer_lock);
+            if (sy) hold.lock();
             char* at = s->ws + s->p.Z;
             float* Xd = reinterpret_cast<float*>(sx ? s->host.p : at);
             float* Yd = reinterpret_cast<float*>(sy ? s->host.p + (sx ? al(xb) : 0) : at + al(xb));

@@ -135,3 +135,29 @@ def test_predictions_around_the_staged_sizes(scf, rows):
         assert np.array_equal(y, Y[r:r + 1000]) and np.array_equal(i, inside[r:r + 1000])
     assert np.array_equal(inside.astype(bool), (np.abs(X) <= 1.0).all(1))
     net.close()
+
+
+def test_threads_read_one_batch(scf):
+    """Four threads read channels and records of one batch; each gets what one thread gets."""
+    import threading
+    print("case: read-outs from four threads", flush=True)
+    cases = [inputs.Case(inputs.Geometry(90 + 30 * k, 20 + k, 20, 60), inputs.Params(gw=(-0.2, 0.2)), seed=k, liquid_x1=30)
+             for k in range(4)]
+    b = scf.Batch(cases, sample_every=10, max_samples=8)
+    b.step(40)
+    want = [b.density(c) for c in range(4)]
+    recs = repr(b.observe())
+    wrong = []
+
+    def read(c):
+        for _ in range(50):
+            got = b.density(c)
+            if not all(np.array_equal(x, y) for x, y in zip(got, want[c])) or repr(b.observe()) != recs:
+                wrong.append(c)
+
+    threads = [threading.Thread(target=read, args=(c,)) for c in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
