@@ -319,14 +319,15 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
  * allocation.  X (n*d_in floats), Y (n*2 floats) and in_hull (optional, n bytes: 1 where every
  * input lies inside the training hull, all 0 before any data or norm was set) are DEVICE
  * pointers owned by the caller.  The same kernels as scf_sur_predict give the same Y bit for bit.
- * Widths up to 256 run as one launch and keep their activations on chip; wider ones keep them in a
- * library-owned device array of 20 MiB per GPU (held until the process ends) instead of the
- * workspace.  At every width one call takes at most the rows whose
+ * Y and in_hull may lie over X, not over each other.  Widths up to 256 run as one launch and keep their
+ * activations on chip, unless an output lies over X; those calls, and wider networks, run a launch per
+ * layer and keep them in a library-owned device array of 20 MiB per GPU (held until the process ends)
+ * instead of the workspace.  At every width one call takes at most the rows whose
  * rows_pad * (4 d_in + 16 width) bytes fit that array (rows_pad = n rounded up to 64, plus
  * alignment), so at width 256 and 5 inputs up to 5056 rows per call; larger n returns SCF_EINVAL
  * and nothing is enqueued.  Asynchronous on the network's stream; no allocation, copy to or from
  * the host, or synchronisation.  The array keeps the last call's contents; every call writes the
- * parts it reads.  Calls of networks wider than 256 that overlap on one GPU race on the array.
+ * parts it reads.  Calls that use the array race on it when they overlap on one GPU.
  * Errors: SCF_EINVAL (NULL, n < 0, n too large), SCF_EDEVICE (launch failure, or no array address
  * on the device current at scf_sur_create). */
 int scf_sur_predict_noalloc(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in_hull);

@@ -82,6 +82,7 @@ hipError_t hull(const float* X, int d_in, int rows, const float* lo, const float
 hipError_t normalise(const float* X, int64_t n, int d_in, int rows, const float* mean, const float* stdv,
                      float* Xn, hipStream_t s);
 hipError_t fill_u8(uint8_t* p, int64_t n, uint8_t v, hipStream_t s);
+hipError_t copy_u8(uint8_t* to, const uint8_t* from, int64_t n, hipStream_t s);
 hipError_t init_params(float* theta, int64_t off, int n_out, int n_in, uint64_t seed, hipStream_t s);
 
 }  // namespace sur

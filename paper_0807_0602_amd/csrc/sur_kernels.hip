@@ -404,6 +404,12 @@ __global__ void __launch_bounds__(kThreads) k_fill_u8(uint8_t* __restrict__ p, i
     if (i < n) p[i] = v;
 }
 
+__global__ void __launch_bounds__(kThreads)
+k_copy_u8(uint8_t* __restrict__ to, const uint8_t* __restrict__ from, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i < n) to[i] = from[i];
+}
+
 // Inputs inside the axis-aligned box of the stored training inputs.
 __global__ void __launch_bounds__(kThreads)
 k_hull(const float* __restrict__ X, int d_in, int rows, const float* __restrict__ lo,
@@ -1169,6 +1175,11 @@ hipError_t normalise(const float* X, int64_t n, int d_in, int rows, const float*
 
 hipError_t fill_u8(uint8_t* p, int64_t n, uint8_t v, hipStream_t s) {
     hipLaunchKernelGGL(k_fill_u8, grid1(n), dim3(kThreads), 0, s, p, n, v);
+    return hipGetLastError();
+}
+
+hipError_t copy_u8(uint8_t* to, const uint8_t* from, int64_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_copy_u8, grid1(n), dim3(kThreads), 0, s, to, from, n);
     return hipGetLastError();
 }
 

@@ -544,7 +544,7 @@ int scf_sur_predict_noalloc(scf_sur* s, const float* X, int64_t n, float* Y, uin
                                          std::to_string(kNoAllocScratchBytes) + " (split the rows over calls)");
     if (!s->scratch_dev) return set_error(SCF_EDEVICE, "no scratch on this device: " + s->scratch_err);
     // one launch reads and writes block by block, so outputs that lie over the inputs take the
-    // layer kernels, which read every input first
+    // layer kernels, which have read every input before the first output is written
     auto apart = [&](const void* q, size_t bytes) {
         const uintptr_t a = reinterpret_cast<uintptr_t>(X), c = reinterpret_cast<uintptr_t>(q);
         return !q || a + 4 * (size_t)n * din <= c || c + bytes <= a;
@@ -578,15 +578,16 @@ int scf_sur_predict_noalloc(scf_sur* s, const float* X, int64_t n, float* Y, uin
     for (int l = 1; l < D; ++l)
         SUR_TRY(scf::sur::gemm_forward(H[(l - 1) & 1], s->Wb(l), s->b(l), (int)rows, Wd, Z[l & 1], H[l & 1],
                                        HT[l & 1], st));
+    // the hull flags before Y is written, which may lie over X; flags that do so themselves wait in the
+    // last layer's activations, which nothing reads any more, until every row has been tested
+    uint8_t* flags = apart(in_hull, (size_t)n) ? in_hull : reinterpret_cast<uint8_t*>(H[(D - 1) & 1]);
+    if (in_hull && s->have_stats)
+        SUR_TRY(scf::sur::hull(X, din, (int)n, s->at<float>(s->p.lo), s->at<float>(s->p.hi), flags, st));
     // output rows m < n straight into the caller's Y (inference: no targets)
     SUR_TRY(scf::sur::output_layer(Z[(D - 1) & 1], Wd, (int)n, s->W(D), s->b(D), nullptr, nullptr, 1.0f, Y,
                                    nullptr, nullptr, nullptr, nullptr, nullptr, st));
-    if (in_hull) {
-        if (s->have_stats)
-            SUR_TRY(scf::sur::hull(X, din, (int)n, s->at<float>(s->p.lo), s->at<float>(s->p.hi), in_hull, st));
-        else
-            SUR_TRY(scf::sur::fill_u8(in_hull, n, 0, st));
-    }
+    if (in_hull && !s->have_stats) SUR_TRY(scf::sur::fill_u8(in_hull, n, 0, st));
+    else if (flags != in_hull) SUR_TRY(scf::sur::copy_u8(in_hull, flags, n, st));
     return SCF_OK;
 }
 
