@@ -23,7 +23,8 @@
  *  - Field arrays are row-major (ny rows of nx values, x fastest), FP64 on the host.  The
  *    device state is FP32.
  *  - Threading: one context per stream; distinct contexts are independent.  Calls on one
- *    context must not overlap.
+ *    context must not overlap, except that several threads may read from it at once: *_observe,
+ *    *_get_density, *_get_populations and scf_sur_predict take their turns.
  */
 #ifndef SCF_H
 #define SCF_H

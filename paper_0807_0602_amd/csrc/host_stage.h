@@ -12,7 +12,9 @@ namespace scf {
 // memory takes 24 us at 64 bytes and 43 at 64 KB; a kernel that writes here, the synchronisation that
 // is needed anyway and a host copy into the caller's array take 13 and 17.  Beyond about 1 MB the host
 // copy costs what it saves.  `p` is NULL where the memory was not to be had; transfers are then copies.
-// A call holds `mu` from its launch to the end of its host copy: threads may read from one context.
+// Threads may read from one context: a read-out holds `mu` from its launch to the end of its host copy,
+// whether it goes through this memory or through the idle population buffer or activations, which other
+// read-outs use too.
 constexpr size_t kStageBytes = (size_t)1 << 20;
 
 struct HostStage {

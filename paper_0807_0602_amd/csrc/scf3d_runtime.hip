@@ -187,12 +187,10 @@ int scf3_get_schedule(const scf3_ctx* c, int32_t* fused, int32_t* cy) {
     return SCF_OK;
 }
 
-int scf3_observe(scf3_ctx* c, scf3_obs* out) {
-    if (!c || !out) return fail(SCF_EINVAL, "NULL argument");
+// The caller holds stage.mu.
+static int observe_held(scf3_ctx* c, scf3_obs* out) {
     auto* parts = reinterpret_cast<scf3::Part3*>(c->ws + c->lay.parts);
     const bool staged = c->stage.holds(sizeof(scf3::Obs3));
-    std::unique_lock<std::mutex> hold(c->stage.mu, std::defer_lock);
-    if (staged) hold.lock();
     auto* obs = reinterpret_cast<scf3::Obs3*>(staged ? c->stage.p : c->ws + c->lay.obs);
     HIP_TRY3(scf3::launch_observe(c->chan, c->d_chan(), c->base(), c->cur, parts, obs, c->stream));
     scf3::Obs3 r;
@@ -207,18 +205,23 @@ int scf3_observe(scf3_ctx* c, scf3_obs* out) {
     return SCF_OK;
 }
 
+int scf3_observe(scf3_ctx* c, scf3_obs* out) {
+    if (!c || !out) return fail(SCF_EINVAL, "NULL argument");
+    const std::lock_guard<std::mutex> hold(c->stage.mu);
+    return observe_held(c, out);
+}
+
 int scf3_get_density(scf3_ctx* c, double* nA, double* nB) {
     if (!c || !nA || !nB) return fail(SCF_EINVAL, "NULL argument");
+    const std::lock_guard<std::mutex> hold(c->stage.mu);
     scf3_obs o;
-    int rc = scf3_observe(c, &o);   // also refreshes the density field
+    int rc = observe_held(c, &o);   // also refreshes the density field
     if (rc && rc != SCF_EUNSTABLE) return rc;
     // converted and compacted on the device: a small field straight into page-locked memory, others into
     // the idle population buffer (the next step overwrites it) and copied from there
     const scf3::Chan3& h = c->chan;
     const size_t cells = (size_t)h.nx * h.ny * h.nz;
     const bool staged = c->stage.holds(2 * sizeof(double) * cells);
-    std::unique_lock<std::mutex> hold(c->stage.mu, std::defer_lock);
-    if (staged) hold.lock();
     double* f = staged ? reinterpret_cast<double*>(c->stage.p)
                        : reinterpret_cast<double*>(c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane);
     HIP_TRY3(scf3::launch_density_out(h, c->base(), f, c->stream));
@@ -237,6 +240,7 @@ int scf3_get_density(scf3_ctx* c, double* nA, double* nB) {
 int scf3_get_populations(scf3_ctx* c, double* f) {
     if (!c || !f) return fail(SCF_EINVAL, "NULL argument");
     const scf3::Chan3& h = c->chan;
+    const std::lock_guard<std::mutex> hold(c->stage.mu);
     HIP_TRY3(scf3::launch_pull_out(h, c->d_chan(), c->base(), c->cur, c->stream));
     std::vector<float> buf((size_t)38 * h.plane);
     HIP_TRY3(hipMemcpyAsync(buf.data(), c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane,

@@ -976,8 +976,7 @@ struct Engine {
         if (c < 0 || c >= nchan || !nA || !nB) return fail(SCF_EINVAL, "bad channel or NULL output");
         const size_t cells = (size_t)geom[c].nx * geom[c].ny;
         const bool staged = stage.holds(2 * sizeof(double) * cells);
-        std::unique_lock<std::mutex> hold(stage.mu, std::defer_lock);
-        if (staged) hold.lock();
+        const std::lock_guard<std::mutex> hold(stage.mu);
         double* out = reinterpret_cast<double*>(
             staged ? stage.p : ws + lay.chan_off[c] + sizeof(float) * (size_t)(cur ^ 1) * 18 * chans[c].plane);
         HIP_TRY(scf::launch_density_out(d_chans(), c, geom[c].ny, base(), cur, out, stream));
@@ -1040,16 +1039,12 @@ int scf_observe(scf_ctx* ctx, scf_obs* out) {
     Engine& e = ctx->e;
     static_assert(sizeof(scf::ObsRec) == sizeof(scf_obs), "record layout");
     const bool staged = e.stage.holds(sizeof(scf::ObsRec) * e.nchan);
-    std::unique_lock<std::mutex> hold(e.stage.mu, std::defer_lock);
-    if (staged) hold.lock();
+    const std::lock_guard<std::mutex> hold(e.stage.mu);
     HIP_TRY(e.launch_obs(staged ? reinterpret_cast<scf::ObsRec*>(e.stage.p) : e.d_now()));
     scf::ObsRec r;
     if (!staged) HIP_TRY(hipMemcpyAsync(&r, e.d_now(), sizeof r, hipMemcpyDeviceToHost, e.stream));
     HIP_TRY(hipStreamSynchronize(e.stream));
-    if (staged) {
-        std::memcpy(&r, e.stage.p, sizeof r);
-        hold.unlock();
-    }
+    if (staged) std::memcpy(&r, e.stage.p, sizeof r);
     std::memcpy(out, &r, sizeof r);
     out->t = e.t;
     e.seen_flags = out->flags;
@@ -1065,6 +1060,7 @@ int scf_get_density(scf_ctx* ctx, double* nA, double* nB) {
 int scf_get_populations(scf_ctx* ctx, double* f) {
     if (!ctx || !f) return fail(SCF_EINVAL, "NULL argument");
     Engine& e = ctx->e;
+    const std::lock_guard<std::mutex> hold(e.stage.mu);
     HIP_TRY(scf::launch_pull_out(e.d_chans(), e.d_rows(), e.lay.nrows, e.base(), e.cur, e.stream));
     const scf_geometry& g = e.geom[0];
     const int pitch = e.chans[0].pitch;
@@ -1227,9 +1223,8 @@ int scf_batch_observe(scf_batch* b, scf_obs* out, int64_t* nsamples) {
     const size_t n = (size_t)e.nchan * have;
     std::vector<scf::ObsRec> h;
     const scf::ObsRec* rec = nullptr;
-    std::unique_lock<std::mutex> hold(e.stage.mu, std::defer_lock);
+    const std::lock_guard<std::mutex> hold(e.stage.mu);
     if (n > 0 && e.stage.holds(sizeof(scf::ObsRec) * n)) {
-        hold.lock();
         auto* to = reinterpret_cast<scf::ObsRec*>(e.stage.p);
         HIP_TRY(scf::launch_pack_ring(e.d_ring(), e.nchan, e.max_samples, (int)have, to, e.stream));
         rec = to;

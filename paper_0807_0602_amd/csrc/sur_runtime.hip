@@ -475,6 +475,7 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
     if (!s || !X || !Y) return set_error(SCF_EINVAL, "NULL argument");
     if (n < 0) return set_error(SCF_EINVAL, "negative row count");
     const int din = s->cfg.d_in;
+    const std::lock_guard<std::mutex> hold(s->host.mu);
     if (scf::sur::predict_fits(s->cfg.width)) {
         // rows per launch: inputs, outputs and hull flags take the place of the activations
         const size_t room = 4 * (size_t)s->cfg.max_batch * s->cfg.width * s->cfg.depth - 512;
@@ -485,8 +486,6 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
             // copies, 32064 rows: 86 for 118)
             const size_t xb = 4 * (size_t)m * din, yb = 8 * (size_t)m;
             const bool sy = s->host.holds(yb + m), sx = s->host.holds(al(xb) + yb + m);
-            std::unique_lock<std::mutex> hold(s->host.mu, std::defer_lock);
-            if (sy) hold.lock();
             char* at = s->ws + s->p.Z;
             float* Xd = reinterpret_cast<float*>(sx ? s->host.p : at);
             float* Yd = reinterpret_cast<float*>(sy ? s->host.p + (sx ? al(xb) : 0) : at + al(xb));
