@@ -15,6 +15,9 @@
  *    (dev_ws, at least scf_*workspace_bytes() bytes, 256-byte aligned) that must stay alive and
  *    untouched until the matching *_destroy.  The caller also passes the HIP stream (a
  *    hipStream_t cast to void*, NULL = the default stream); all device work is enqueued on it.
+ *    Small read-outs go through page-locked host memory that the contexts of a process share: 1 MiB
+ *    for each such call at a time, at most 8, allocated when first needed; the last context gives
+ *    back all but 1 MiB.
  *  - Geometry: a box nx x ny, periodic in x and y.  Rows y = 0 and y = ny-1 are solid for
  *    x in [x0, x1) (the coated capillary, bounce-back walls); elsewhere those rows are fluid
  *    (the reservoir).  Channel height H = ny - 2.  Liquid (component A) is expected to start

@@ -74,7 +74,7 @@ struct scf3_ctx {
     int rows = 0;             // rows per tile that steps run with, 0: two kernels
     int cus = 0;
     int32_t seen_flags = 0;   // flags of the last scf3_observe (see scf3_step)
-    scf::HostStage stage;     // the record and a small density field on their way to the caller
+    scf::HostStage stage;     // the record and the density field on their way to the caller
     float* base() const { return reinterpret_cast<float*>(ws); }
     scf3::Chan3* d_chan() const { return reinterpret_cast<scf3::Chan3*>(ws + lay.chan); }
 };
@@ -126,10 +126,6 @@ int scf3_init(scf3_ctx** out, const scf3_geometry* geom, const scf_params* p, co
         hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         c->cus = 256;
     c->rows = scf3::best_schedule(h, c->cus);   // until a schedule is set
-    {
-        const size_t f = 2 * sizeof(double) * (size_t)geom->nx * geom->ny * geom->nz;
-        c->stage.reserve(f <= scf::kStageBytes ? std::max(f, sizeof(scf3::Obs3)) : sizeof(scf3::Obs3));
-    }
     h.G = (float)p->G;
     for (int k = 0; k < 2; ++k) {
         h.gw[k] = (float)p->gw[k];
@@ -190,13 +186,14 @@ int scf3_get_schedule(const scf3_ctx* c, int32_t* fused, int32_t* cy) {
 // The caller holds stage.mu.
 static int observe_held(scf3_ctx* c, scf3_obs* out) {
     auto* parts = reinterpret_cast<scf3::Part3*>(c->ws + c->lay.parts);
-    const bool staged = c->stage.holds(sizeof(scf3::Obs3));
-    auto* obs = reinterpret_cast<scf3::Obs3*>(staged ? c->stage.p : c->ws + c->lay.obs);
+    scf::StageLease buf(sizeof(scf3::Obs3), c->stream);
+    auto* obs = reinterpret_cast<scf3::Obs3*>(buf.p ? buf.p : c->ws + c->lay.obs);
     HIP_TRY3(scf3::launch_observe(c->chan, c->d_chan(), c->base(), c->cur, parts, obs, c->stream));
     scf3::Obs3 r;
-    if (!staged) HIP_TRY3(hipMemcpyAsync(&r, obs, sizeof r, hipMemcpyDeviceToHost, c->stream));
+    if (!buf.p) HIP_TRY3(hipMemcpyAsync(&r, obs, sizeof r, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY3(hipStreamSynchronize(c->stream));
-    if (staged) std::memcpy(&r, obs, sizeof r);
+    buf.done();
+    if (buf.p) std::memcpy(&r, obs, sizeof r);
     static_assert(sizeof(scf3::Obs3) == sizeof(scf3_obs), "record layout");
     std::memcpy(out, &r, sizeof r);
     out->t = c->t;
@@ -221,8 +218,9 @@ int scf3_get_density(scf3_ctx* c, double* nA, double* nB) {
     // the idle population buffer (the next step overwrites it) and copied from there
     const scf3::Chan3& h = c->chan;
     const size_t cells = (size_t)h.nx * h.ny * h.nz;
-    const bool staged = c->stage.holds(2 * sizeof(double) * cells);
-    double* f = staged ? reinterpret_cast<double*>(c->stage.p)
+    scf::StageLease buf(2 * sizeof(double) * cells, c->stream);
+    const bool staged = buf.p != nullptr;
+    double* f = staged ? reinterpret_cast<double*>(buf.p)
                        : reinterpret_cast<double*>(c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane);
     HIP_TRY3(scf3::launch_density_out(h, c->base(), f, c->stream));
     if (!staged) {
@@ -230,6 +228,7 @@ int scf3_get_density(scf3_ctx* c, double* nA, double* nB) {
         HIP_TRY3(hipMemcpyAsync(nB, f + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
     }
     HIP_TRY3(hipStreamSynchronize(c->stream));
+    buf.done();
     if (staged) {
         std::memcpy(nA, f, sizeof(double) * cells);
         std::memcpy(nB, f + cells, sizeof(double) * cells);

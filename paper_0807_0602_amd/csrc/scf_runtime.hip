@@ -198,7 +198,7 @@ struct Engine {
     int sample_every = 0, max_samples = 1;
     int64_t recorded = 0;
     bool batch = false;
-    scf::HostStage stage;   // records and small density fields on their way to the caller
+    scf::HostStage stage;   // records and density fields on their way to the caller
     // flags of the last observation copied to the host (scf_observe, scf_batch_observe); a
     // later step reports bit 1 as SCF_EUNSTABLE without synchronising
     int32_t seen_flags = 0;
@@ -736,16 +736,6 @@ struct Engine {
             HIP_TRY(hipGetDevice(&dev));
             HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
         }
-        {
-            // room for every channel's record, and for the fields and rings that are small enough
-            size_t want = sizeof(scf::ObsRec) * nch;
-            for (int c = 0; c < nch; ++c) {
-                const size_t f = 2 * sizeof(double) * (size_t)g[c].nx * g[c].ny;
-                if (f <= scf::kStageBytes) want = std::max(want, f);
-            }
-            if (samp_every > 0) want = std::max(want, std::min(scf::kStageBytes, sizeof(scf::ObsRec) * nch * (size_t)max_samp));
-            stage.reserve(want);
-        }
         nchan = nch;
         geom.assign(g, g + nch);
         mhash.clear();
@@ -975,16 +965,18 @@ struct Engine {
     int get_density(int c, double* nA, double* nB) {
         if (c < 0 || c >= nchan || !nA || !nB) return fail(SCF_EINVAL, "bad channel or NULL output");
         const size_t cells = (size_t)geom[c].nx * geom[c].ny;
-        const bool staged = stage.holds(2 * sizeof(double) * cells);
         const std::lock_guard<std::mutex> hold(stage.mu);
+        scf::StageLease buf(2 * sizeof(double) * cells, stream);
+        const bool staged = buf.p != nullptr;
         double* out = reinterpret_cast<double*>(
-            staged ? stage.p : ws + lay.chan_off[c] + sizeof(float) * (size_t)(cur ^ 1) * 18 * chans[c].plane);
+            staged ? buf.p : ws + lay.chan_off[c] + sizeof(float) * (size_t)(cur ^ 1) * 18 * chans[c].plane);
         HIP_TRY(scf::launch_density_out(d_chans(), c, geom[c].ny, base(), cur, out, stream));
         if (!staged) {
             HIP_TRY(hipMemcpyAsync(nA, out, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
             HIP_TRY(hipMemcpyAsync(nB, out + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
         }
         HIP_TRY(hipStreamSynchronize(stream));
+        buf.done();
         if (staged) {
             std::memcpy(nA, out, sizeof(double) * cells);
             std::memcpy(nB, out + cells, sizeof(double) * cells);
@@ -1038,13 +1030,14 @@ int scf_observe(scf_ctx* ctx, scf_obs* out) {
     if (!ctx || !out) return fail(SCF_EINVAL, "NULL argument");
     Engine& e = ctx->e;
     static_assert(sizeof(scf::ObsRec) == sizeof(scf_obs), "record layout");
-    const bool staged = e.stage.holds(sizeof(scf::ObsRec) * e.nchan);
     const std::lock_guard<std::mutex> hold(e.stage.mu);
-    HIP_TRY(e.launch_obs(staged ? reinterpret_cast<scf::ObsRec*>(e.stage.p) : e.d_now()));
+    scf::StageLease buf(sizeof(scf::ObsRec), e.stream);
+    HIP_TRY(e.launch_obs(buf.p ? reinterpret_cast<scf::ObsRec*>(buf.p) : e.d_now()));
     scf::ObsRec r;
-    if (!staged) HIP_TRY(hipMemcpyAsync(&r, e.d_now(), sizeof r, hipMemcpyDeviceToHost, e.stream));
+    if (!buf.p) HIP_TRY(hipMemcpyAsync(&r, e.d_now(), sizeof r, hipMemcpyDeviceToHost, e.stream));
     HIP_TRY(hipStreamSynchronize(e.stream));
-    if (staged) std::memcpy(&r, e.stage.p, sizeof r);
+    buf.done();
+    if (buf.p) std::memcpy(&r, buf.p, sizeof r);
     std::memcpy(out, &r, sizeof r);
     out->t = e.t;
     e.seen_flags = out->flags;
@@ -1224,8 +1217,9 @@ int scf_batch_observe(scf_batch* b, scf_obs* out, int64_t* nsamples) {
     std::vector<scf::ObsRec> h;
     const scf::ObsRec* rec = nullptr;
     const std::lock_guard<std::mutex> hold(e.stage.mu);
-    if (n > 0 && e.stage.holds(sizeof(scf::ObsRec) * n)) {
-        auto* to = reinterpret_cast<scf::ObsRec*>(e.stage.p);
+    scf::StageLease buf(sizeof(scf::ObsRec) * n, e.stream);
+    if (buf.p) {
+        auto* to = reinterpret_cast<scf::ObsRec*>(buf.p);
         HIP_TRY(scf::launch_pack_ring(e.d_ring(), e.nchan, e.max_samples, (int)have, to, e.stream));
         rec = to;
     } else if (n > 0) {
@@ -1235,6 +1229,7 @@ int scf_batch_observe(scf_batch* b, scf_obs* out, int64_t* nsamples) {
         rec = h.data();
     }
     HIP_TRY(hipStreamSynchronize(e.stream));
+    buf.done();
     bool unstable = false;
     for (int c = 0; c < e.nchan; ++c)
         for (int64_t s = 0; s < e.max_samples; ++s) {

@@ -313,7 +313,6 @@ int scf_sur_create(scf_sur** out, const scf_sur_cfg* cfg, void* dev_ws, size_t w
     if (e == hipSuccess) e = s->shadows(st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail("surrogate initialisation", e);
-    if (scf::sur::predict_fits(cfg->width)) s->host.reserve(scf::kStageBytes);
     // address of the allocation-free prediction's scratch on the current device (the one that
     // holds the workspace); a failure only disables scf_sur_predict_noalloc
     int dev = -1;
@@ -485,10 +484,11 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
             // results and, where both fit, rows go through page-locked memory (501 rows: 27 us for 50 with
             // copies, 32064 rows: 86 for 118)
             const size_t xb = 4 * (size_t)m * din, yb = 8 * (size_t)m;
-            const bool sy = s->host.holds(yb + m), sx = s->host.holds(al(xb) + yb + m);
+            scf::StageLease buf(yb + m, s->stream);
+            const bool sy = buf.p != nullptr, sx = sy && al(xb) + yb + m <= scf::kStageBytes;
             char* at = s->ws + s->p.Z;
-            float* Xd = reinterpret_cast<float*>(sx ? s->host.p : at);
-            float* Yd = reinterpret_cast<float*>(sy ? s->host.p + (sx ? al(xb) : 0) : at + al(xb));
+            float* Xd = reinterpret_cast<float*>(sx ? buf.p : at);
+            float* Yd = reinterpret_cast<float*>(sy ? buf.p + (sx ? al(xb) : 0) : at + al(xb));
             uint8_t* in = reinterpret_cast<uint8_t*>(Yd + 2 * m);
             if (sx) std::memcpy(Xd, X + r0 * din, xb);
             else SUR_TRY(hipMemcpyAsync(Xd, X + r0 * din, xb, hipMemcpyHostToDevice, s->stream));
@@ -501,6 +501,7 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
                 if (in_hull) SUR_TRY(hipMemcpyAsync(in_hull + r0, in, (size_t)m, hipMemcpyDeviceToHost, s->stream));
             }
             SUR_TRY(hipStreamSynchronize(s->stream));
+            buf.done();
             if (sy) {
                 std::memcpy(Y + 2 * r0, Yd, yb);
                 if (in_hull) std::memcpy(in_hull + r0, in, (size_t)m);
