@@ -390,9 +390,10 @@ int scf3_init(scf3_ctx** out, const scf3_geometry* geom, const scf_params* param
 int scf3_step(scf3_ctx* ctx, int64_t nsteps);
 
 /* Step schedule: fused = 1 (one kernel, cy >= 1 rows of y per tile) or fused = 0 (two kernels, cy
- * ignored).  The state is unchanged; results do not depend on the schedule.  *_get_* writes the
- * current one; before any *_set_* it reports fused = 1 and cy = 16 (fused = 0 where the fused form
- * does not fit) while the steps run with the form chosen for the box's size.
+ * ignored).  The state is unchanged; results do not depend on the schedule.  fused = 1 with cy = 16 is
+ * the default schedule, which runs the form chosen for the box's size; other values run as given.
+ * *_get_* writes the current schedule: the default one (fused = 0 where the fused form does not fit)
+ * before any *_set_*.
  * Errors: SCF_EINVAL (fused not 0/1, cy < 1, or fused = 1 where a component's 19 planes exceed
  * 4 GiB). */
 int scf3_set_schedule(scf3_ctx* ctx, int32_t fused, int32_t cy);
