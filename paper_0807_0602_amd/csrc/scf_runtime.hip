@@ -814,7 +814,7 @@ struct Engine {
         tl->graph_steps = graph_steps;
         tl->fuse = fuse;
         const int g = fuse == 2 ? grid2 : grid1;
-        tl->blocks_per_cu = (persistent() && cus > 0) ? g / cus : 0;
+        tl->blocks_per_cu = (persistent() && cus > 0) ? g / cus : bpc;
     }
 
     // Time each candidate by repeated steps that all read the resident buffer and write the
