@@ -120,7 +120,7 @@ typedef struct {
                              as the kernel's occupancy allows; scf_get_tile reports the number
                              the two-step (fuse = 2) or single-step list uses, and under other
                              orders the number as set.  With fuse = 2 and 0 (or, persistent, the
-                             full occupancy) boxes of up to about 0.7 M nodes
+                             occupancy of either kernel) boxes of up to about 0.7 M nodes
                              in all run a node-parallel kernel of up to four steps per launch in
                              place of the tiles above, and larger ones (higher than about 9 rows) a
                              pipelined one of four; any other number keeps the tiles as given. */

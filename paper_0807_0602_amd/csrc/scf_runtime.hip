@@ -423,12 +423,13 @@ struct Engine {
         deal_runs(t0, starts, nb, nblocks, SCF_ORDER_XCD, tl, first);
     }
 
-    // Schedules that ask for the row-walking kernels as they are: an explicit number of blocks per
-    // CU (below the kernel's occupancy, under a persistent order).
+    // Schedules that ask for the row-walking kernels as they are: an explicit number of blocks per CU.
+    // Under a persistent order it is not the occupancy, which get_tile reports for no number at all (of
+    // the single-step or of the two-step kernel, whichever runs).
     bool walk_forced(int bxv, int ord) const {
         if (bpc <= 0) return false;
         if (!(ord & SCF_ORDER_PERSIST)) return true;
-        return bpc < scf::resident_blocks_per_cu(bxv, any_masked, 2);
+        return bpc != scf::resident_blocks_per_cu(bxv, any_masked, 1) && bpc != scf::resident_blocks_per_cu(bxv, any_masked, 2);
     }
 
     // The pipelined step takes every box the node-parallel one leaves (us per step, against the

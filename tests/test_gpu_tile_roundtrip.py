@@ -1,5 +1,5 @@
 """Tiles kept as given by an explicit number of blocks per CU: what scf_get_tile reports, set back, runs
-the same step."""
+the same step, and a number above the occupancy counts as one."""
 import numpy as np
 import pytest
 
@@ -29,8 +29,10 @@ def _us(torch, ch, steps=96):
     return best * 1e3 / steps
 
 
-# 1000 x 1000: the pipelined step takes 17 us, a walk of 48 rows per tile 65
-@pytest.mark.parametrize("tile", [dict(bx=256, cy=48, order=3, fuse=2, blocks_per_cu=1)])
+# 1000 x 1000: the pipelined step takes 17 us; whole-width walks of 48 rows per tile, and persistent
+# ones of more blocks than fit, take longer
+@pytest.mark.parametrize("tile", [dict(bx=256, cy=48, order=3, fuse=2, blocks_per_cu=1),
+                                  dict(bx=256, cy=16, order=6, fuse=2, blocks_per_cu=32)])
 def test_explicit_blocks_per_cu(torch, tile):
     from paper_0807_0602_amd import scf
     print(f"case: {tile} read and set back", flush=True)
