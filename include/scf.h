@@ -122,8 +122,9 @@ typedef struct {
                              orders the number as set.  With fuse = 2 and 0 (or, persistent, the
                              occupancy of either kernel) boxes of up to about 0.7 M nodes
                              in all run a node-parallel kernel of up to four steps per launch in
-                             place of the tiles above, and larger ones (higher than about 9 rows) a
-                             pipelined one of four; any other number keeps the tiles as given. */
+                             place of the tiles above, and larger ones (higher than about 9 rows, and
+                             not of channels much narrower than 240 under a narrow bx) a pipelined
+                             one of four; any other number keeps the tiles as given. */
 } scf_tile;
 
 enum { SCF_ORDER_STRIPS = 0, SCF_ORDER_BANDS = 1, SCF_ORDER_XCD = 2, SCF_ORDER_PERSIST = 4 };

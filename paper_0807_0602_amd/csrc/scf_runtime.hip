@@ -436,15 +436,20 @@ struct Engine {
     // two-step walk: 4096 x 202 14.1 for 35.7, 8192 x 202 19.2 for 36.9, 4096 x 640 30 for 49, 16384 x
     // 1024 157 for 272) but those so low that the rows before and after a strip cost more than its four
     // steps per pass save: 1048000 x 20 278 for 411, x 14 219 for 288; from there a height of 9, 2.5
-    // rows gone through per row, is where the two would meet.
-    bool pipe_pays() const {
-        double rows = 0.0, strips = 0.0;
+    // rows gone through per row, is where the two would meet.  And a tile narrower than its 256 lanes
+    // stays where the walk goes through half as many lanes and rows or fewer, per lane the two being
+    // about as fast (tile of 64 columns, walk and pipelined: 16 x 60000 42 and 94, 64 x 20000 31 and 40,
+    // 1500 boxes of 48 x 48 89 and 147; past the line, 160 x 160 boxes 54 and 40, 130 x 10000 36 and 25).
+    bool pipe_pays(int bxv) const {
+        double rows = 0.0, strips = 0.0, walk = 0.0;
         for (const scf_geometry& g : geom) {
             const double n = (g.nx + kPipeWide - 1) / kPipeWide;
             rows += n * g.ny;
             strips += n;
+            walk += (double)((g.nx + strip2(bxv) - 1) / strip2(bxv)) * bxv * (g.ny + 6);
         }
-        return cus > 0 && cus <= kMaxPersistBlocks && rows + kPipeLead * strips <= 2.5 * rows;
+        return cus > 0 && cus <= kMaxPersistBlocks && rows + kPipeLead * strips <= 2.5 * rows &&
+               scf::kPipeCols * (rows + kPipeLead * strips) < 2.0 * walk;
     }
 
     // Strips of 240 columns, or of 224, whose edges fall on 128-byte lines.  A line that two strips
@@ -562,7 +567,7 @@ struct Engine {
         if (!walk_forced(bxv, ord)) {
             std::vector<scf::TileDesc> more;
             plan_regions(more, tl2);
-            if (!region_k && pipe_pays()) {
+            if (!region_k && pipe_pays(bxv)) {
                 std::vector<int32_t> f;
                 make_tiles_pipe(pipe_strip(), cus, more, f);
                 pipe = (int)more.size() <= lay.max_tiles;
@@ -846,7 +851,7 @@ struct Engine {
             for (int bxv : bxs)
                 for (int k = 1; k <= 2; ++k) cands.push_back({bxv, cy, ord, k, 0.0f});
         // where the node-parallel or the pipelined step runs, every two-step schedule is that kernel
-        if (region_count(scf::kRegionLarge, 2) <= region_max_tiles() || pipe_pays()) {
+        if (region_count(scf::kRegionLarge, 2) <= region_max_tiles() || pipe_pays(256)) {
             cands.erase(std::remove_if(cands.begin(), cands.end(), [](const Cand& c) { return c.fuse == 2; }), cands.end());
             cands.push_back({256, 16, SCF_ORDER_PERSIST | SCF_ORDER_XCD, 2, 0.0f});
         }
