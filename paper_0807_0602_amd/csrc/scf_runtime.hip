@@ -49,7 +49,7 @@ constexpr int kPipeWide = 240, kPipeAligned = 224;         // strip widths
 static_assert(kPipeWide <= scf::pipe_out_x(scf::kPipeSteps), "a strip and its halo fit the block");
 // Version of the schedule space and kernels in the autotuner cache key (a cached schedule from
 // another version is timed again).
-constexpr int kTuneVersion = 7;
+constexpr int kTuneVersion = 8;
 constexpr int kPlanesPerChannel = 38;   // 2 x 18 population planes + 2 density planes
 
 // Float planes of one channel: populations and densities, plus one for the uint16 codes of a
@@ -498,18 +498,28 @@ struct Engine {
     // large ones; 4096 x 22: 3.5 us with 187 regions of 3 steps, 5.8 with 456 of 4).  Beyond, two
     // steps per launch, up to four blocks per CU: at 2048 x 300 (3.7) 11.8 us against 12.7 for the
     // pipelined step, at 4096 x 202 (4.9) 14.4 against 14.1.
-    void plan_regions(std::vector<scf::TileDesc>& tl, std::vector<scf::TileDesc>& walk) {
-        region_k = 0;
+    bool region_pick(int* region_out, int* k_out) const {
         struct Pick { int region, k; int64_t most; };
         const Pick picks[] = {{scf::kRegionSmall, 4, cus}, {scf::kRegionLarge, 4, cus}, {scf::kRegionLarge, 3, cus},
                               {scf::kRegionLarge, 2, region_max_tiles()}};
         for (const Pick& p : picks)
             if (region_count(p.region, p.k) <= p.most) {
-                region = p.region;
-                region_k = p.k;
-                break;
+                *region_out = p.region;
+                *k_out = p.k;
+                return true;
             }
-        if (!region_k) return;
+        return false;
+    }
+
+    // Another step takes the place of two-step tiles bxv wide that are not kept as given.
+    bool tiles_replaced(int bxv) const {
+        int r, k;
+        return region_pick(&r, &k) || pipe_pays(bxv);
+    }
+
+    void plan_regions(std::vector<scf::TileDesc>& tl, std::vector<scf::TileDesc>& walk) {
+        region_k = 0;
+        if (!region_pick(&region, &region_k)) return;
         tl.clear();
         for (int k = 1; k <= region_k; ++k) {
             const int ox = scf::region_out_x(region, k), oy = scf::region_out_y(region, k);
@@ -835,29 +845,28 @@ struct Engine {
         hipEvent_t e0, e1;
         HIP_TRY(hipEventCreate(&e0));
         HIP_TRY(hipEventCreate(&e1));
-        const int saved_variant = variant, saved_fuse = fuse;
+        const int saved_variant = variant, saved_fuse = fuse, saved_bpc = bpc;
         variant = SCF_VARIANT_FUSED;
-        bpc = 0;   // persistent candidates fill the CUs to the kernel's occupancy
-        struct Cand { int bx, cy, ord, fuse; float ms; };   // ms per time step
+        struct Cand { int bx, cy, ord, fuse, bpc; float ms; };   // ms per time step
         std::vector<Cand> cands;
+        // two steps per launch: tiles as given (one block per CU asks for that; it does not limit these orders)
         for (int ord = 0; ord < 4; ++ord)
             for (int bxv : bxs)
                 for (int cyv : cys) {
                     if (cyv != (1 << 30) && cyv >= maxny) continue;
-                    for (int k = 1; k <= 2; ++k) cands.push_back({bxv, cyv, ord, k, 0.0f});
+                    for (int k = 1; k <= 2; ++k) cands.push_back({bxv, cyv, ord, k, k - 1, 0.0f});
                 }
-        // persistent schedules (range lengths follow from the occupancy, cy is not used)
+        // persistent schedules, which fill the CUs to the kernel's occupancy (range lengths follow from it, cy
+        // is not used); of those that the node-parallel or the pipelined step replaces, which are all alike, one
         for (int ord : {(int)SCF_ORDER_PERSIST, (int)(SCF_ORDER_PERSIST | SCF_ORDER_XCD)})
             for (int bxv : bxs)
-                for (int k = 1; k <= 2; ++k) cands.push_back({bxv, cy, ord, k, 0.0f});
-        // where the node-parallel or the pipelined step runs, every two-step schedule is that kernel
-        if (region_count(scf::kRegionLarge, 2) <= region_max_tiles() || pipe_pays(256)) {
-            cands.erase(std::remove_if(cands.begin(), cands.end(), [](const Cand& c) { return c.fuse == 2; }), cands.end());
-            cands.push_back({256, 16, SCF_ORDER_PERSIST | SCF_ORDER_XCD, 2, 0.0f});
-        }
+                for (int k = 1; k <= 2; ++k)
+                    if (k == 1 || !tiles_replaced(bxv)) cands.push_back({bxv, cy, ord, k, 0, 0.0f});
+        if (tiles_replaced(256)) cands.push_back({256, 16, SCF_ORDER_PERSIST | SCF_ORDER_XCD, 2, 0, 0.0f});
         // time every candidate with `trial` launches, then the best eight again with four
         // times as many, and keep the fastest of the second round
         auto time_cand = [&](Cand& cd, int launches) -> int {
+            bpc = cd.bpc;
             int rc = upload_tiles(cd.bx, cd.cy, cd.ord);
             if (rc) return rc;
             fuse = cd.fuse;
@@ -887,10 +896,12 @@ struct Engine {
         variant = saved_variant;
         if (rc) {
             fuse = saved_fuse;
+            bpc = saved_bpc;
             return rc;
         }
         drop_graphs();
         fuse = cands[0].fuse;
+        bpc = cands[0].bpc;
         tuned_ms = cands[0].ms;
         rc = upload_tiles(cands[0].bx, cands[0].cy, cands[0].ord);
         if (rc) return rc;
