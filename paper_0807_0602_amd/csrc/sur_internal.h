@@ -30,7 +30,7 @@ struct TrainState {
     float *theta, *grad, *m1, *m2;
     __bf16 *Wb, *WbT;
     float* loss;
-    int64_t* step;   // [0] steps done, [1] scratch
+    int64_t* step;   // [0] steps done, [1] the step in progress
     const float* lr;
     float b1, b2, eps;
 };

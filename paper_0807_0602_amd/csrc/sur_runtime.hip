@@ -133,7 +133,7 @@ Plan plan(const scf_sur_cfg& c) {
     p.dY = take(8 * (size_t)B);
     p.rowloss = take(4 * (size_t)B);
     p.loss = take(4);
-    p.step = take(8);
+    p.step = take(2 * sizeof(int64_t));   // steps done, the step in progress (see TrainState)
     p.inhull = take((size_t)B);
     p.lr = take(4);
     p.total = o;
