@@ -40,9 +40,9 @@ struct TrainState {
 // Others take the layer kernels.
 inline bool train_fits(int width, int depth) { return (width == 128 || width == 256) && depth >= 2 && depth <= 4; }
 // Forward, loss and backward over `rows` (a multiple of 64) rows, then one Adam update (update) or
-// the gradient into st.grad; the mean loss into st.loss.
+// the gradient into st.grad; the mean loss into st.loss.  `cus`: the device's compute units.
 hipError_t train_pass(const TrainBatch& b, int d_in, int width, int depth, int rows, float inv_n, const float* mean,
-                      const float* stdv, const TrainWork& wk, const TrainState& st, int update, hipStream_t s);
+                      const float* stdv, const TrainWork& wk, const TrainState& st, int update, int cus, hipStream_t s);
 
 // Launchers, asynchronous on stream s.  Matrices are row-major; "T" names a transposed copy.
 hipError_t gemm_forward(const __bf16* Hprev, const __bf16* Wb, const float* bias, int rows, int width,
@@ -66,7 +66,7 @@ inline bool predict_fits(int width) { return width <= 256; }
 // Rows of X (raw) to Y and, with `in`, the hull test (hull 0: all rows outside); one launch.
 hipError_t predict(const float* X, int64_t n, int d_in, int width, int depth, const float* mean, const float* stdv,
                    const float* lo, const float* hi, int hull, const float* theta, const __bf16* Wb, float* Y,
-                   uint8_t* in, hipStream_t s);
+                   uint8_t* in, int cus, hipStream_t s);
 hipError_t loss_sum(const float* rowloss, int rows, float inv_n, float* out, hipStream_t s);
 hipError_t adam(float* theta, const float* grad, float* m1, float* m2, int64_t n, int64_t* step,
                 const float* lr, float b1, float b2, float eps, hipStream_t s);

@@ -36,10 +36,9 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
 }
 
 constexpr int kThreads = 256;
-// Predictions of up to this many rows (16 per CU) take 16 rows per block.
-constexpr int64_t kPredictRows16 = 4096;
-// So do training batches of 256 units; of 128, whose blocks have half the threads, twice as many.
-constexpr int kTrainRows16 = 4096;
+// Predictions of up to this many rows per CU take 16 rows per block; so do training batches of 256 units,
+// and of 128, whose blocks have half the threads, of twice as many.
+constexpr int64_t kRows16 = 16;
 
 // Fixed-order block reduction (kThreads threads).
 template <typename T>
@@ -1030,9 +1029,9 @@ hipError_t gemm_weight_grad(const __bf16* dZbT, const __bf16* HT, int rows, int 
 }
 
 hipError_t train_pass(const TrainBatch& b, int d_in, int W, int D, int rows, float inv_n, const float* mean, const float* stdv,
-                      const TrainWork& wk, const TrainState& st, int update, hipStream_t s) {
+                      const TrainWork& wk, const TrainState& st, int update, int cus, hipStream_t s) {
     const TrainData d{b.X, b.T, b.w, b.src_rows, d_in, b.rng, mean, stdv, b.seed, st.step};
-    const bool small = rows <= kTrainRows16 * 256 / W;
+    const bool small = rows <= kRows16 * cus * 256 / W;
     const dim3 grid(rows / (small ? 16 : 32)), block(4 * W);
 #define ROWS_OF(WW, DD)                                                                                                \
     case WW * 8 + DD:                                                                                                  \
@@ -1072,24 +1071,24 @@ static hipError_t predict_of(const float* X, int64_t n, int d_in, int depth, con
 template <int W>
 static hipError_t predict_w(const float* X, int64_t n, int d_in, int depth, const float* mean, const float* stdv,
                             const float* lo, const float* hi, int hull, const float* theta, const __bf16* Wb, float* Y,
-                            uint8_t* in, hipStream_t s) {
+                            uint8_t* in, int cus, hipStream_t s) {
     // Few rows: the smallest tile, 16 rows, over as many CUs as there are, one unit tile per wave
     // (256 units: 16 waves).  More rows than 16 per CU: 32 rows per block of half the waves, two
     // blocks per CU, so that one's activations overlap the other's products (256 x 4, us per
     // launch: 5000 rows 16.1, against 25.7 with 64 rows per block; 32064 rows 53, against 59 with
     // 64 rows and 68 with 32 rows and all the waves).
-    if (n <= kPredictRows16) return predict_of<W, 1, 1>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
+    if (n <= kRows16 * cus) return predict_of<W, 1, 1>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
     return predict_of<W, 2, 2>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
 }
 
 hipError_t predict(const float* X, int64_t n, int d_in, int width, int depth, const float* mean, const float* stdv,
                    const float* lo, const float* hi, int hull, const float* theta, const __bf16* Wb, float* Y,
-                   uint8_t* in, hipStream_t s) {
+                   uint8_t* in, int cus, hipStream_t s) {
     switch (width) {
-        case 64: return predict_w<64>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
-        case 128: return predict_w<128>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
-        case 192: return predict_w<192>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
-        case 256: return predict_w<256>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, s);
+        case 64: return predict_w<64>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, cus, s);
+        case 128: return predict_w<128>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, cus, s);
+        case 192: return predict_w<192>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, cus, s);
+        case 256: return predict_w<256>(X, n, d_in, depth, mean, stdv, lo, hi, hull, theta, Wb, Y, in, cus, s);
         default: return hipErrorInvalidValue;
     }
 }

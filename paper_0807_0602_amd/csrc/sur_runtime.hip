@@ -150,6 +150,7 @@ struct scf_sur {
     hipStream_t cap = nullptr;
     int64_t n_data = 0;
     bool have_stats = false;
+    int cus = 256;                   // compute units of the device
     hipGraphExec_t train_graph = nullptr;
     int train_rows = 0;
     void* scratch_dev = nullptr;     // this device's address of `scratch` (NULL: see scratch_err)
@@ -239,7 +240,7 @@ struct scf_sur {
                                           at<__bf16>(p.wbt), at<float>(p.loss), step(), at<float>(p.lr), cfg.beta1,
                                           cfg.beta2, cfg.eps};
             return scf::sur::train_pass(b, cfg.d_in, cfg.width, cfg.depth, rows, inv_n, at<float>(p.mean),
-                                        at<float>(p.stdv), wk, st, update, s);
+                                        at<float>(p.stdv), wk, st, update, cus, s);
         }
         hipError_t e = scf::sur::gather(at<float>(stored ? p.Xd : p.Xs), at<float>(stored ? p.Td : p.Ts),
                                         at<float>(stored ? p.wd : p.wsb), stored ? n_data : rows, cfg.d_in, rows,
@@ -317,6 +318,7 @@ int scf_sur_create(scf_sur** out, const scf_sur_cfg* cfg, void* dev_ws, size_t w
     // holds the workspace); a failure only disables scf_sur_predict_noalloc
     int dev = -1;
     e = hipGetDevice(&dev);
+    if (e == hipSuccess && hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) s->cus = 256;
     if (e != hipSuccess) {
         s->scratch_err = std::string("hipGetDevice: ") + hipGetErrorString(e);
     } else if (dev < 0 || dev >= kMaxDevices) {
@@ -495,7 +497,7 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
             SUR_TRY(scf::sur::predict(Xd, m, din, s->cfg.width, s->cfg.depth, s->at<float>(s->p.mean),
                                       s->at<float>(s->p.stdv), s->at<float>(s->p.lo), s->at<float>(s->p.hi),
                                       s->have_stats, s->theta(), s->at<__bf16>(s->p.wb), Yd, in_hull ? in : nullptr,
-                                      s->stream));
+                                      s->cus, s->stream));
             if (!sy) {
                 SUR_TRY(hipMemcpyAsync(Y + 2 * r0, Yd, yb, hipMemcpyDeviceToHost, s->stream));
                 if (in_hull) SUR_TRY(hipMemcpyAsync(in_hull + r0, in, (size_t)m, hipMemcpyDeviceToHost, s->stream));
@@ -552,7 +554,7 @@ int scf_sur_predict_noalloc(scf_sur* s, const float* X, int64_t n, float* Y, uin
     if (scf::sur::predict_fits(Wd) && apart(Y, 8 * (size_t)n) && apart(in_hull, (size_t)n)) {
         SUR_TRY(scf::sur::predict(X, n, din, Wd, D, s->at<float>(s->p.mean), s->at<float>(s->p.stdv),
                                   s->at<float>(s->p.lo), s->at<float>(s->p.hi), s->have_stats, s->theta(),
-                                  s->at<__bf16>(s->p.wb), Y, in_hull, s->stream));
+                                  s->at<__bf16>(s->p.wb), Y, in_hull, s->cus, s->stream));
         return SCF_OK;
     }
     char* base = static_cast<char*>(s->scratch_dev);
