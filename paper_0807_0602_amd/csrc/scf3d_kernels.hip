@@ -168,19 +168,20 @@ __device__ __forceinline__ float sum19(const float* f) {
 
 // The two-kernel step works on rows: a wave's 64 nodes lie on one row (y, z), so row addresses,
 // periodic wraps in y and z and the rows' wall tests are scalar.  Blocks of four waves cover 256
-// nodes of a row, or several rows where a row has fewer; XCD k (blocks b = k mod 8) takes the k-th
-// contiguous eighth of the rows, so that the densities of the rows around a row, which nine rows
-// read, come from one L2.
+// nodes of a row, or several rows where a row has fewer.  With EIGHTHS XCD k (blocks b = k mod 8) takes
+// the k-th contiguous eighth of the rows, so that the densities of the rows around a row, which nine rows
+// read, come from one L2; see by_eighths.
 struct Row {
     int x, y, z;
     bool in;
 };
 
+template <bool EIGHTHS>
 __device__ __forceinline__ Row row_of(const Chan3& c) {
     const int wpr = min((c.nx + 63) / 64, kThreads / 64), per_block = kThreads / 64 / wpr;   // waves a row, rows a block
     const int segs = (c.nx + kThreads - 1) / kThreads;
     const int nb = gridDim.x, blk = blockIdx.x, xcd = blk & 7, per = nb >> 3, rem = nb & 7;
-    const int b = xcd * per + min(xcd, rem) + (blk >> 3);
+    const int b = EIGHTHS ? xcd * per + min(xcd, rem) + (blk >> 3) : blk;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t row = (uint32_t)(b / segs) * per_block + wave / wpr, rows = (uint32_t)c.ny * (uint32_t)c.nz;   // < 2^32
     Row r;
@@ -193,10 +194,10 @@ __device__ __forceinline__ Row row_of(const Chan3& c) {
 
 __device__ __forceinline__ int64_t row_at(const Chan3& c, int y, int z) { return ((int64_t)z * c.ny + y) * c.pitch; }
 
-template <bool WIDE>
+template <bool WIDE, bool EIGHTHS>
 __global__ void __launch_bounds__(kThreads)
 k3_density(const Chan3 c, float* __restrict__ ws, int src) {
-    const Row r = row_of(c);
+    const Row r = row_of<EIGHTHS>(c);
     if (!r.in) return;
     const uint32_t code = solid_code(c, r.x, r.y, r.z);
     float* __restrict__ dn = ws + c.off + 76 * c.plane + row_at(c, r.y, r.z);
@@ -291,10 +292,10 @@ __device__ __forceinline__ void collide(const Chan3& c, const float* f, float nA
           __builtin_fmaf(c.tm[1], aB[2], U[2]), c.omega[1], out, 19);
 }
 
-template <bool WIDE, bool NT>
+template <bool WIDE, bool NT, bool EIGHTHS>
 __global__ void __launch_bounds__(kThreads)
 k3_collide(const Chan3 c, float* __restrict__ ws, int src) {
-    const Row r = row_of(c);
+    const Row r = row_of<EIGHTHS>(c);
     if (!r.in) return;
     const int x = r.x, y = r.y, z = r.z;
     const uint32_t code = solid_code(c, x, y, z);
@@ -661,9 +662,18 @@ bool streams(const Chan3& c) { return (int64_t)304 * c.nx * c.ny * c.nz > ((int6
 
 bool wide(const Chan3& c) { return !fused_fits(c.plane); }
 
+// Rows by XCD eighths (row_of), or all XCDs side by side: then the z planes around a row are still in the
+// last-level cache that the XCDs share, where eighths keep eight sets of planes there (us per step,
+// eighths and side by side: 96 x 24 x 24 11.0 and 12.9, 256 x 128 x 64 187 and 193, 300 x 120 x 90 384 and
+// 399, 500 x 60 x 182 519 and 503, 512 x 182 x 182 1593 and 1528, 512 x 340 x 340 5640 and 5440).
+// Boxes of 64-bit addresses count as past the line.
+bool by_eighths(const Chan3& c) { return (int64_t)c.nx * c.ny * c.nz < 4000000; }
+
 void density(const Chan3& h, float* ws, int src, hipStream_t s) {
-    if (wide(h)) hipLaunchKernelGGL(k3_density<true>, dim3(row_blocks(h)), dim3(kThreads), 0, s, h, ws, src);
-    else hipLaunchKernelGGL(k3_density<false>, dim3(row_blocks(h)), dim3(kThreads), 0, s, h, ws, src);
+    const dim3 grid(row_blocks(h)), block(kThreads);
+    if (wide(h)) hipLaunchKernelGGL((k3_density<true, false>), grid, block, 0, s, h, ws, src);
+    else if (by_eighths(h)) hipLaunchKernelGGL((k3_density<false, true>), grid, block, 0, s, h, ws, src);
+    else hipLaunchKernelGGL((k3_density<false, false>), grid, block, 0, s, h, ws, src);
 }
 
 int64_t walk_tiles(const Chan3& c, int bx, int bz, int cy) {
@@ -691,9 +701,10 @@ hipError_t launch_step(const Chan3& h, float* ws, int src, hipStream_t s) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 grid(row_blocks(h)), block(kThreads);
-    if (wide(h)) hipLaunchKernelGGL((k3_collide<true, true>), grid, block, 0, s, h, ws, src);
-    else if (streams(h)) hipLaunchKernelGGL((k3_collide<false, true>), grid, block, 0, s, h, ws, src);
-    else hipLaunchKernelGGL((k3_collide<false, false>), grid, block, 0, s, h, ws, src);
+    if (wide(h)) hipLaunchKernelGGL((k3_collide<true, true, false>), grid, block, 0, s, h, ws, src);
+    else if (!by_eighths(h)) hipLaunchKernelGGL((k3_collide<false, true, false>), grid, block, 0, s, h, ws, src);
+    else if (streams(h)) hipLaunchKernelGGL((k3_collide<false, true, true>), grid, block, 0, s, h, ws, src);
+    else hipLaunchKernelGGL((k3_collide<false, false, true>), grid, block, 0, s, h, ws, src);
     return hipGetLastError();
 }
 
@@ -730,7 +741,7 @@ hipError_t launch_step_fused(const Chan3& h, float* ws, int src, int cy, int cus
 
 // A walk's iteration takes about 16 us at full CUs and the two kernels 95 ps per node (LLC-resident
 // boxes 80): 96 x 24 x 24 11.7 us per step with two kernels, 27 with the walk at its best; 256 x 128
-// x 64 188 and 203; 300 x 120 x 90 377 and 280; 512 x 182 x 182 1628 and 1183.  Returns the rows per
+// x 64 188 and 203; 300 x 120 x 90 384 and 273; 512 x 182 x 182 1528 and 1168.  Returns the rows per
 // tile, 0 for the two kernels.
 int best_schedule(const Chan3& h, int cus) {
     if (wide(h)) return 0;
