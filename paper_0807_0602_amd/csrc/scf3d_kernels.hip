@@ -732,6 +732,10 @@ hipError_t launch_step_fused(const Chan3& h, float* ws, int src, int cy, int cus
     int best = 0;
     for (int k = 1; k < 3; ++k)
         if (walk_cost(h, kWalks[k], cy, cus) < walk_cost(h, kWalks[best], cy, cus)) best = k;
+    // so few tiles that a CU gets one of 128 x 4 at most: these have half the threads, and an iteration of
+    // one alone is shorter (300 x 120 x 90 in 60 rows 444 us for 575 with 256 x 4, 40 x 100 x 30 in 4 rows 33
+    // for 50, 512 x 8 x 8 in single rows 17 for 22)
+    if (walk_tiles(h, 128, 4, cy) <= cus) best = 1;
     switch (best) {
         case 0: return launch_walk<256, 4>(h, ws, src, cy, s);
         case 1: return launch_walk<128, 4>(h, ws, src, cy, s);
