@@ -517,14 +517,13 @@ struct Engine {
         return region_pick(&r, &k) || pipe_pays(bxv);
     }
 
-    void plan_regions(std::vector<scf::TileDesc>& tl, std::vector<scf::TileDesc>& walk) {
-        region_k = 0;
-        if (!region_pick(&region, &region_k)) return;
-        tl.clear();
-        for (int k = 1; k <= region_k; ++k) {
-            const int ox = scf::region_out_x(region, k), oy = scf::region_out_y(region, k);
-            region_first[k] = (int)(walk.size() + tl.size());
-            region_tiles[k] = (int)region_count(region, k);
+    // Tiles of 1 .. k steps per launch in regions `rg`, one list after the other (a single channel's
+    // follow from the block index).
+    void plan_regions(int rg, int k, std::vector<scf::TileDesc>& tl, int* tiles, int* first) const {
+        for (int i = 1; i <= k; ++i) {
+            const int ox = scf::region_out_x(rg, i), oy = scf::region_out_y(rg, i);
+            first[i] = (int)tl.size();
+            tiles[i] = (int)region_count(rg, i);
             if (nchan == 1) continue;
             for (int c = 0; c < nchan; ++c)
                 for (int y = 0; y < geom[c].ny; y += oy)
@@ -537,8 +536,6 @@ struct Engine {
                         tl.push_back(td);
                     }
         }
-        if ((int64_t)walk.size() + (int64_t)tl.size() > lay.max_tiles) region_k = 0;
-        else walk.insert(walk.end(), tl.begin(), tl.end());
     }
 
     // Blocks of a persistent launch: every CU filled to the kernel's occupancy (a multiple of 8
@@ -558,54 +555,50 @@ struct Engine {
     static int strip2(int bxv) { return bxv == 512 ? 480 : bxv == 256 ? 224 : bxv - 6; }
 
     int upload_tiles(int bxv, int cyv, int ord) {
+        int rg = 0, rk = 0, rtiles[scf::kRegionMaxSteps + 1] = {}, rfirst[scf::kRegionMaxSteps + 1] = {};
+        bool pp = false;
+        if (!walk_forced(bxv, ord) && !region_pick(&rg, &rk)) pp = pipe_pays(bxv);
         std::vector<scf::TileDesc> tl, tl2;
         std::vector<int32_t> f1, f2;
         int g1 = 0, g2 = 0;
+        const bool walk = !rk && !pp;   // the list of two-step tiles is planned where it is run
         if (ord & SCF_ORDER_PERSIST) {
             g1 = persist_blocks(bxv, 1, ord);
             g2 = persist_blocks(bxv, 2, ord);
             if (!g1 || !g2) return fail(SCF_EDEVICE, "occupancy query for the persistent schedule failed");
             make_tiles_persist(bxv, 2, g1, ord, tl, f1);
-            make_tiles_persist(strip2(bxv), 6, g2, ord, tl2, f2);
+            if (walk) make_tiles_persist(strip2(bxv), 6, g2, ord, tl2, f2);
         } else {
             tl = make_tiles(bxv, cyv, ord);
-            tl2 = make_tiles(strip2(bxv), cyv, ord);
+            if (walk) tl2 = make_tiles(strip2(bxv), cyv, ord);
         }
-        int n2 = (int)tl2.size();
-        region_k = 0;
-        pipe = false;
-        if (!walk_forced(bxv, ord)) {
-            std::vector<scf::TileDesc> more;
-            plan_regions(more, tl2);
-            if (!region_k && pipe_pays(bxv)) {
-                std::vector<int32_t> f;
-                make_tiles_pipe(pipe_strip(), cus, more, f);
-                pipe = (int)more.size() <= lay.max_tiles;
-                if (pipe) {
-                    tl2 = more;
-                    n2 = (int)tl2.size();
-                    f2 = f;
-                }
-            }
-        }
+        if (rk) plan_regions(rg, rk, tl2, rtiles, rfirst);
+        if (pp) make_tiles_pipe(pipe_strip(), cus, tl2, f2);
+        // (regions: at most four lists of 4 x CUs; runs of strips: a tile per strip and one per block)
         if ((int)tl.size() > lay.max_tiles || (int)tl2.size() > lay.max_tiles)
             return fail(SCF_EINVAL, "tile list exceeds its reserved space");
         HIP_TRY(hipMemcpyAsync(d_tiles(), tl.data(), sizeof(scf::TileDesc) * tl.size(),
                                hipMemcpyHostToDevice, stream));
-        HIP_TRY(hipMemcpyAsync(d_tiles2(), tl2.data(), sizeof(scf::TileDesc) * tl2.size(),
-                               hipMemcpyHostToDevice, stream));
+        if (!tl2.empty())
+            HIP_TRY(hipMemcpyAsync(d_tiles2(), tl2.data(), sizeof(scf::TileDesc) * tl2.size(),
+                                   hipMemcpyHostToDevice, stream));
         if (!f1.empty())
             HIP_TRY(hipMemcpyAsync(d_first(), f1.data(), sizeof(int32_t) * f1.size(), hipMemcpyHostToDevice, stream));
         if (!f2.empty())
             HIP_TRY(hipMemcpyAsync(d_first2(), f2.data(), sizeof(int32_t) * f2.size(), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         ntiles = (int)tl.size();
-        ntiles2 = n2;
+        ntiles2 = (int)tl2.size();
         grid1 = g1;
         grid2 = g2;
         bx = bxv;
         cy = cyv;
         order = ord;
+        region = rg;
+        region_k = rk;
+        std::copy(rtiles, rtiles + scf::kRegionMaxSteps + 1, region_tiles);
+        std::copy(rfirst, rfirst + scf::kRegionMaxSteps + 1, region_first);
+        pipe = pp;
         return SCF_OK;
     }
 
