@@ -190,7 +190,10 @@ struct Engine {
     // steps per launch of the node-parallel step (0: the row-walking kernels run), its region and,
     // per step count, its tiles (in d_tiles2() from entry region_first when nchan > 1)
     int region_k = 0, region = 0;
-    bool pipe = false;   // the two-step list holds the tiles of the pipelined step, which runs instead
+    // the pipelined step runs, its tiles and offsets behind those of the walk, which is kept for a
+    // remainder of two steps (walk_two) or not there
+    bool pipe = false, walk_two = false;
+    int pipe_tile = 0, pipe_block = 0;
     int region_tiles[scf::kRegionMaxSteps + 1] = {}, region_first[scf::kRegionMaxSteps + 1] = {};
     float tuned_ms = 0.0f;   // time per step of the last autotuned schedule
     hipGraphExec_t g_steps[2] = {nullptr, nullptr};
@@ -452,6 +455,22 @@ struct Engine {
                scf::kPipeCols * (rows + kPipeLead * strips) < 2.0 * walk;
     }
 
+    // Two steps at the end of a count are a launch of the pipelined step like three or four, or one of the
+    // walk, if its tiles are wide, past the last-level cache and in the lowest boxes (us for two steps, walk
+    // and pipelined: 100000 x 12 56 and 58, 4096 x 640 99 and 98, 2000 x 2000 145 and 161, 8192 x 512 153 and
+    // 153, 16384 x 512 280 and 307, 16384 x 1024 542 and 594; 65536 x 160 398 and 371; with 128 columns per
+    // tile 16384 x 1024 711 and 593).
+    bool walk_for_two(int bxv) const {
+        double nodes = 0.0, rows = 0.0, strips = 0.0;
+        for (const scf_geometry& g : geom) {
+            const double n = (g.nx + kPipeWide - 1) / kPipeWide;
+            nodes += (double)g.nx * g.ny;
+            rows += n * g.ny;
+            strips += n;
+        }
+        return bxv >= 256 && (nodes > 3.5e6 || rows < kPipeLead * strips);
+    }
+
     // Strips of 240 columns, or of 224, whose edges fall on 128-byte lines.  A line that two strips
     // share is written by both; where the neighbour strip is high it comes to it after the line has
     // left the caches (us per step with 240 and with 224: 16384 x 1024 166 and 158, 16384 x 512 87 and
@@ -558,10 +577,11 @@ struct Engine {
         int rg = 0, rk = 0, rtiles[scf::kRegionMaxSteps + 1] = {}, rfirst[scf::kRegionMaxSteps + 1] = {};
         bool pp = false;
         if (!walk_forced(bxv, ord) && !region_pick(&rg, &rk)) pp = pipe_pays(bxv);
-        std::vector<scf::TileDesc> tl, tl2;
-        std::vector<int32_t> f1, f2;
+        std::vector<scf::TileDesc> tl, tl2, more;
+        std::vector<int32_t> f1, f2, fp;
         int g1 = 0, g2 = 0;
-        const bool walk = !rk && !pp;   // the list of two-step tiles is planned where it is run
+        // the walk's own list of two-step tiles, where it runs
+        bool walk = !rk && (!pp || walk_for_two(bxv));
         if (ord & SCF_ORDER_PERSIST) {
             g1 = persist_blocks(bxv, 1, ord);
             g2 = persist_blocks(bxv, 2, ord);
@@ -573,7 +593,19 @@ struct Engine {
             if (walk) tl2 = make_tiles(strip2(bxv), cyv, ord);
         }
         if (rk) plan_regions(rg, rk, tl2, rtiles, rfirst);
-        if (pp) make_tiles_pipe(pipe_strip(), cus, tl2, f2);
+        int pt = 0, pb = 0;   // the pipelined step's first tile and offset, behind the walk's
+        if (pp) {
+            make_tiles_pipe(pipe_strip(), cus, more, fp);
+            if (walk && (tl2.size() + more.size() > (size_t)lay.max_tiles || f2.size() + fp.size() > kMaxPersistBlocks + 1)) {
+                walk = false;
+                tl2.clear();
+                f2.clear();
+            }
+            pt = (int)tl2.size();
+            pb = (int)f2.size();
+            tl2.insert(tl2.end(), more.begin(), more.end());
+            f2.insert(f2.end(), fp.begin(), fp.end());
+        }
         // (regions: at most four lists of 4 x CUs; runs of strips: a tile per strip and one per block)
         if ((int)tl.size() > lay.max_tiles || (int)tl2.size() > lay.max_tiles)
             return fail(SCF_EINVAL, "tile list exceeds its reserved space");
@@ -588,7 +620,7 @@ struct Engine {
             HIP_TRY(hipMemcpyAsync(d_first2(), f2.data(), sizeof(int32_t) * f2.size(), hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         ntiles = (int)tl.size();
-        ntiles2 = (int)tl2.size();
+        ntiles2 = pp ? pt : (int)tl2.size();
         grid1 = g1;
         grid2 = g2;
         bx = bxv;
@@ -599,6 +631,9 @@ struct Engine {
         std::copy(rtiles, rtiles + scf::kRegionMaxSteps + 1, region_tiles);
         std::copy(rfirst, rfirst + scf::kRegionMaxSteps + 1, region_first);
         pipe = pp;
+        pipe_tile = pt;
+        pipe_block = pb;
+        walk_two = pp && walk;
         return SCF_OK;
     }
 
@@ -617,8 +652,9 @@ struct Engine {
             return scf::launch_step_region(region, k, any_masked, chans[0], d_chans(),
                                            nchan == 1 ? nullptr : d_tiles2() + region_first[k], region_tiles[k], base(),
                                            src, s);
-        if (k >= 2 && pipe)
-            return scf::launch_step_pipe(k, any_masked, d_chans(), d_tiles2(), d_first2(), cus, base(), src, s);
+        if (k >= 2 && pipe && !(k == 2 && walk_two))
+            return scf::launch_step_pipe(k, any_masked, d_chans(), d_tiles2() + pipe_tile, d_first2() + pipe_block, cus,
+                                         base(), src, s);
         if (k == 2)
             return scf::launch_step_fused2(bx, any_masked, d_chans(), d_tiles2(), ntiles2, p ? d_first2() : nullptr,
                                            grid2, base(), src, s);
