@@ -221,6 +221,13 @@ struct scf_sur {
         return e == hipSuccess ? shadows(s) : e;
     }
 
+    // Normalised inputs, targets and weights of `rows` rows: drawn from the n stored ones or the staged batch.
+    hipError_t gather(bool stored, int64_t n, int rows, hipStream_t s) const {
+        return scf::sur::gather(at<float>(stored ? p.Xd : p.Xs), at<float>(stored ? p.Td : p.Ts),
+                                at<float>(stored ? p.wd : p.wsb), n, cfg.d_in, rows, at<float>(p.mean), at<float>(p.stdv),
+                                at<float>(p.Xn), at<float>(p.Tb), at<float>(p.wbb), stored, cfg.seed, step(), s);
+    }
+
     // Forward, backward and (update) Adam on `rows` rows of the staged batch or, with `stored`, on a
     // random minibatch of the stored set; the gradient into grad otherwise.
     hipError_t train_step(int rows, bool stored, float inv_n, bool update, hipStream_t s) const {
@@ -242,17 +249,15 @@ struct scf_sur {
             return scf::sur::train_pass(b, cfg.d_in, cfg.width, cfg.depth, rows, inv_n, at<float>(p.mean),
                                         at<float>(p.stdv), wk, st, update, cus, s);
         }
-        hipError_t e = scf::sur::gather(at<float>(stored ? p.Xd : p.Xs), at<float>(stored ? p.Td : p.Ts),
-                                        at<float>(stored ? p.wd : p.wsb), stored ? n_data : rows, cfg.d_in, rows,
-                                        at<float>(p.mean), at<float>(p.stdv), at<float>(p.Xn), at<float>(p.Tb),
-                                        at<float>(p.wbb), stored, cfg.seed, step(), s);
+        // a staged batch has been gathered by stage()
+        hipError_t e = stored ? gather(true, n_data, rows, s) : hipSuccess;
         if (e == hipSuccess) e = pass(rows, true, inv_n, s);
         if (e == hipSuccess && update) e = adam_and_shadows(s);
         return e;
     }
 
     // Copy an explicit batch (host, n rows) into the staging area, padded to a multiple of 64
-    // rows with zero-weight rows.
+    // rows with zero-weight rows; for the layer kernels also gather it, ahead of the wait.
     int stage(const float* X, const float* T, const float* w, int n, int* rows_out) {
         const int rows = (n + 63) / 64 * 64;
         if (n < 1 || rows > cfg.max_batch) return set_error(SCF_EINVAL, "batch must have 1..max_batch rows");
@@ -264,6 +269,7 @@ struct scf_sur {
         SUR_TRY(hipMemcpyAsync(at<float>(p.Xs), x.data(), sizeof(float) * x.size(), hipMemcpyHostToDevice, stream));
         SUR_TRY(hipMemcpyAsync(at<float>(p.Ts), t.data(), sizeof(float) * t.size(), hipMemcpyHostToDevice, stream));
         SUR_TRY(hipMemcpyAsync(at<float>(p.wsb), ww.data(), sizeof(float) * ww.size(), hipMemcpyHostToDevice, stream));
+        if (!scf::sur::train_fits(cfg.width, cfg.depth)) SUR_TRY(gather(false, rows, rows, stream));
         SUR_TRY(hipStreamSynchronize(stream));   // the host vectors go out of scope
         *rows_out = rows;
         return SCF_OK;
@@ -516,8 +522,6 @@ int scf_sur_predict(scf_sur* s, const float* X, int64_t n, float* Y, uint8_t* in
         int rows = 0;
         int rc = s->stage(X + r0 * din, nullptr, nullptr, m, &rows);
         if (rc) return rc;
-        SUR_TRY(scf::sur::normalise(s->at<float>(s->p.Xs), rows, din, rows, s->at<float>(s->p.mean),
-                                    s->at<float>(s->p.stdv), s->at<float>(s->p.Xn), s->stream));
         SUR_TRY(s->pass(rows, false, 1.0f, s->stream));
         SUR_TRY(hipMemcpyAsync(Y + 2 * r0, s->at<float>(s->p.Y), sizeof(float) * 2 * m, hipMemcpyDeviceToHost, s->stream));
         if (in_hull) {
