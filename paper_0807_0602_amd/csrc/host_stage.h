@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include <cstring>
 #include <mutex>
 
 namespace scf {
@@ -109,6 +110,32 @@ public:
     }
     void done() { idle = true; }
 };
+
+// FP64 fields of up to kWidenBytes each come as FP32, half the bytes, into the upper halves of the
+// caller's arrays and are widened there in place; larger ones come as they are (two fields, us in FP32 and
+// in FP64, into arrays in use and into fresh pages: 90000 nodes 81 and 96, 359 and 406; 819200 610 and 766,
+// 3230 and 3890; 2621440 2200 and 2415, 11260 and 12540; 5242880 4820 and 4920, 23700 and 25200; 16777216
+// 16060 and 15580, 78100 and 81680).
+constexpr size_t kWidenBytes = (size_t)40 << 20;
+
+// a[i] = the i-th of the n FP32 values in the upper half of a, for every i.  In order and eight at a time:
+// what is written ends before the values that are still to be read.
+inline void widen(double* a, size_t n) {
+    const char* f = reinterpret_cast<const char*>(a) + sizeof(float) * n;
+    size_t i = 0;
+    for (; i + 8 <= n; i += 8) {
+        float v[8];
+        double d[8];
+        std::memcpy(v, f + sizeof(float) * i, sizeof v);
+        for (int j = 0; j < 8; ++j) d[j] = v[j];
+        std::memcpy(a + i, d, sizeof d);
+    }
+    for (; i < n; ++i) {
+        float v;
+        std::memcpy(&v, f + sizeof(float) * i, sizeof v);
+        a[i] = v;
+    }
+}
 
 // A context's part: threads may read from one context, so a read-out holds `mu` from its launch to the
 // end of its host copy, whether it goes through a buffer or through the idle population buffer or

@@ -49,8 +49,9 @@ hipError_t launch_step_fused(const Chan3& h, float* ws, int src, int cy, int cus
 int best_schedule(const Chan3& h, int cus);
 hipError_t launch_observe(const Chan3& h, const Chan3* c, float* ws, int src, Part3* parts, Obs3* out,
                           hipStream_t s);
-// The density field of the last launch_observe in FP64 (n_A, n_B, nz x ny x nx each, unpadded).
+// The density field of the last launch_observe (n_A, n_B, nz x ny x nx each, unpadded).
 hipError_t launch_density_out(const Chan3& h, const float* ws, double* out, hipStream_t s);
+hipError_t launch_density_out(const Chan3& h, const float* ws, float* out, hipStream_t s);
 hipError_t launch_pull_out(const Chan3& h, const Chan3* c, float* ws, int src, hipStream_t s);
 
 }  // namespace scf3

@@ -634,12 +634,14 @@ k3_obs_final(const Chan3* __restrict__ cp, const float* __restrict__ ws, const P
     }
 }
 
-// The density field in FP64 without padding into `out` (n_A, then n_B), as the caller's arrays have it.
+// The density field without padding into `out` (n_A, then n_B): FP64 as the caller's arrays have it, or
+// FP32 for half the way to the host.
+template <class T>
 __global__ void __launch_bounds__(kThreads)
-k3_density_out(Chan3 c, const float* __restrict__ ws, double* __restrict__ out) {
+k3_density_out(Chan3 c, const float* __restrict__ ws, T* __restrict__ out) {
     const int64_t row = (int64_t)blockIdx.y * c.ny + blockIdx.x, cells = (int64_t)c.nx * c.ny * c.nz;
     const float* __restrict__ n = ws + c.off + 76 * c.plane + row * c.pitch;
-    double* o = out + row * c.nx;
+    T* o = out + row * c.nx;
     for (int x = threadIdx.x; x < c.nx; x += kThreads) {
         o[x] = n[x];
         o[cells + x] = n[c.plane + x];
@@ -778,7 +780,12 @@ hipError_t launch_observe(const Chan3& h, const Chan3* c, float* ws, int src, Pa
 }
 
 hipError_t launch_density_out(const Chan3& h, const float* ws, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k3_density_out, dim3(h.ny, h.nz), dim3(kThreads), 0, s, h, ws, out);
+    hipLaunchKernelGGL(k3_density_out<double>, dim3(h.ny, h.nz), dim3(kThreads), 0, s, h, ws, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_density_out(const Chan3& h, const float* ws, float* out, hipStream_t s) {
+    hipLaunchKernelGGL(k3_density_out<float>, dim3(h.ny, h.nz), dim3(kThreads), 0, s, h, ws, out);
     return hipGetLastError();
 }
 

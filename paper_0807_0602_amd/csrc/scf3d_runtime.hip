@@ -218,24 +218,28 @@ int scf3_get_density(scf3_ctx* c, double* nA, double* nB) {
     scf3_obs o;
     int rc = observe_held(c, &o);   // also refreshes the density field
     if (rc && rc != SCF_EUNSTABLE) return rc;
-    // converted and compacted on the device: a small field straight into page-locked memory, others into
-    // the idle population buffer (the next step overwrites it) and copied from there
+    // compacted on the device: a small field in FP64 straight into page-locked memory, others into the idle
+    // population buffer (the next step overwrites it) and copied from there, middle-sized ones in FP32
     const scf3::Chan3& h = c->chan;
     const size_t cells = (size_t)h.nx * h.ny * h.nz;
     scf::StageLease buf(2 * sizeof(double) * cells, c->stream);
-    const bool staged = buf.p != nullptr;
-    double* f = staged ? reinterpret_cast<double*>(buf.p)
-                       : reinterpret_cast<double*>(c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane);
-    HIP_TRY3(scf3::launch_density_out(h, c->base(), f, c->stream));
-    if (!staged) {
-        HIP_TRY3(hipMemcpyAsync(nA, f, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY3(hipMemcpyAsync(nB, f + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, c->stream));
+    const bool half = !buf.p && sizeof(double) * cells <= scf::kWidenBytes;
+    char* f = buf.p ? buf.p : reinterpret_cast<char*>(c->base() + h.off + (size_t)(c->cur ^ 1) * 38 * h.plane);
+    const size_t bytes = (half ? sizeof(float) : sizeof(double)) * cells, up = sizeof(double) * cells - bytes;
+    if (half) HIP_TRY3(scf3::launch_density_out(h, c->base(), reinterpret_cast<float*>(f), c->stream));
+    else HIP_TRY3(scf3::launch_density_out(h, c->base(), reinterpret_cast<double*>(f), c->stream));
+    if (!buf.p) {
+        HIP_TRY3(hipMemcpyAsync(reinterpret_cast<char*>(nA) + up, f, bytes, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY3(hipMemcpyAsync(reinterpret_cast<char*>(nB) + up, f + bytes, bytes, hipMemcpyDeviceToHost, c->stream));
     }
     HIP_TRY3(hipStreamSynchronize(c->stream));
     buf.done();
-    if (staged) {
-        std::memcpy(nA, f, sizeof(double) * cells);
-        std::memcpy(nB, f + cells, sizeof(double) * cells);
+    if (buf.p) {
+        std::memcpy(nA, f, bytes);
+        std::memcpy(nB, f + bytes, bytes);
+    } else if (half) {
+        scf::widen(nA, cells);
+        scf::widen(nB, cells);
     }
     return SCF_OK;
 }

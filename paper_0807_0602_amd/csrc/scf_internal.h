@@ -95,8 +95,9 @@ hipError_t launch_step_two_kernel(const Chan* chans, const RowRef* rows, int nro
 hipError_t launch_observe(const Chan* chans, const RowRef* rows, int nrows, int nchan, float* ws,
                           int src, RowPartial* partials, ObsRec* now, ObsRec* ring,
                           int32_t* counter, int max_samples, int record, hipStream_t s);
-// FP64 densities of channel ch (n_A, n_B, ny x nx each, unpadded) into `out`.
+// Densities of channel ch (n_A, n_B, ny x nx each, unpadded) into `out`.
 hipError_t launch_density_out(const Chan* chans, int ch, int ny, const float* ws, int src, double* out, hipStream_t s);
+hipError_t launch_density_out(const Chan* chans, int ch, int ny, const float* ws, int src, float* out, hipStream_t s);
 // The first `have` (>= 1) records of every channel's ring, packed into `out`.
 hipError_t launch_pack_ring(const ObsRec* ring, int nchan, int max_samples, int have, ObsRec* out, hipStream_t s);
 hipError_t launch_pull_out(const Chan* chans, const RowRef* rows, int nrows, float* ws, int src,

@@ -1096,22 +1096,23 @@ k_pull_out(const Chan* __restrict__ chans, const RowRef* __restrict__ rows, floa
     }
 }
 
-// Densities of channel `ch` in FP64 into `out` (n_A, then n_B, ny rows of nx values without padding),
-// as the caller's arrays have them: the host then only copies.  One row per block, memory bound
-// (16384 x 1024: 0.31 ms, 4.7 TB/s); with FP32 rows converted on the host that read-out took 50 ms,
-// now 27, which is the copy into fresh pageable arrays.
+// Densities of channel `ch` into `out` (n_A, then n_B, ny rows of nx values without padding), as the
+// caller's FP64 arrays have them, or in FP32 for half the way to the host (see kWidenBytes).  One row per
+// block, memory bound (16384 x 1024 in FP64: 0.31 ms, 4.7 TB/s); with FP32 rows and their padding converted
+// on the host that read-out took 50 ms, now 27, which is the copy into fresh pageable arrays.
+template <class T>
 __global__ void __launch_bounds__(kRowThreads)
-k_density_out(const Chan* __restrict__ chans, int ch, const float* __restrict__ ws, int src, double* __restrict__ out) {
+k_density_out(const Chan* __restrict__ chans, int ch, const float* __restrict__ ws, int src, T* __restrict__ out) {
     const Chan c = chans[ch];
     const float* __restrict__ g = ws + c.off + (int64_t)src * 18 * c.plane;
     const int y = blockIdx.x;
-    double* oA = out + (int64_t)y * c.nx;
-    double* oB = oA + (int64_t)c.nx * c.ny;
+    T* oA = out + (int64_t)y * c.nx;
+    T* oB = oA + (int64_t)c.nx * c.ny;
     for (int x = threadIdx.x; x < c.nx; x += kRowThreads) {
         float p[18];
         const bool solid = pull_node(g, c, ws, x, y, p) & 1u;
-        oA[x] = solid ? 0.0 : (double)sum9(p);
-        oB[x] = solid ? 0.0 : (double)sum9(p + 9);
+        oA[x] = solid ? T(0) : (T)sum9(p);
+        oB[x] = solid ? T(0) : (T)sum9(p + 9);
     }
 }
 
@@ -1483,7 +1484,12 @@ hipError_t launch_observe(const Chan* chans, const RowRef* rows, int nrows, int 
 }
 
 hipError_t launch_density_out(const Chan* chans, int ch, int ny, const float* ws, int src, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_density_out, dim3(ny), dim3(kRowThreads), 0, s, chans, ch, ws, src, out);
+    hipLaunchKernelGGL(k_density_out<double>, dim3(ny), dim3(kRowThreads), 0, s, chans, ch, ws, src, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_density_out(const Chan* chans, int ch, int ny, const float* ws, int src, float* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_density_out<float>, dim3(ny), dim3(kRowThreads), 0, s, chans, ch, ws, src, out);
     return hipGetLastError();
 }
 

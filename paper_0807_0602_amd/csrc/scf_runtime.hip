@@ -1006,26 +1006,30 @@ struct Engine {
         return SCF_OK;
     }
 
-    // Converted and compacted on the device: small fields straight into page-locked memory, others
-    // into the idle population buffer (the next step overwrites it) and copied from there.
+    // Compacted on the device: small fields in FP64 straight into page-locked memory, others into the idle
+    // population buffer (the next step overwrites it) and copied from there, middle-sized ones in FP32.
     int get_density(int c, double* nA, double* nB) {
         if (c < 0 || c >= nchan || !nA || !nB) return fail(SCF_EINVAL, "bad channel or NULL output");
         const size_t cells = (size_t)geom[c].nx * geom[c].ny;
         const std::lock_guard<std::mutex> hold(stage.mu);
         scf::StageLease buf(2 * sizeof(double) * cells, stream);
-        const bool staged = buf.p != nullptr;
-        double* out = reinterpret_cast<double*>(
-            staged ? buf.p : ws + lay.chan_off[c] + sizeof(float) * (size_t)(cur ^ 1) * 18 * chans[c].plane);
-        HIP_TRY(scf::launch_density_out(d_chans(), c, geom[c].ny, base(), cur, out, stream));
-        if (!staged) {
-            HIP_TRY(hipMemcpyAsync(nA, out, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
-            HIP_TRY(hipMemcpyAsync(nB, out + cells, sizeof(double) * cells, hipMemcpyDeviceToHost, stream));
+        const bool half = !buf.p && sizeof(double) * cells <= scf::kWidenBytes;
+        char* out = buf.p ? buf.p : ws + lay.chan_off[c] + sizeof(float) * (size_t)(cur ^ 1) * 18 * chans[c].plane;
+        const size_t bytes = (half ? sizeof(float) : sizeof(double)) * cells, up = sizeof(double) * cells - bytes;
+        if (half) HIP_TRY(scf::launch_density_out(d_chans(), c, geom[c].ny, base(), cur, reinterpret_cast<float*>(out), stream));
+        else HIP_TRY(scf::launch_density_out(d_chans(), c, geom[c].ny, base(), cur, reinterpret_cast<double*>(out), stream));
+        if (!buf.p) {
+            HIP_TRY(hipMemcpyAsync(reinterpret_cast<char*>(nA) + up, out, bytes, hipMemcpyDeviceToHost, stream));
+            HIP_TRY(hipMemcpyAsync(reinterpret_cast<char*>(nB) + up, out + bytes, bytes, hipMemcpyDeviceToHost, stream));
         }
         HIP_TRY(hipStreamSynchronize(stream));
         buf.done();
-        if (staged) {
-            std::memcpy(nA, out, sizeof(double) * cells);
-            std::memcpy(nB, out + cells, sizeof(double) * cells);
+        if (buf.p) {
+            std::memcpy(nA, out, bytes);
+            std::memcpy(nB, out + bytes, bytes);
+        } else if (half) {
+            scf::widen(nA, cells);
+            scf::widen(nB, cells);
         }
         return SCF_OK;
     }
