@@ -448,7 +448,7 @@ def duct3d(args) -> int:
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "traffic_gbs": round(traffic / step_s / 1e9, 1) if traffic else None,
                      "traffic_frac": round(traffic / step_s / 1e9 / HBM_PEAK_GBS, 4) if traffic else None,
-                     "kernel": ("k3_fused, %d rows of y per tile" % sched["cy"]) if fused
+                     "kernel": ("k3_fused, %s rows of y per tile" % ("default" if sched["cy"] == 16 else sched["cy"])) if fused
                      else "k3_density + k3_collide", "bytes_per_node_update": bpl,
                      "event_ms_per_step": round(step_s * 1e3, 5)},
         "health": {"flags": obs["flags"], "z": obs["z"], "mass": list(obs["mass"])},
@@ -553,7 +553,8 @@ def main() -> int:
     ap.add_argument("--workload", choices=["roofline", "sweep", "surrogate", "duct3d", "small", "washburn"],
                     default="roofline")
     ap.add_argument("--cy3", type=int, default=16,
-                    help="duct3d: rows of y per tile of the fused 3-D step; 0 = the two-kernel step")
+                    help="duct3d: rows of y per tile of the fused 3-D step, 16 = the default schedule, which "
+                         "chooses them for the box; 0 = the two-kernel step")
     ap.add_argument("--weights", default=os.path.join(ROOT, "paper_0807_0602_amd", "surrogate_weights_5in.npz"))
     ap.add_argument("--summarize-counters", nargs=4, default=None,
                     metavar=("FETCH_CSV", "WRITE_CSV", "FETCH_COPY_CSV", "WRITE_COPY_CSV"),

@@ -352,10 +352,11 @@ k3_collide(const Chan3 c, float* __restrict__ ws, int src) {
 // A wave's 64 nodes lie on one row (y, z), so the row offsets of a pull, its periodic wraps and the
 // wall tests of its rows are scalar; per lane there are three byte offsets (x - 1, x, x + 1).  The
 // ring's z rows are pulled by waves 0 .. 2 BX / 64 - 1, its x columns and corners by the next wave.
-// Bound by the lines that reach L2 from beyond it (about 5.6 TB/s): the node's own 304 bytes, the
-// z rows and x columns of the ring.  Two slices of populations take 76 registers; the rest fits into
-// 128, which lets 16 waves share a CU (157 registers and three blocks of 64 x 4 before: 1.52 ms per
-// step of 512 x 182 x 182, 11.2 GLUPS; now 1.18 ms, 14.3).
+// What it waits for are the lines that reach L2 from beyond it: the node's own 304 bytes, the z rows and
+// x columns of the ring, 352 bytes per node at 5.1 TB/s with the 23 rows per tile that 512 x 182 x 182
+// takes (501 at 5.6 on the former 64 x 4 tiles).  Two slices of populations take 76 registers; the rest
+// fits into 128 but for one (64 x 8: three), which lets 16 waves share a CU (157 registers and three
+// blocks of 64 x 4 before: 1.52 ms per step of 512 x 182 x 182, 11.2 GLUPS; now 1.17 ms, 14.5).
 // ---------------------------------------------------------------------------------------------
 // A value the compiler may not reason about: keeps what is derived from it inside the loop, where
 // recomputing it costs a few instructions and holding it a register for the whole walk.

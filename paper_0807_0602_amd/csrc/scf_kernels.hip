@@ -680,10 +680,12 @@ k_step_fused2(const Chan* __restrict__ chans, const TileDesc* __restrict__ tiles
 // drain.  All columns compute alike, those whose neighbours are not there included: what they get
 // wrong spreads two columns per step and stays within the halo.
 //
-// Bound by memory at 16384 x 1024, 172 bytes per node and pass at 4.5 TB/s (a plain copy reaches
-// 4.7), and next to it by its vector arithmetic, 245 instructions per node and step: an iteration of
-// 1.93 us there, 1.45 in boxes that fit the last-level cache.  us per step against the two-step walk
-// (159 bytes, 4.9 TB/s): 157 for 272; K = 3 209, K = 2 298.  One code path per role: with the roles
+// In boxes that fit the last-level cache an iteration takes 1.45 us and the vector units are busy 88 % of
+// its cycles, 245 instructions per node and step; at 16384 x 1024 1.93 us, 172 bytes per node and pass at
+// 4.5 TB/s.  That is no ceiling: the single step moves 5.6 TB/s, with more rows in flight than the one
+// per block here.  us per step against the two-step walk (159 bytes, 4.9 TB/s): 157 to 164 in runs of
+// hundreds of steps (167 to 179 over the first twenty), for 272; K = 3 209, K = 2 298 (where two steps
+// are left over and the walk is faster, see walk_for_two).  One code path per role: with the roles
 // decided per row, copies and waits for loads just issued took it to 222.  Strips start on 128-byte
 // lines: shifted by 16 columns the pulls span fewer lines, but two strips write the shared ones (181).
 // ---------------------------------------------------------------------------------------------
@@ -868,9 +870,9 @@ k_step_pipe(const Chan* __restrict__ chans, const TileDesc* __restrict__ tiles, 
 //
 // Bound by the latency of one launch and of K stages in small boxes (about 4 us and 1 us a stage
 // at one wave per SIMD, 2 us at four) and by its vector arithmetic, halo included, in larger ones.
-// Measured, us per step, against the row-walking kernels with their best schedule: 200 x 24 2.1
-// (9.1), 1200 x 42 3.3 (7.3), 2048 x 130 6.9 (10.7), 4096 x 202 15.8 (16.9), 8192 x 202 27.9
-// (26.6).  Tiles dealt to the XCDs in contiguous eighths against block order: 2048 x 130 6.7 for
+// Measured, us per step, against the two-step walk with its best schedule: 200 x 24 2.1 (9.1), 1200 x 42
+// 3.3 (7.3), 2048 x 130 6.9 (10.7); from about 4096 x 202 on (14.4) the pipelined step is as fast (14.1).
+// Tiles dealt to the XCDs in contiguous eighths against block order: 2048 x 130 6.7 for
 // 8.4.  A 16 x 16 region (256 lanes, K = 3) measured within 5 % of 22 x 23 with K = 4; wider than
 // high regions (38 x 26, 64 x 16) were slower at every size.
 // ---------------------------------------------------------------------------------------------

@@ -177,9 +177,9 @@ struct Engine {
     int cur = 0;
     int64_t t = 0;
     int variant = SCF_VARIANT_FUSED;
-    // default schedule: the one the autotuner picks for the 16384 x 1024 capillary (two steps
-    // per launch, 256-wide blocks on 224-column strips, persistent strip-aligned bands dealt to
-    // the XCDs in eighths)
+    // default schedule: several steps per launch.  The tiles (256-wide blocks on 224-column strips,
+    // persistent strip-aligned bands dealt to the XCDs in eighths) are those of the two-step walk, whose
+    // place the node-parallel or the pipelined step takes in most boxes (region_pick, pipe_pays)
     int bx = 256, cy = 16, order = SCF_ORDER_PERSIST | SCF_ORDER_XCD, graph_steps = 64, fuse = 2;
     int ntiles = 0, ntiles2 = 0;
     // blocks of the single-step and two-step launches under a persistent schedule (0: one

@@ -36,7 +36,8 @@ struct TrainState {
 };
 
 // Networks whose training step is train_pass (two launches): a block's waves own 16 units each and
-// keep every layer's silu' in registers, which ends at 256 units (1024 threads) and four layers.
+// keep every layer's silu' in registers, which ends at 256 units (1024 threads) and four layers (some
+// of those spill).
 // Others take the layer kernels.
 inline bool train_fits(int width, int depth) { return (width == 128 || width == 256) && depth >= 2 && depth <= 4; }
 // Forward, loss and backward over `rows` (a multiple of 64) rows, then one Adam update (update) or

@@ -612,7 +612,8 @@ k_predict(const float* __restrict__ X, int64_t n, int d_in, int depth, const flo
 
 // ---------------------------------------------------------------------------------------------
 // A training step in two launches.  k_train_rows takes 16 or 32 rows through the forward pass, the loss
-// and the backward pass, keeping silu'(z) of every layer in registers; it writes what the weight
+// and the backward pass, keeping silu'(z) of every layer in registers (at 256 x 4, the most it takes, 30
+// of the 128 spill with 32 rows per block and 3 with 16; elsewhere none); it writes what the weight
 // gradients read: both transposed BF16 operands of every hidden layer, the FP32 dz of every layer
 // and the last activations.  k_train_grads reduces them over the batch, one block per 32 x 32 tile
 // of a hidden matrix or 16 columns of a sum, and applies Adam to what it has just summed (or
